@@ -5,9 +5,6 @@
 //    fused Lanczos epilogue (w -= beta_{j-1} v_{j-1}; alpha_j and y_j partials).
 //  * gaussian / copy_start : start vectors of Eqs. (E-1-1), (E-1-2) and their norms.
 //  * update : u = w - alpha_j v_j, beta_j = |u| (Lanczos recursion of Sec. 2.3).
-//  * tridiag : Krylov eigenpairs by implicit QL (Bowdler, Martin, Reinsch and
-//    Wilkinson, Numer. Math. 11 (1968)) tracking two rows of the eigenvector
-//    matrix.
 //  * boltzmann : the sums of Eqs. (E-2-C) and (E-2-D) in log-sum-exp form.
 //
 // Every reduction is a fixed-order tree (wave shuffles, LDS, then one block that
@@ -2459,138 +2456,6 @@ int launch_zero_state(double *scale_max, int *done, int *n_used, unsigned *count
   const int n = K > n_counters ? K : n_counters;
   hipLaunchKernelGGL(zero_state_kernel, dim3((n + 255) / 256), dim3(256), 0, s, scale_max, done,
                      n_used, counters, n_counters, K);
-  return hipGetLastError() == hipSuccess ? FTLM_OK : FTLM_EHIP;
-}
-
-// ------------------------------------------------------------------ tridiagonal
-// Implicit QL with shifts on T = tridiag(alpha, beta) (n <= n_lanczos), one
-// thread per column; Z = product of the plane rotations, of which only the rows
-// e_1^T Z (-> Q_1n) and y^T Z (-> sum_a y_a Q_an) are carried along.
-// Scratch layout [4][n_lanczos][n_cols].
-// LDS: the four work arrays of the block's columns live in LDS ([4][nl][blockDim]),
-// else in the global scratch ([4][nl][n_cols]).
-template <bool LDS>
-__global__ void tridiag_kernel(int n_cols, int nl, const int *n_used, int used_stride,
-                               int in_stride, const double *alpha, const double *beta, const double *y,
-                               double *eps, double *q1, double *qy, int out_stride, int out_col0,
-                               double *scratch) {
-  extern __shared__ double tri_sh[];
-  const int col = blockIdx.x * blockDim.x + threadIdx.x;
-  if (col >= n_cols) return;
-  const int n = n_used ? n_used[col * used_stride] : nl;
-  const size_t S = LDS ? (size_t)blockDim.x : (size_t)n_cols;
-  double *base = LDS ? tri_sh + threadIdx.x : scratch + col;
-  double *d = base;
-  double *e = base + (size_t)nl * S;
-  double *z1 = base + 2 * (size_t)nl * S;
-  double *zy = base + 3 * (size_t)nl * S;
-#define AT(p, i) (p)[(size_t)(i)*S]
-  for (int i = 0; i < n; i++) {
-    AT(d, i) = alpha[(size_t)i * in_stride + col];
-    AT(e, i) = (i + 1 < n) ? beta[(size_t)i * in_stride + col] : 0.0;
-    AT(z1, i) = (i == 0) ? 1.0 : 0.0;
-    AT(zy, i) = y ? y[(size_t)i * in_stride + col] : 0.0;
-  }
-  for (int l = 0; l < n; l++) {
-    int iter = 0;
-    while (true) {
-      int m = l;
-      {
-        double dm = AT(d, l);
-        for (; m < n - 1; m++) {
-          const double dm1 = AT(d, m + 1);
-          const double dd = fabs(dm) + fabs(dm1);
-          if (fabs(AT(e, m)) <= 2.220446049250313e-16 * dd) break;
-          dm = dm1;
-        }
-      }
-      if (m == l || iter++ >= 100) break;
-      double gg = (AT(d, l + 1) - AT(d, l)) / (2.0 * AT(e, l));
-      double r = hypot(gg, 1.0);
-      gg = AT(d, m) - AT(d, l) + AT(e, l) / (gg + copysign(r, gg));
-      double s = 1.0, c = 1.0, p = 0.0;
-      int i = m - 1;
-      bool underflow = false;
-      // A step at i reads e[i], d[i], d[i+1] and rows i, i+1 of the tracked Z
-      // rows and writes indices i+1 and i only, so the next step's reads (index
-      // i-1) are issued one step ahead, d[i+1] is the previous step's d[i], and
-      // the rotated Z entries of index i stay in registers for the next step.
-      double d_hi = AT(d, m), z1_hi = AT(z1, m), zy_hi = AT(zy, m);
-      double e_i = AT(e, m - 1), d_i = AT(d, m - 1), z1_i = AT(z1, m - 1), zy_i = AT(zy, m - 1);
-      for (; i >= l; i--) {
-        double e_n = 0.0, d_n = 0.0, z1_n = 0.0, zy_n = 0.0;
-        if (i > l) {
-          e_n = AT(e, i - 1);
-          d_n = AT(d, i - 1);
-          z1_n = AT(z1, i - 1);
-          zy_n = AT(zy, i - 1);
-        }
-        const double f = s * e_i, b = c * e_i;
-        r = hypot(f, gg);
-        AT(e, i + 1) = r;
-        if (r == 0.0) {
-          AT(d, i + 1) = d_hi - p;
-          AT(e, m) = 0.0;
-          AT(z1, i + 1) = z1_hi;
-          AT(zy, i + 1) = zy_hi;
-          underflow = true;
-          break;
-        }
-        s = f / r;
-        c = gg / r;
-        gg = d_hi - p;
-        r = (d_i - gg) * s + 2.0 * c * b;
-        p = s * r;
-        AT(d, i + 1) = gg + p;
-        gg = c * r - b;
-        // rotate columns i, i+1 of Z in the two tracked rows
-        const double z1_lo = c * z1_i - s * z1_hi;
-        AT(z1, i + 1) = s * z1_i + c * z1_hi;
-        z1_hi = z1_lo;
-        const double zy_lo = c * zy_i - s * zy_hi;
-        AT(zy, i + 1) = s * zy_i + c * zy_hi;
-        zy_hi = zy_lo;
-        d_hi = d_i;
-        e_i = e_n;
-        d_i = d_n;
-        z1_i = z1_n;
-        zy_i = zy_n;
-      }
-      if (underflow) continue;
-      AT(z1, l) = z1_hi;
-      AT(zy, l) = zy_hi;
-      AT(d, l) -= p;
-      AT(e, l) = gg;
-      AT(e, m) = 0.0;
-    }
-  }
-  const size_t os = (size_t)out_stride;
-  for (int i = 0; i < nl; i++) {
-    const bool ok = i < n;
-    eps[(size_t)i * os + out_col0 + col] = ok ? AT(d, i) : 0.0;
-    q1[(size_t)i * os + out_col0 + col] = ok ? AT(z1, i) : 0.0;
-    qy[(size_t)i * os + out_col0 + col] = ok ? AT(zy, i) : 0.0;
-  }
-#undef AT
-}
-
-int launch_tridiag(int n_cols, int n_lanczos, const int *n_used, int used_stride, int in_stride,
-                   const double *alpha, const double *beta, const double *y, double *eps,
-                   double *q1, double *qy, int out_stride, int out_col0, double *scratch,
-                   hipStream_t s) {
-  // 64 KB of LDS per block: as many columns as fit (at most 64), else global scratch
-  const int per_col = 32 * n_lanczos;  // bytes of the four work arrays
-  int cpb = per_col > 0 ? 65536 / per_col : 0;
-  if (cpb > 64) cpb = 64;
-  if (cpb >= 1) {
-    hipLaunchKernelGGL(tridiag_kernel<true>, dim3((n_cols + cpb - 1) / cpb), dim3(cpb),
-                       (size_t)cpb * per_col, s, n_cols, n_lanczos, n_used, used_stride, in_stride,
-                       alpha, beta, y, eps, q1, qy, out_stride, out_col0, scratch);
-  } else {
-    hipLaunchKernelGGL(tridiag_kernel<false>, dim3((n_cols + 63) / 64), dim3(64), 0, s, n_cols,
-                       n_lanczos, n_used, used_stride, in_stride, alpha, beta, y, eps, q1, qy,
-                       out_stride, out_col0, scratch);
-  }
   return hipGetLastError() == hipSuccess ? FTLM_OK : FTLM_EHIP;
 }
 

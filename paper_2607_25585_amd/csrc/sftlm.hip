@@ -104,96 +104,6 @@ __global__ void gram_reduce_kernel(const double2 *__restrict__ part, int nsplit,
   ok[idx] = make_double2(r, i);
 }
 
-// Implicit QL with shifts (Bowdler, Martin, Reinsch and Wilkinson, Numer. Math.
-// 11 (1968)) on T = tridiag(alpha[0..n), beta[0..n-1)), one block per column;
-// thread 0 runs each sweep's scalar recurrence and records its plane rotations,
-// then every thread applies them to its rows of the full eigenvector matrix Z
-// (LDS, column-major Z[i][a]).  Output: eps[n], Q[a][m] = Z (row-major, nl x nl),
-// zero beyond n.
-__global__ void tridiag_full_kernel(int nl, const int *__restrict__ n_used, const double *__restrict__ alpha,
-                                    const double *__restrict__ beta, double *__restrict__ eps,
-                                    double *__restrict__ Qout) {
-  extern __shared__ double sh[];
-  double *d = sh, *e = d + nl, *rc = e + nl, *rs = rc + nl, *Z = rs + nl;  // Z: [nl][nl]
-  __shared__ int s_lo, s_hi, s_done;
-  const int t = threadIdx.x;
-  const int n = n_used ? *n_used : nl;
-  for (int i = t; i < nl; i += blockDim.x) {
-    d[i] = i < n ? alpha[i] : 0.0;
-    e[i] = (i + 1 < n) ? beta[i] : 0.0;
-  }
-  for (int idx = t; idx < nl * nl; idx += blockDim.x) Z[idx] = (idx / nl == idx % nl) ? 1.0 : 0.0;
-  __syncthreads();
-  for (int l = 0; l < n; l++) {
-    int iter = 0;
-    while (true) {
-      if (t == 0) {
-        s_done = 0;
-        int m = l;
-        for (; m < n - 1; m++) {
-          const double dd = fabs(d[m]) + fabs(d[m + 1]);
-          if (fabs(e[m]) <= 2.220446049250313e-16 * dd) break;
-        }
-        if (m == l || iter >= 100) {
-          s_done = 1;
-        } else {
-          double gg = (d[l + 1] - d[l]) / (2.0 * e[l]);
-          double r = hypot(gg, 1.0);
-          gg = d[m] - d[l] + e[l] / (gg + copysign(r, gg));
-          double s = 1.0, c = 1.0, p = 0.0;
-          int i = m - 1;
-          bool underflow = false;
-          for (; i >= l; i--) {
-            const double f = s * e[i], b = c * e[i];
-            r = hypot(f, gg);
-            e[i + 1] = r;
-            if (r == 0.0) {
-              d[i + 1] -= p;
-              e[m] = 0.0;
-              underflow = true;
-              break;
-            }
-            s = f / r;
-            c = gg / r;
-            gg = d[i + 1] - p;
-            r = (d[i] - gg) * s + 2.0 * c * b;
-            p = s * r;
-            d[i + 1] = gg + p;
-            gg = c * r - b;
-            rc[i] = c;
-            rs[i] = s;
-          }
-          s_hi = m - 1;
-          s_lo = underflow ? i + 1 : l;
-          if (!underflow) {
-            d[l] -= p;
-            e[l] = gg;
-            e[m] = 0.0;
-          }
-        }
-      }
-      __syncthreads();
-      if (s_done) break;
-      iter++;
-      const int lo = s_lo, hi = s_hi;
-      for (int a = t; a < nl; a += blockDim.x)
-        for (int i = hi; i >= lo; i--) {
-          const double c = rc[i], s = rs[i];
-          const double fz = Z[(i + 1) * nl + a];
-          Z[(i + 1) * nl + a] = s * Z[i * nl + a] + c * fz;
-          Z[i * nl + a] = c * Z[i * nl + a] - s * fz;
-        }
-      __syncthreads();
-    }
-    __syncthreads();
-  }
-  for (int i = t; i < nl; i += blockDim.x) eps[i] = i < n ? d[i] : 0.0;
-  for (int idx = t; idx < nl * nl; idx += blockDim.x) {
-    const int a = idx / nl, m = idx % nl;  // Q[a][m] = Z column m, row a
-    Qout[idx] = (a < n && m < n) ? Z[m * nl + a] : 0.0;
-  }
-}
-
 // One block per temperature: ln Z, E, C and the symmetric M over the R vectors
 // of one field.  eps [R][nl], Q [R][nl][nl], OK [R][nl][nl] (complex), n_used [R].
 __global__ __launch_bounds__(256) void sftlm_boltzmann_kernel(int R, int nl, const int *__restrict__ n_used,
@@ -341,8 +251,6 @@ T *at2(void *ws, size_t off) {
   return reinterpret_cast<T *>(reinterpret_cast<char *>(ws) + off);
 }
 
-size_t tridiag_full_smem(int nl) { return sizeof(double) * ((size_t)4 * nl + (size_t)nl * nl); }
-
 int validate_sftlm(const ftlm_hamiltonian *h, const ftlm_run_params *p, std::string &err) {
   if (!p) { err = "params is NULL"; return FTLM_EINVAL; }
   if (p->R < 2 || (p->R & 1)) { err = "R must be even and >= 2 (time-reversed pairs)"; return FTLM_EINVAL; }
@@ -419,15 +327,6 @@ int ftlm_run_sftlm(const ftlm_hamiltonian *hc, const ftlm_run_params *p, void *w
   const size_t vbytes = (size_t)pl.dim * pl.es;
   char *V = at2<char>(ws, pl.V), *Wb = at2<char>(ws, pl.W);
   const int NL = pl.NL;
-  const size_t tsm = tridiag_full_smem(NL);
-  {
-    static size_t granted = 0;
-    if (tsm > granted) {
-      (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&tridiag_full_kernel),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)tsm);
-      granted = tsm;
-    }
-  }
   const uint32_t tgrid = (uint32_t)std::min<uint64_t>(4096, (pl.dim + 255) / 256);
   for (int f = 0; f < pl.nF; f++) {
     if (p->fields) {
@@ -520,10 +419,9 @@ int ftlm_run_sftlm(const ftlm_hamiltonian *hc, const ftlm_run_params *p, void *w
       double2 *okr = at2<double2>(ws, pl.OK) + (size_t)r * NL * NL;
       hipLaunchKernelGGL(gram_reduce_kernel, dim3((NL * NL + 255) / 256), dim3(256), 0, s, gpart, pl.nsplit, NL, okr);
       // full eigenpairs of the tridiagonal
-      hipLaunchKernelGGL(tridiag_full_kernel, dim3(1), dim3(std::min(256, ((NL + 63) / 64) * 64)), tsm, s, NL,
-                         at2<int>(ws, pl.nused), at2<double>(ws, pl.alpha), at2<double>(ws, pl.beta),
-                         at2<double>(ws, pl.eps) + (size_t)r * NL, at2<double>(ws, pl.Q) + (size_t)r * NL * NL);
-      if (hipGetLastError() != hipSuccess) return fail(FTLM_EHIP, "sFTLM kernel launch failed");
+      if (launch_tridiag_full(1, NL, at2<int>(ws, pl.nused), at2<double>(ws, pl.alpha), at2<double>(ws, pl.beta), 1,
+                              at2<double>(ws, pl.eps) + (size_t)r * NL, at2<double>(ws, pl.Q) + (size_t)r * NL * NL, s))
+        return fail(FTLM_EHIP, "sFTLM kernel launch failed");
       if (hipMemcpyAsync(at2<int>(ws, pl.nused_all) + (size_t)f * pl.R + r, at2<int>(ws, pl.nused), sizeof(int),
                          hipMemcpyDeviceToDevice, s) != hipSuccess)
         return fail(FTLM_EHIP, "copy of n_used failed");
