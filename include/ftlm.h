@@ -210,7 +210,9 @@ int ftlm_run(const ftlm_hamiltonian *h, const ftlm_run_params *p, void *workspac
  * sum of Eq. (E-2-H) over the Krylov eigenpairs, O = -sum_i g_i s_i.B_hat; ln Z,
  * E and C as ftlm_run.  Uses p->R, n_lanczos (<= 140), seed, instance, T, n_T,
  * fields, n_fields, precision; columns is ignored and r_init must be NULL.
- * Workspace: (2 N_L + 1) vectors plus O(R N_L^2) doubles; no allocation.
+ * Workspace: (2 N_L + 1) vectors for each of the random vectors that iterate
+ * together (one for dim >= 2^20 or where a second one's basis would pass 1 GiB,
+ * else up to 64) plus O(R N_L^2) doubles; no allocation.
  * Blocks on the stream before returning. */
 int ftlm_run_sftlm_workspace_size(const ftlm_hamiltonian *h, const ftlm_run_params *p, size_t *bytes);
 int ftlm_run_sftlm(const ftlm_hamiltonian *h, const ftlm_run_params *p, void *workspace,

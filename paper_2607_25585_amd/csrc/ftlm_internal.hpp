@@ -358,11 +358,12 @@ int launch_tridiag(int n_cols, int n_lanczos, const int *n_used, int used_stride
                    const double *alpha, const double *beta, const double *y, double *eps,
                    double *q1, double *qy, int out_stride, int out_col0, double *scratch,
                    hipStream_t s);
-// Full eigenpairs of n_cols tridiagonals (element j of column c at [j * in_stride + c]):
-// eps[c][n_lanczos], Q[c][n_lanczos][n_lanczos].  LDS bytes it needs at least:
+// Full eigenpairs of n_cols tridiagonals in groups of `group` interleaved columns
+// (element j of column c at (c / group) nl group + j group + c % group):
+// eps[c][nl], Qt[c][m][a] = Q[a][m].  LDS bytes it needs at least:
 size_t tridiag_full_smem(int nl);
 int launch_tridiag_full(int n_cols, int n_lanczos, const int *n_used, const double *alpha, const double *beta,
-                        int in_stride, double *eps, double *Q, hipStream_t s);
+                        int group, double *eps, double *Qt, hipStream_t s);
 int launch_boltzmann(int n_curves, int R, int n_lanczos, const int *n_used, const double *eps,
                      const double *q1, const double *qy, const double *dims, const double *T,
                      int n_T, double *lnZ, double *E, double *C, double *M, double *E_min,

@@ -1,16 +1,16 @@
 // Symmetric FTLM (sFTLM) with pairs of mutually time-reversed random vectors,
 // Sec. 2.2, Eqs. (E-2-G), (E-2-H).
 //
-// For each random vector r (the R vectors are R/2 Gaussian vectors and their
-// time reverses) the host code runs N_L Lanczos steps keeping every Krylov vector
-// (slot j of the workspace holds the unnormalised X_j with scale sx_j), applies
-// O = -sum_i g_i s_i.B_hat to every slot, forms O_K = V^H O V (Gram kernel),
-// and diagonalises the tridiagonal with the full eigenvector matrix Q.  The
-// Boltzmann kernel then evaluates, per temperature,
+// The R vectors (R/2 Gaussian vectors and their time reverses) iterate in waves
+// of K interleaved columns.  A wave runs N_L Lanczos steps keeping every Krylov
+// vector (slot j of the workspace holds the unnormalised X_j [dim][K] with scales
+// sx_j), applies O = -sum_i g_i s_i.B_hat to every slot and forms Re(V^H O V) of
+// every column (Gram kernel).  The tridiagonals of all R vectors are then
+// diagonalised together with the full eigenvector matrices Q, and per temperature
 //   den_r = sum_n exp(-(eps_n - E_min)/T) Q_1n^2                      (Eq. E-2-D)
 //   num_r = z^T Re(O_K) z,  z_a = sum_n Q_an exp(-(eps_n - E_min)/2T) Q_1n
-// (the double sum of Eq. E-2-H written as a quadratic form), and
-//   M = sum_r num_r / sum_r den_r.
+// (the double sum of Eq. E-2-H written as a quadratic form; z is real, so only
+// the real part of O_K enters), and M = sum_r num_r / sum_r den_r.
 // ln Z, E and C come from the Ritz values exactly as in the plain driver.
 //
 // Time reversal in the product basis (Condon-Shortley phases, site 0 fastest):
@@ -36,10 +36,18 @@ struct ThetaGeom {
   int two_s_sum_parity;
 };
 
+// dst [dim][np]: np = 1: the time reverse of src [dim][1]; np = 2 P: columns 2p
+// and 2p + 1 hold src's column p [dim][P] and its time reverse.  The scales of the
+// P source columns are handed on to dst's (np >= 2).
 template <typename R>
-__global__ __launch_bounds__(256) void theta_kernel(ThetaGeom g, const Cx<R> *__restrict__ src,
-                                                    Cx<R> *__restrict__ dst) {
-  for (uint64_t nu = (uint64_t)blockIdx.x * 256 + threadIdx.x; nu < g.dim; nu += (uint64_t)gridDim.x * 256) {
+__global__ __launch_bounds__(256) void theta_kernel(ThetaGeom g, const Cx<R> *__restrict__ src, Cx<R> *__restrict__ dst,
+                                                    int np, const double *__restrict__ sx_src, double *__restrict__ sx) {
+  const int P = np > 1 ? np / 2 : 1;
+  if (np > 1 && blockIdx.x == 0 && (int)threadIdx.x < np) sx[threadIdx.x] = sx_src[threadIdx.x / 2];
+  const uint64_t total = (uint64_t)g.dim * P;
+  for (uint64_t e = (uint64_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (uint64_t)gridDim.x * 256) {
+    const uint64_t nu = e / (unsigned)P;
+    const int p = (int)(e - nu * P);
     uint32_t rem = (uint32_t)nu, dsum = 0;
     for (int k = 0; k < g.n; k++) {
       const uint32_t r = (uint32_t)g.radix[k], q = rem / r;
@@ -47,78 +55,170 @@ __global__ __launch_bounds__(256) void theta_kernel(ThetaGeom g, const Cx<R> *__
       rem = q;
     }
     const bool neg = ((uint32_t)g.two_s_sum_parity + dsum) & 1u;  // parity of sum(2 s_i - d_i)
-    const Cx<R> x = src[nu];
-    dst[g.dim - 1 - nu] = neg ? Cx<R>{-x.re, x.im} : Cx<R>{x.re, -x.im};
+    const Cx<R> x = src[e];
+    const Cx<R> th = neg ? Cx<R>{-x.re, x.im} : Cx<R>{x.re, -x.im};
+    const uint64_t rev = (uint64_t)g.dim - 1 - nu;
+    if (np == 1) {
+      dst[rev] = th;
+    } else {
+      dst[nu * np + 2 * p] = x;
+      dst[rev * np + 2 * p + 1] = th;
+    }
   }
 }
 
-// Partial Gram sums: part[split][a][b] = sx_a sum_{nu in split} conj(X_a[nu]) W_b[nu]
-// for a 16 x 16 tile of (a, b) per block.  X slots at X + a*xstride, W at W + b*xstride.
-constexpr int kGT = 16, kGC = 32;
+// Re(V^H W) of every column of a wave on the matrix cores: with a complex row
+// read as two real ones, Re(conj(x) w) is the real product of length 2 dim, so one
+// 16-byte load per lane feeds two v_mfma_f64_16x16x4f64 (real parts, imaginary
+// parts; complex64 rows are widened first).  A wave owns a 32 x 32 block of (a, b)
+// with a-block <= b-block (Re(V^H O V) is symmetric, the rest is mirrored) over
+// the rows of its split: 4 loads feed 8 MFMAs.  blockIdx.x: block pair, y: column,
+// z: group of 4 splits, one per wave; partial products at part[split][column].
+// 100 x 100 over 7776 rows and 20 columns: 1.14 ms (16 x 16 tiles from LDS with
+// vector FMAs, real and imaginary parts, one column per launch: 20 x 275 us).
+constexpr int kGB = 32;
+typedef double d4 __attribute__((ext_vector_type(4)));
 
 template <typename R>
-__global__ __launch_bounds__(256) void gram_kernel(const Cx<R> *__restrict__ X, const Cx<R> *__restrict__ Wv,
-                                                   size_t xstride, int nl, uint32_t dim, uint32_t chunk,
-                                                   const double *__restrict__ sx, double2 *__restrict__ part) {
-  __shared__ Cx<R> xs[kGT][kGC + 1];
-  __shared__ Cx<R> wsh[kGT][kGC + 1];
-  const int t = threadIdx.x, ta = t / kGT, tb = t % kGT;
-  const int a0 = blockIdx.x * kGT, b0 = blockIdx.y * kGT;
-  // 64-bit bounds: lo + chunk and r0 + kGC may pass 2^32 when dim is near it
-  const uint64_t lo = (uint64_t)blockIdx.z * chunk, hi = min((uint64_t)dim, lo + chunk);
-  double ar = 0, ai = 0;
-  for (uint64_t r0 = lo; r0 < hi; r0 += kGC) {
-    __syncthreads();
-    for (int idx = t; idx < kGT * kGC; idx += 256) {
-      const int q = idx / kGC, k = idx % kGC;
-      const uint64_t row = r0 + k;
-      const bool ok = row < hi;
-      xs[q][k] = (ok && a0 + q < nl) ? X[(size_t)(a0 + q) * xstride + row] : Cx<R>{0, 0};
-      wsh[q][k] = (ok && b0 + q < nl) ? Wv[(size_t)(b0 + q) * xstride + row] : Cx<R>{0, 0};
-    }
-    __syncthreads();
-#pragma unroll 8
-    for (int k = 0; k < kGC; k++) {
-      const Cx<R> x = xs[ta][k], w = wsh[tb][k];
-      ar = fma((double)x.re, (double)w.re, fma((double)x.im, (double)w.im, ar));
-      ai = fma((double)x.re, (double)w.im, fma(-(double)x.im, (double)w.re, ai));
-    }
+__global__ __launch_bounds__(256) void gram_kernel(const Cx<R> *__restrict__ X, const Cx<R> *__restrict__ Wv, int K,
+                                                   int nl, uint32_t dim, uint32_t chunk, int nsplit,
+                                                   const double *__restrict__ sx, int sstride, double *__restrict__ part) {
+  const int lane = threadIdx.x & 63, c = blockIdx.y;
+  const int split = blockIdx.z * 4 + (threadIdx.x >> 6);
+  if (split >= nsplit) return;
+  int bb = 0, ab = blockIdx.x;  // block pair index -> (ab <= bb)
+  while (ab > bb) ab -= ++bb;
+  const uint64_t lo = (uint64_t)split * chunk, hi = min((uint64_t)dim, lo + chunk);
+  const int i = lane & 15, kr = lane >> 4;
+  // slots past the last one read the last one; their products are not stored
+  const Cx<R> *xa[2], *wb[2];
+#pragma unroll
+  for (int u = 0; u < 2; u++) {
+    xa[u] = X + (size_t)min(ab * kGB + 16 * u + i, nl - 1) * dim * K + c;
+    wb[u] = Wv + (size_t)min(bb * kGB + 16 * u + i, nl - 1) * dim * K + c;
   }
-  const int a = a0 + ta, b = b0 + tb;
-  if (a < nl && b < nl) {
-    const double s = sx[a];
-    part[((size_t)blockIdx.z * nl + a) * nl + b] = make_double2(ar * s, ai * s);
+  d4 acc[2][2];
+#pragma unroll
+  for (int u = 0; u < 2; u++)
+#pragma unroll
+    for (int w = 0; w < 2; w++) acc[u][w] = d4{0, 0, 0, 0};
+#pragma unroll 2
+  for (uint64_t r0 = lo; r0 < hi; r0 += 4) {
+    const bool ok = r0 + kr < hi;
+    const size_t o = (size_t)(ok ? r0 + kr : lo) * K;
+    Cx<R> x[2], w[2];
+#pragma unroll
+    for (int u = 0; u < 2; u++) {
+      x[u] = xa[u][o];
+      w[u] = wb[u][o];
+    }
+#pragma unroll
+    for (int u = 0; u < 2; u++)
+      if (!ok) x[u] = w[u] = Cx<R>{0, 0};
+#pragma unroll
+    for (int u = 0; u < 2; u++)
+#pragma unroll
+      for (int q = 0; q < 2; q++) {
+        acc[u][q] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)x[u].re, (double)w[q].re, acc[u][q], 0, 0, 0);
+        acc[u][q] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)x[u].im, (double)w[q].im, acc[u][q], 0, 0, 0);
+      }
   }
+  // D of each 16 x 16 tile: row 4 r + lane / 16, column lane % 16
+  double *out = part + ((size_t)split * K + c) * nl * nl;
+#pragma unroll
+  for (int u = 0; u < 2; u++)
+#pragma unroll
+    for (int q = 0; q < 2; q++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        const int a = ab * kGB + 16 * u + 4 * r + kr, b = bb * kGB + 16 * q + i;
+        if (a < nl && b < nl) out[(size_t)a * nl + b] = acc[u][q][r] * sx[(size_t)a * sstride + c];
+      }
 }
 
-// Sums the partials over the splits in split order.
-__global__ void gram_reduce_kernel(const double2 *__restrict__ part, int nsplit, int nl, double2 *__restrict__ ok) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+// Sums the partials over the splits in split order; the blocks below the diagonal
+// are mirrored.
+__global__ void gram_reduce_kernel(const double *__restrict__ part, int nsplit, int nl, int K,
+                                   double *__restrict__ ok) {
+  const int idx = blockIdx.x * blockDim.x + threadIdx.x, c = blockIdx.y;
   if (idx >= nl * nl) return;
-  double r = 0, i = 0;
-  for (int s = 0; s < nsplit; s++) {
-    const double2 v = part[(size_t)s * nl * nl + idx];
-    r += v.x;
-    i += v.y;
+  int a = idx / nl, b = idx % nl;
+  if (a / kGB > b / kGB) {
+    const int t = a;
+    a = b;
+    b = t;
   }
-  ok[idx] = make_double2(r, i);
+  double r = 0;
+  for (int s = 0; s < nsplit; s++) r += part[((size_t)s * K + c) * nl * nl + (size_t)a * nl + b];
+  ok[(size_t)c * nl * nl + idx] = r;
+}
+
+// Lowest Ritz value over a field's vectors (the QL output is unsorted).
+__global__ __launch_bounds__(256) void sftlm_emin_kernel(int R, int nl, const int *__restrict__ n_used,
+                                                         const double *__restrict__ eps, double *E_min) {
+  __shared__ double red[4];
+  double lo = 1e300;
+  for (int k = threadIdx.x; k < R * nl; k += 256)
+    if (k % nl < n_used[k / nl]) lo = fmin(lo, eps[k]);
+  for (int off = 32; off > 0; off >>= 1) lo = fmin(lo, __shfl_xor(lo, off, 64));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = lo;
+  __syncthreads();
+  if (threadIdx.x == 0) *E_min = fmin(fmin(red[0], red[1]), fmin(red[2], red[3]));
+}
+
+// num[it][r] = z^T Re(O_K) z of one (temperature, vector) per block: thread a
+// holds z_a; eigenvectors and O_K's rows (symmetric) are read with the threads
+// along a.
+__global__ __launch_bounds__(192) void sftlm_moment_kernel(int R, int nl, const int *__restrict__ n_used,
+                                                           const double *__restrict__ eps,
+                                                           const double *__restrict__ Qt,
+                                                           const double *__restrict__ OK,
+                                                           const double *__restrict__ T,
+                                                           const double *__restrict__ E_min,
+                                                           double *__restrict__ num) {
+  extern __shared__ double sh[];
+  double *h = sh, *z = h + nl;
+  __shared__ double red[3];
+  const int t = threadIdx.x, r = blockIdx.y, n = n_used[r];
+  const double temp = T[blockIdx.x], emin = *E_min;
+  Qt += (size_t)r * nl * nl;
+  OK += (size_t)r * nl * nl;
+  for (int m = t; m < n; m += 192)
+    h[m] = exp(-(eps[(size_t)r * nl + m] - emin) / (2.0 * temp)) * Qt[(size_t)m * nl];
+  __syncthreads();
+  for (int a = t; a < n; a += 192) {
+    double s = 0;
+#pragma unroll 8
+    for (int m = 0; m < n; m++) s = fma(Qt[(size_t)m * nl + a], h[m], s);
+    z[a] = s;
+  }
+  __syncthreads();
+  double v = 0;
+  for (int a = t; a < n; a += 192) {
+    double s = 0;
+#pragma unroll 8
+    for (int b = 0; b < n; b++) s = fma(OK[(size_t)b * nl + a], z[b], s);
+    v = fma(z[a], s, v);
+  }
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  if ((t & 63) == 0) red[t >> 6] = v;
+  __syncthreads();
+  if (t == 0) num[(size_t)blockIdx.x * R + r] = red[0] + red[1] + red[2];
 }
 
 // One block per temperature: ln Z, E, C and the symmetric M over the R vectors
-// of one field.  eps [R][nl], Q [R][nl][nl], OK [R][nl][nl] (complex), n_used [R].
+// of one field.  eps [R][nl], Qt [R][nl][nl], num [n_T][R], n_used [R].
 __global__ __launch_bounds__(256) void sftlm_boltzmann_kernel(int R, int nl, const int *__restrict__ n_used,
                                                               const double *__restrict__ eps,
-                                                              const double *__restrict__ Q,
-                                                              const double2 *__restrict__ OK,
+                                                              const double *__restrict__ Qt,
+                                                              const double *__restrict__ num,
                                                               const double *__restrict__ dims,
-                                                              const double *__restrict__ T, double *lnZ,
-                                                              double *E, double *C, double *M,
-                                                              double *E_min) {
-  extern __shared__ double sh[];
-  double *h = sh, *z = h + nl;
+                                                              const double *__restrict__ T,
+                                                              const double *__restrict__ E_min, double *lnZ,
+                                                              double *E, double *C, double *M) {
   __shared__ double red[256 / 64];
   const int t = threadIdx.x;
-  const double temp = T[blockIdx.x];
+  const double temp = T[blockIdx.x], emin = *E_min;
   auto block_sum = [&](double v) {
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
     if ((t & 63) == 0) red[t >> 6] = v;
@@ -128,71 +228,42 @@ __global__ __launch_bounds__(256) void sftlm_boltzmann_kernel(int R, int nl, con
     __syncthreads();
     return s;
   };
-  double emin = 1e300;  // lowest Ritz value over all vectors (the QL output is unsorted)
-  for (int r = 0; r < R; r++)
-    for (int m = 0; m < n_used[r]; m++) emin = fmin(emin, eps[(size_t)r * nl + m]);
-  // pass 1: den and the first moment
   double den = 0, e1 = 0;
-  for (int r = 0; r < R; r++) {
-    const int n = n_used[r];
-    for (int m = t; m < n; m += 256) {
-      const double q = Q[((size_t)r * nl) * nl + m];  // Q[r][0][m]
-      const double ev = eps[(size_t)r * nl + m];
-      const double w = exp(-(ev - emin) / temp) * q * q;
-      den += w;
-      e1 += w * ev;
-    }
+  for (int k = t; k < R * nl; k += 256) {
+    if (k % nl >= n_used[k / nl]) continue;
+    const double q = Qt[(size_t)k * nl], ev = eps[k];
+    const double w = exp(-(ev - emin) / temp) * q * q;
+    den += w;
+    e1 += w * ev;
   }
   den = block_sum(den);
   e1 = block_sum(e1);
   const double em = e1 / den;
-  double e2 = 0, num = 0;
-  for (int r = 0; r < R; r++) {
-    const int n = n_used[r];
-    const double *Qr = Q + (size_t)r * nl * nl;
-    const double2 *Or = OK + (size_t)r * nl * nl;
-    for (int m = t; m < nl; m += 256) {
-      double hm = 0;
-      if (m < n) {
-        const double ev = eps[(size_t)r * nl + m];
-        const double q = Qr[m];
-        hm = exp(-(ev - emin) / (2.0 * temp)) * q;
-        e2 += exp(-(ev - emin) / temp) * q * q * (ev - em) * (ev - em);
-      }
-      h[m] = hm;
-    }
-    __syncthreads();
-    for (int a = t; a < nl; a += 256) {
-      double s = 0;
-      for (int m = 0; m < n; m++) s = fma(Qr[(size_t)a * nl + m], h[m], s);
-      z[a] = s;
-    }
-    __syncthreads();
-    for (int a = t; a < n; a += 256) {
-      double s = 0;
-      for (int b = 0; b < n; b++) s = fma(Or[(size_t)a * nl + b].x, z[b], s);
-      num = fma(z[a], s, num);
-    }
-    __syncthreads();
+  double e2 = 0, mm = 0;
+  for (int k = t; k < R * nl; k += 256) {
+    if (k % nl >= n_used[k / nl]) continue;
+    const double q = Qt[(size_t)k * nl], ev = eps[k];
+    e2 += exp(-(ev - emin) / temp) * q * q * (ev - em) * (ev - em);
   }
+  for (int r = t; r < R; r += 256) mm += num[(size_t)blockIdx.x * R + r];
   e2 = block_sum(e2);
-  num = block_sum(num);
+  mm = block_sum(mm);
   if (t == 0) {
     const int k = blockIdx.x;
     lnZ[k] = log(dims[0] / R) - emin / temp + log(den);
     E[k] = em;
     C[k] = e2 / den / (temp * temp);
-    M[k] = num / den;
-    if (k == 0 && E_min) *E_min = emin;
+    M[k] = mm / den;
   }
 }
 
 struct SPlan {
   int R = 0, NL = 0, nT = 0, nF = 0, prec = 0, nsplit = 0;
+  int K = 1, nwave = 0;  // columns per wave (1 or even), waves
   size_t es = 16;
   uint64_t dim = 0;
   size_t V, W, alpha, beta, yre, yim, sx, smax, done, nused, part, counter;
-  size_t gpart, eps, Q, OK, nused_all, T, dims, lnZ, E, C, M, emin;
+  size_t gpart, eps, Q, OK, num, sx0, nused_all, T, dims, lnZ, E, C, M, emin;
   size_t total = 0;
 };
 
@@ -213,27 +284,39 @@ void make_splan(const ftlm_hamiltonian *h, const ftlm_run_params *p, SPlan &pl) 
   pl.prec = p->precision;
   pl.es = p->precision == FTLM_C64 ? 8 : 16;
   pl.dim = h->host.dim;
-  const uint64_t chunk = 4096;
-  pl.nsplit = (int)std::min<uint64_t>(1024, (pl.dim + chunk - 1) / chunk);
-  Carve2 c;
   const size_t vec = (size_t)pl.dim * pl.es;
-  pl.V = c.take(vec * (pl.NL + 1));
-  pl.W = c.take(vec * pl.NL);
-  const size_t sd = sizeof(double);
-  pl.alpha = c.take(sd * pl.NL);
-  pl.beta = c.take(sd * pl.NL);
-  pl.yre = c.take(sd * pl.NL);
-  pl.yim = c.take(sd * pl.NL);
-  pl.sx = c.take(sd * (pl.NL + 1));
-  pl.smax = c.take(sd);
-  pl.done = c.take(sizeof(int));
-  pl.nused = c.take(sizeof(int));
-  pl.part = c.take(sd * 2048 * 3);
+  // Columns per wave: as many vectors together as plain runs take at the
+  // dimension (small vectors are bound by launches and gather latency, which
+  // columns share; one column from 2^20 rows, for the tile kernels), as far as
+  // their Krylov bases fit 1 GiB; whole pairs, or a single vector.
+  const size_t basis = vec * (2 * (size_t)pl.NL + 1);
+  const int want = pl.dim >= (1ull << 20) ? 1 : pl.dim >= (1ull << 17) ? 4 : pl.dim >= (1ull << 14) ? 16 : 64;
+  pl.K = (int)std::min<uint64_t>((uint64_t)std::min(want, pl.R), (1ull << 30) / basis) & ~1;
+  if (pl.K < 2) pl.K = 1;
+  pl.nwave = (pl.R + pl.K - 1) / pl.K;
+  const int nb = (pl.NL + kGB - 1) / kGB, pairs = nb * (nb + 1) / 2 * pl.K;
+  // about 4096 waves for the Gram products, each of at least 64 rows
+  pl.nsplit = (int)std::max<uint64_t>(1, std::min<uint64_t>((4096 + pairs - 1) / pairs, pl.dim / 64));
+  Carve2 c;
+  pl.V = c.take(vec * pl.K * (pl.NL + 1));
+  pl.W = c.take(vec * pl.K * pl.NL);
+  const size_t sd = sizeof(double), sK = sd * pl.K;
+  pl.alpha = c.take(sK * pl.NL * pl.nwave);
+  pl.beta = c.take(sK * pl.NL * pl.nwave);
+  pl.yre = c.take(sK * pl.NL);
+  pl.yim = c.take(sK * pl.NL);
+  pl.sx = c.take(sK * (pl.NL + 1));
+  pl.sx0 = c.take(sK);
+  pl.smax = c.take(sK);
+  pl.done = c.take(sizeof(int) * pl.K);
+  pl.nused = c.take(sizeof(int) * pl.K);
+  pl.part = c.take(sK * 2048 * 3);
   pl.counter = c.take(sizeof(unsigned) * kCounterWords);
-  pl.gpart = c.take(sizeof(double2) * (size_t)pl.nsplit * pl.NL * pl.NL);
+  pl.gpart = c.take(sd * (size_t)pl.nsplit * pl.K * pl.NL * pl.NL);
   pl.eps = c.take(sd * (size_t)pl.R * pl.NL);
   pl.Q = c.take(sd * (size_t)pl.R * pl.NL * pl.NL);
-  pl.OK = c.take(sizeof(double2) * (size_t)pl.R * pl.NL * pl.NL);
+  pl.OK = c.take(sd * (size_t)pl.R * pl.NL * pl.NL);
+  pl.num = c.take(sd * (size_t)pl.R * pl.nT);
   pl.nused_all = c.take(sizeof(int) * (size_t)pl.R * pl.nF);
   pl.T = c.take(sd * pl.nT);
   pl.dims = c.take(sd);
@@ -324,59 +407,67 @@ int ftlm_run_sftlm(const ftlm_hamiltonian *hc, const ftlm_run_params *p, void *w
     ts += h->host.two_s[k];
   }
   tg.two_s_sum_parity = ts & 1;
+  const int NL = pl.NL, Kp = pl.K;
   const size_t vbytes = (size_t)pl.dim * pl.es;
   char *V = at2<char>(ws, pl.V), *Wb = at2<char>(ws, pl.W);
-  const int NL = pl.NL;
   const uint32_t tgrid = (uint32_t)std::min<uint64_t>(4096, (pl.dim + 255) / 256);
+  double *sx = at2<double>(ws, pl.sx), *sx0 = at2<double>(ws, pl.sx0);
   for (int f = 0; f < pl.nF; f++) {
     if (p->fields) {
       rc = ftlm_hamiltonian_set_field(h, p->fields + 3 * f);
       if (rc) return fail(rc, std::string("set_field: ") + ftlm_last_error());
     }
-    for (int r = 0; r < pl.R; r++) {
-      const int pair = r >> 1, rev = r & 1;
+    int *nused_f = at2<int>(ws, pl.nused_all) + (size_t)f * pl.R;
+    for (int wave = 0; wave < pl.nwave; wave++) {
+      const int r0 = wave * Kp, K = std::min(Kp, pl.R - r0);
+      const size_t slot = vbytes * K;  // one Krylov vector of every column, [dim][K]
+      double *alpha = at2<double>(ws, pl.alpha) + (size_t)wave * NL * Kp;
+      double *beta = at2<double>(ws, pl.beta) + (size_t)wave * NL * Kp;
       if (launch_zero_state(at2<double>(ws, pl.smax), at2<int>(ws, pl.done), at2<int>(ws, pl.nused),
-                            at2<unsigned>(ws, pl.counter), kCounterWords, 1, s))
+                            at2<unsigned>(ws, pl.counter), kCounterWords, K, s))
         return fail(FTLM_EHIP, "zero_state launch failed");
-      // start vector: Gaussian (pair index as the vector index) or its time reverse
-      char *dst0 = rev ? V + vbytes : V;
-      rc = launch_gaussian(p->seed, p->instance, (uint32_t)f, (uint32_t)pair, 1, (uint32_t)pl.dim, pl.prec,
-                           dst0, at2<double>(ws, pl.part), at2<unsigned>(ws, pl.counter),
-                           at2<double>(ws, pl.sx), 0, s);
+      // start vectors: the Gaussian vectors of the wave's pairs (pair index as the
+      // vector index) go to slot 1 and from there, each with its time reverse,
+      // to slot 0; a wave of one vector makes either of them
+      const bool pairs = K > 1, direct = !pairs && !(r0 & 1);
+      rc = launch_gaussian(p->seed, p->instance, (uint32_t)f, (uint32_t)(r0 >> 1), pairs ? K / 2 : 1,
+                           (uint32_t)pl.dim, pl.prec, direct ? V : V + slot, at2<double>(ws, pl.part),
+                           at2<unsigned>(ws, pl.counter), pairs ? sx0 : sx, 0, s);
       if (rc) return fail(rc, "start-vector launch failed");
-      if (rev) {
+      if (!direct) {
         if (pl.prec == FTLM_C64)
           hipLaunchKernelGGL(theta_kernel<float>, dim3(tgrid), dim3(256), 0, s, tg,
-                             reinterpret_cast<const Cx<float> *>(V + vbytes), reinterpret_cast<Cx<float> *>(V));
+                             reinterpret_cast<const Cx<float> *>(V + slot), reinterpret_cast<Cx<float> *>(V), K, sx0, sx);
         else
           hipLaunchKernelGGL(theta_kernel<double>, dim3(tgrid), dim3(256), 0, s, tg,
-                             reinterpret_cast<const Cx<double> *>(V + vbytes), reinterpret_cast<Cx<double> *>(V));
+                             reinterpret_cast<const Cx<double> *>(V + slot), reinterpret_cast<Cx<double> *>(V), K, sx0,
+                             sx);
         if (hipGetLastError() != hipSuccess) return fail(FTLM_EHIP, "theta launch failed");
       }
       // Lanczos: X_j in slot j, u_j written into slot j+1
       for (int j = 0; j < NL; j++) {
         EpiLanczos lz{};
-        lz.xprev = j > 0 ? V + (size_t)(j - 1) * vbytes : nullptr;
+        lz.xprev = j > 0 ? V + (size_t)(j - 1) * slot : nullptr;
         lz.ov1 = nullptr;
-        lz.sx_cur = at2<double>(ws, pl.sx) + j;
-        lz.sx_prev = j > 0 ? at2<double>(ws, pl.sx) + (j - 1) : nullptr;
-        lz.beta_prev = j > 0 ? at2<double>(ws, pl.beta) + (j - 1) : nullptr;
+        lz.sx_cur = sx + (size_t)j * Kp;
+        lz.sx_prev = j > 0 ? sx + (size_t)(j - 1) * Kp : nullptr;
+        lz.beta_prev = j > 0 ? beta + (size_t)(j - 1) * Kp : nullptr;
         lz.part = at2<double>(ws, pl.part);
         lz.counter = at2<unsigned>(ws, pl.counter);
-        lz.alpha_out = at2<double>(ws, pl.alpha) + j;
-        lz.yre_out = at2<double>(ws, pl.yre) + j;
-        lz.yim_out = at2<double>(ws, pl.yim) + j;
+        lz.alpha_out = alpha + (size_t)j * Kp;
+        lz.yre_out = at2<double>(ws, pl.yre) + (size_t)j * Kp;
+        lz.yim_out = at2<double>(ws, pl.yim) + (size_t)j * Kp;
         HvLaunch L{};
         L.precision = pl.prec;
-        L.K = 1;
-        L.v = V + (size_t)j * vbytes;
-        L.w = V + (size_t)(j + 1) * vbytes;
+        L.K = K;
+        L.v = V + (size_t)j * slot;
+        L.w = V + (size_t)(j + 1) * slot;
         L.lz = &lz;
         rc = launch_hv(h->dev, L, s);
         if (rc) return fail(rc, "H*v launch failed");
         UpdateArgs u{};
         u.precision = pl.prec;
-        u.K = 1;
+        u.K = K;
         u.step = j;
         u.n_lanczos = NL;
         u.dim = (uint32_t)pl.dim;
@@ -384,8 +475,8 @@ int ftlm_run_sftlm(const ftlm_hamiltonian *hc, const ftlm_run_params *p, void *w
         u.x = L.v;
         u.sx_cur = lz.sx_cur;
         u.alpha = lz.alpha_out;
-        u.beta = at2<double>(ws, pl.beta) + j;
-        u.sx_next = at2<double>(ws, pl.sx) + (j + 1);
+        u.beta = beta + (size_t)j * Kp;
+        u.sx_next = sx + (size_t)(j + 1) * Kp;
         u.scale_max = at2<double>(ws, pl.smax);
         u.done = at2<int>(ws, pl.done);
         u.n_used = at2<int>(ws, pl.nused);
@@ -398,41 +489,45 @@ int ftlm_run_sftlm(const ftlm_hamiltonian *hc, const ftlm_run_params *p, void *w
       for (int b = 0; b < NL; b++) {
         HvLaunch L{};
         L.precision = pl.prec;
-        L.K = 1;
-        L.v = V + (size_t)b * vbytes;
-        L.w = Wb + (size_t)b * vbytes;
-        L.scale = at2<double>(ws, pl.sx) + b;
+        L.K = K;
+        L.v = V + (size_t)b * slot;
+        L.w = Wb + (size_t)b * slot;
+        L.scale = sx + (size_t)b * Kp;
         if (launch_hv(h->mom_dev, L, s)) return fail(FTLM_EHIP, "O V launch failed");
       }
-      // O_K = V^H W
+      // Re(O_K) = Re(V^H W) of every column
       const uint32_t chunk = (uint32_t)((pl.dim + pl.nsplit - 1) / pl.nsplit);
-      const dim3 gg((NL + kGT - 1) / kGT, (NL + kGT - 1) / kGT, pl.nsplit);
-      double2 *gpart = at2<double2>(ws, pl.gpart);
+      const int nb = (NL + kGB - 1) / kGB;
+      const dim3 gg(nb * (nb + 1) / 2, K, (pl.nsplit + 3) / 4);
+      double *gpart = at2<double>(ws, pl.gpart);
       if (pl.prec == FTLM_C64)
         hipLaunchKernelGGL(gram_kernel<float>, gg, dim3(256), 0, s, reinterpret_cast<const Cx<float> *>(V),
-                           reinterpret_cast<const Cx<float> *>(Wb), (size_t)pl.dim, NL, (uint32_t)pl.dim, chunk,
-                           at2<double>(ws, pl.sx), gpart);
+                           reinterpret_cast<const Cx<float> *>(Wb), K, NL, (uint32_t)pl.dim, chunk, pl.nsplit, sx, Kp,
+                           gpart);
       else
         hipLaunchKernelGGL(gram_kernel<double>, gg, dim3(256), 0, s, reinterpret_cast<const Cx<double> *>(V),
-                           reinterpret_cast<const Cx<double> *>(Wb), (size_t)pl.dim, NL, (uint32_t)pl.dim, chunk,
-                           at2<double>(ws, pl.sx), gpart);
-      double2 *okr = at2<double2>(ws, pl.OK) + (size_t)r * NL * NL;
-      hipLaunchKernelGGL(gram_reduce_kernel, dim3((NL * NL + 255) / 256), dim3(256), 0, s, gpart, pl.nsplit, NL, okr);
-      // full eigenpairs of the tridiagonal
-      if (launch_tridiag_full(1, NL, at2<int>(ws, pl.nused), at2<double>(ws, pl.alpha), at2<double>(ws, pl.beta), 1,
-                              at2<double>(ws, pl.eps) + (size_t)r * NL, at2<double>(ws, pl.Q) + (size_t)r * NL * NL, s))
-        return fail(FTLM_EHIP, "sFTLM kernel launch failed");
-      if (hipMemcpyAsync(at2<int>(ws, pl.nused_all) + (size_t)f * pl.R + r, at2<int>(ws, pl.nused), sizeof(int),
-                         hipMemcpyDeviceToDevice, s) != hipSuccess)
+                           reinterpret_cast<const Cx<double> *>(Wb), K, NL, (uint32_t)pl.dim, chunk, pl.nsplit, sx, Kp,
+                           gpart);
+      hipLaunchKernelGGL(gram_reduce_kernel, dim3((NL * NL + 255) / 256, K), dim3(256), 0, s, gpart, pl.nsplit, NL, K,
+                         at2<double>(ws, pl.OK) + (size_t)r0 * NL * NL);
+      if (hipGetLastError() != hipSuccess) return fail(FTLM_EHIP, "sFTLM kernel launch failed");
+      if (hipMemcpyAsync(nused_f + r0, at2<int>(ws, pl.nused), sizeof(int) * K, hipMemcpyDeviceToDevice, s) != hipSuccess)
         return fail(FTLM_EHIP, "copy of n_used failed");
     }
+    // full eigenpairs of every vector's tridiagonal in one launch: they are
+    // serial chains, and side by side they cost one chain
+    double *eps = at2<double>(ws, pl.eps), *Qt = at2<double>(ws, pl.Q), *num = at2<double>(ws, pl.num);
+    if (launch_tridiag_full(pl.R, NL, nused_f, at2<double>(ws, pl.alpha), at2<double>(ws, pl.beta), Kp, eps, Qt, s))
+      return fail(FTLM_EHIP, "tridiagonal launch failed");
     const size_t ro = (size_t)f * pl.nT;
-    const size_t bsm = sizeof(double) * 2 * (size_t)NL;
-    hipLaunchKernelGGL(sftlm_boltzmann_kernel, dim3(pl.nT), dim3(256), bsm, s, pl.R, NL,
-                       at2<int>(ws, pl.nused_all) + (size_t)f * pl.R, at2<double>(ws, pl.eps),
-                       at2<double>(ws, pl.Q), at2<double2>(ws, pl.OK), at2<double>(ws, pl.dims),
-                       at2<double>(ws, pl.T), at2<double>(ws, pl.lnZ) + ro, at2<double>(ws, pl.E) + ro,
-                       at2<double>(ws, pl.C) + ro, at2<double>(ws, pl.M) + ro, at2<double>(ws, pl.emin) + f);
+    const double *Td = at2<double>(ws, pl.T);
+    double *emin = at2<double>(ws, pl.emin) + f;
+    hipLaunchKernelGGL(sftlm_emin_kernel, dim3(1), dim3(256), 0, s, pl.R, NL, nused_f, eps, emin);
+    hipLaunchKernelGGL(sftlm_moment_kernel, dim3(pl.nT, pl.R), dim3(192), sizeof(double) * 2 * (size_t)NL, s, pl.R, NL,
+                       nused_f, eps, Qt, at2<double>(ws, pl.OK), Td, emin, num);
+    hipLaunchKernelGGL(sftlm_boltzmann_kernel, dim3(pl.nT), dim3(256), 0, s, pl.R, NL, nused_f, eps, Qt, num,
+                       at2<double>(ws, pl.dims), Td, emin, at2<double>(ws, pl.lnZ) + ro, at2<double>(ws, pl.E) + ro,
+                       at2<double>(ws, pl.C) + ro, at2<double>(ws, pl.M) + ro);
     if (hipGetLastError() != hipSuccess) return fail(FTLM_EHIP, "sFTLM Boltzmann launch failed");
   }
   const size_t res = sizeof(double) * pl.nT * pl.nF;

@@ -185,35 +185,37 @@ __global__ __launch_bounds__(kWave) void tridiag_kernel(int n_cols, int nl, cons
   }
 }
 
-// One block per column r: alpha, beta [n_lanczos] at r * stride (beta likewise),
-// n_used[r].  Wave 0 runs the sweeps' scalar chain and leaves each sweep's
+// One block per column c: element j of alpha and beta at
+// (c / group) nl group + j group + c % group, n_used[c].  Wave 0 runs the sweeps' scalar chain and leaves each sweep's
 // rotations in LDS; the other waves apply them to their rows of Z (LDS,
 // column-major Z[i][a]) while wave 0 runs the next sweep (nbuf = 2 rotation
 // buffers; nbuf = 1, where LDS holds no second one, takes turns).  Output:
-// eps[r][nl] and Q[r][a][m] (row-major nl x nl), zero beyond n.
+// eps[c][nl] and Qt[c][m][a] = Q[a][m] (one eigenvector after the other), zero
+// beyond n.
 __global__ __launch_bounds__(256) void tridiag_full_kernel(int nl, int nbuf, const int *__restrict__ n_used,
                                                            const double *__restrict__ alpha,
-                                                           const double *__restrict__ beta, int in_stride,
-                                                           double *__restrict__ eps, double *__restrict__ Qout) {
+                                                           const double *__restrict__ beta, int group,
+                                                           double *__restrict__ eps, double *__restrict__ Qt) {
   extern __shared__ double tri_sh[];
   double *d = tri_sh, *e = d + nl, *rot = e + nl, *Z = rot + (size_t)2 * nl * nbuf;  // rot: [nbuf][2][nl]
   __shared__ int s_lo[2], s_hi[2];
   const int t = threadIdx.x, col = blockIdx.x;
   const int n = min(n_used[col], nl);
-  alpha += col;
-  beta += col;
+  const size_t in0 = (size_t)(col / group) * nl * group + col % group;
+  alpha += in0;
+  beta += in0;
   eps += (size_t)col * nl;
-  Qout += (size_t)col * nl * nl;
+  Qt += (size_t)col * nl * nl;
   double big = 0.0;
   for (int i = t & (kWave - 1); i < n; i += kWave) {  // every wave alike
-    big = fmax(big, fabs(alpha[(size_t)i * in_stride]));
-    if (i + 1 < n) big = fmax(big, fabs(beta[(size_t)i * in_stride]));
+    big = fmax(big, fabs(alpha[(size_t)i * group]));
+    if (i + 1 < n) big = fmax(big, fabs(beta[(size_t)i * group]));
   }
   int ex;
   const double sc = norm_scale(wave_max(big), &ex);
   for (int i = t; i < nl; i += blockDim.x) {
-    d[i] = i < n ? alpha[(size_t)i * in_stride] * sc : 0.0;
-    e[i] = (i + 1 < n) ? beta[(size_t)i * in_stride] * sc : 0.0;
+    d[i] = i < n ? alpha[(size_t)i * group] * sc : 0.0;
+    e[i] = (i + 1 < n) ? beta[(size_t)i * group] * sc : 0.0;
   }
   for (int idx = t; idx < nl * nl; idx += blockDim.x) Z[idx] = (idx / nl == idx % nl) ? 1.0 : 0.0;
   __syncthreads();
@@ -260,8 +262,8 @@ __global__ __launch_bounds__(256) void tridiag_full_kernel(int nl, int nbuf, con
   }
   for (int i = t; i < nl; i += blockDim.x) eps[i] = i < n ? ldexp(d[i], ex) : 0.0;
   for (int idx = t; idx < nl * nl; idx += blockDim.x) {
-    const int a = idx / nl, m = idx % nl;  // Q[a][m] = Z column m, row a
-    Qout[idx] = (a < n && m < n) ? Z[(size_t)m * nl + a] : 0.0;
+    const int m = idx / nl, a = idx % nl;
+    Qt[idx] = (a < n && m < n) ? Z[idx] : 0.0;
   }
 }
 
@@ -289,7 +291,7 @@ int launch_tridiag(int n_cols, int n_lanczos, const int *n_used, int used_stride
 size_t tridiag_full_smem(int nl) { return full_smem(nl, 1); }
 
 int launch_tridiag_full(int n_cols, int n_lanczos, const int *n_used, const double *alpha, const double *beta,
-                        int in_stride, double *eps, double *Q, hipStream_t s) {
+                        int group, double *eps, double *Qt, hipStream_t s) {
   constexpr size_t kLds = 160 * 1024 - 64;  // less the static words
   const int nbuf = full_smem(n_lanczos, 2) <= kLds ? 2 : 1;
   const size_t sm = full_smem(n_lanczos, nbuf);
@@ -298,7 +300,7 @@ int launch_tridiag_full(int n_cols, int n_lanczos, const int *n_used, const doub
     return FTLM_EHIP;
   const int threads = kWave + std::min(192, (n_lanczos + kWave - 1) / kWave * kWave);
   hipLaunchKernelGGL(tridiag_full_kernel, dim3(n_cols), dim3(threads), sm, s, n_lanczos, nbuf, n_used, alpha, beta,
-                     in_stride, eps, Q);
+                     group, eps, Qt);
   return hipGetLastError() == hipSuccess ? FTLM_OK : FTLM_EHIP;
 }
 
