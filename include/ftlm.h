@@ -124,8 +124,9 @@ int ftlm_hamiltonian_autotune(ftlm_hamiltonian *h, int32_t precision, int32_t n_
 /* Sets the H*v configuration for (precision, n_cols) directly (e.g. from a cache
  * of earlier autotune results); variant 0 restores the built-in heuristic: for
  * one column of at least 2^20 rows the single-pass tile kernel (variant 6) when
- * the Hamiltonian has no s+- s^z pair pieces, else the LDS tile (spin 1/2, N >=
- * 11) or the windowed passes; below that the direct gather. */
+ * the Hamiltonian has no s+- s^z pair pieces; else, for spin 1/2, the LDS tile
+ * over L2 windows (variant 5) from 2^19 rows and the direct gather below; other
+ * spins the windowed passes from 2^20 rows; otherwise the direct gather. */
 int ftlm_hamiltonian_set_tuning(ftlm_hamiltonian *h, int32_t precision, int32_t n_cols,
                                 int32_t variant, int32_t grid_cap, int32_t kc);
 

@@ -2052,13 +2052,13 @@ static size_t hv_tile_win_smem(const HamGeom &g, const WinPass &W) {
 }
 
 // Threads per tile-window block: 256 G (G groups of rows on one LDS tile).
-// want = 1, 2 or 4 (the tuned choice), else 2 for complex128 (the tile's LDS
-// allows two blocks per CU, so every doubling of G doubles the resident waves
-// up to 8 per SIMD at G = 4) and 1 for complex64 (four 256-thread blocks
-// already fit).
-static int tile_win_groups(int want, bool f32) {
+// want = 1, 2 or 4 (the tuned choice), else 2: the tile's LDS allows two blocks per
+// CU at complex128, so a second group doubles the resident waves.  At complex64
+// four 256-thread blocks fit and G = 1 is faster once there are four tiles per CU
+// (2^21 rows: 143 us against 188; 2^20: 106 against 88).
+static int tile_win_groups(int want, bool f32, uint32_t dim) {
   if (want == 1 || want == 2 || want == 4) return want;
-  return f32 ? 1 : 2;
+  return f32 && dim >= (1u << 21) ? 1 : 2;
 }
 
 template <typename R, int G>
@@ -2079,7 +2079,7 @@ static int launch_tile_win(const DevHam &dh, const DevTables<R> &tb, const WinPl
   const HamGeom &g = dh.geom;
   if (!plan.d_plist || !plan.d_pcoef || plan.passes.empty() || !g.spin_half || g.n <= kTileBits) return FTLM_EINVAL;
   const Cx<R> *pcl = reinterpret_cast<const Cx<R> *>(plan.d_pcoef);
-  const int G = tile_win_groups(groups, sizeof(R) == 4);
+  const int G = tile_win_groups(groups, sizeof(R) == 4, g.dim);
   for (const WinPass &W : plan.passes) {
     const uint64_t items = (uint64_t)W.nwin * W.nin;
     uint32_t gx = (uint32_t)(items < (uint64_t)cap ? items : (uint64_t)cap);
@@ -2110,6 +2110,19 @@ int launch_hv(const DevHam &dh, const HvLaunch &Lin, hipStream_t s) {
   // it beat the multi-pass and tile kernels on every such workload measured
   if (!L.variant && L.K == 1 && dh.geom.dim >= (1u << 20) && (L.precision == FTLM_C64 ? dh.sp32 : dh.sp64).ok)
     L.variant = 6;
+  // spin-1/2 systems with those pieces: the LDS tile kernel over L2 windows from
+  // 2^19 rows, below that the direct gather.  Measured with all pairs coupled
+  // (us, complex128 / complex64):
+  //   rows            2^17       2^18       2^19       2^20       2^22       2^24
+  //   direct gather   29 / 26    49 / 39    96 / 85    181 / 163  882 / 762  4619 / 3633
+  //   LDS tile        98 / 71    120 / 78   142 / 92   159 / 109  792 / 405  3759 / 1850
+  //   over windows    54 / 48    78 / 53    91 / 73    117 / 88   544 / 298  2660 / 1454
+  // (a tile walks its pairs serially, so a vector of few tiles leaves the chip idle)
+  if (!L.variant && L.K == 1 && dh.geom.spin_half) {
+    const WinPlan &tw = L.precision == FTLM_C64 ? dh.tw32 : dh.tw64;
+    if (dh.geom.dim < (1u << 19)) L.variant = 1;
+    else if (!tw.passes.empty()) L.variant = 5;
+  }
   g_variant = L.variant;
   int gx, gy, kc;
   const int rcg = hv_grid_blocks(dh, L, &gx, &gy, &kc);
