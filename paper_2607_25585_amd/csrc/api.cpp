@@ -42,8 +42,29 @@ struct Blob {
 
 template <typename R>
 struct TableOffsets {
-  size_t hdiag, hoff, gp, gm, mval, pij, pc, pzz, zz, czp, czm, pc_half, hflip, cz_half, lowf;
+  size_t hdiag, hoff, gp, gm, mval, pij, pc, pzz, zz, czp, czm, pc_half, hflip, cz_half, lowf, gblob;
+  int n_gpair;
 };
+
+// The general-radix pair terms: every ladder term with a non-zero coefficient, in
+// pair order.
+template <typename R>
+static std::vector<GTerm<R>> gen_terms(const HostHam &hh, const std::vector<int> &perm) {
+  const int n = hh.n;
+  std::vector<GTerm<R>> pair;
+  for (int p : perm) {
+    const int i = hh.pi[p], j = hh.pj[p];
+    for (int q = 0; q < 4; q++) {
+      if (hh.pc[4 * p + q].re == 0.0 && hh.pc[4 * p + q].im == 0.0) continue;
+      const int im = q >> 1, jm = q & 1;  // '-' ladder on site i / j
+      const uint32_t off = (im ? hh.stride[i] : 0u - hh.stride[i]) + (jm ? hh.stride[j] : 0u - hh.stride[j]);
+      pair.push_back(GTerm<R>{{(R)hh.pc[4 * p + q].re, (R)hh.pc[4 * p + q].im}, (int)off, i | j << 8,
+                              16 * (im ? n + i : i), 16 * (jm ? n + j : j)});
+    }
+  }
+  while (pair.empty() || pair.size() % kTermBatch) pair.push_back(GTerm<R>{{0, 0}, 0, 0, 32 * n, 32 * n});
+  return pair;
+}
 
 template <typename R>
 static TableOffsets<R> pack_tables(const HostHam &hh, const std::vector<int> &perm, Blob &b) {
@@ -133,6 +154,33 @@ static TableOffsets<R> pack_tables(const HostHam &hh, const std::vector<int> &pe
   o.hflip = b.add(hflip.data(), hflip.size() * sizeof(Cx<R>));
   o.cz_half = b.add(czh.data(), czh.size() * sizeof(Cx<R>));
   o.lowf = b.add(lowf.data(), lowf.size() * sizeof(Cx<R>));
+  const std::vector<GTerm<R>> pair = gen_terms<R>(hh, perm);
+  const GenBlob<R> L(n, hh.has_z, (int)pair.size());
+  std::vector<unsigned char> blob(L.total, 0);
+  auto put = [&](int at, const void *src, size_t bytes) {
+    if (bytes) std::memcpy(blob.data() + at, src, bytes);
+  };
+  put(L.pair, pair.data(), pair.size() * sizeof(GTerm<R>));
+  put(L.hoff, hoff.data(), hoff.size() * sizeof(Cx<R>));
+  put(L.zz, zz.data(), zz.size() * sizeof(R));
+  if (hh.has_z) {
+    put(L.czp, czp.data(), czp.size() * sizeof(Cx<R>));
+    put(L.czm, czm.data(), czm.size() * sizeof(Cx<R>));
+  }
+  put(L.hd, hdiag.data(), hdiag.size() * sizeof(R));
+  put(L.m, mval.data(), mval.size() * sizeof(R));
+  put(L.f, gp.data(), gp.size() * sizeof(R));
+  put(L.f + (int)sizeof(R) * 16 * n, gm.data(), gm.size() * sizeof(R));
+  for (int k = 0; k < n; k++) {
+    int4 st = make_int4((int)hh.stride[k], hh.radix[k], site_has_singles(hh, k) ? 1 : 0, 0);
+    for (int d = 0; d + 2 < hh.radix[k]; d++) {
+      const Cx<double> up = hh.h[(size_t)k * 256 + d * 16 + d + 2], dn = hh.h[(size_t)k * 256 + (d + 2) * 16 + d];
+      if (up.re != 0.0 || up.im != 0.0 || dn.re != 0.0 || dn.im != 0.0) st.z |= 2;
+    }
+    put(L.site + k * (int)sizeof(int4), &st, sizeof(st));
+  }
+  o.gblob = b.add(blob.data(), blob.size());
+  o.n_gpair = (int)pair.size();
   return o;
 }
 
@@ -172,6 +220,7 @@ static DevTables<R> resolve(const TableOffsets<R> &o, unsigned char *base) {
   t.hflip = reinterpret_cast<const Cx<R> *>(base + o.hflip);
   t.cz_half = reinterpret_cast<const Cx<R> *>(base + o.cz_half);
   t.lowf = reinterpret_cast<const Cx<R> *>(base + o.lowf);
+  t.gblob = reinterpret_cast<const uint4 *>(base + o.gblob);
   return t;
 }
 
@@ -414,11 +463,13 @@ int upload_tables(const HostHam &hh, DevHam &dh, std::string &err) {
   g.single_mask = 0;
   for (int k = 0; k < n; k++)
     if (site_has_singles(hh, k)) g.single_mask |= 1u << k;
+  g.n_gpair = o64.n_gpair;
   g.dim = (uint32_t)hh.dim;
   for (int k = 0; k < n; k++) {
     g.radix[k] = hh.radix[k];
     g.stride[k] = hh.stride[k];
     g.s[k] = 0.5f * hh.two_s[k];
+    g.rinv[k] = 1.0 / hh.radix[k];
   }
   const int rc = build_pass_records(dh, err);
   const uint64_t sig = launch_signature(dh);

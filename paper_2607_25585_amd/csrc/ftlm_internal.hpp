@@ -72,6 +72,49 @@ int compile_hamiltonian(const ftlm_system *sys, HostHam &hh, std::string &err);
 void compile_site_terms(HostHam &hh);
 double count_nnz_per_row(const HostHam &hh);
 
+// One ladder term of a pair in the general-radix direct gather: the row's partner
+// is row + off when the ladder factors of its digits do not vanish; coefficient
+// c f[fa + digit(a)] f[fb + digit(b)] with f = gp (entries 16 k..) then gm
+// (16 (n + k)..).  The list is padded to a multiple of kTermBatch with terms whose
+// factor is 0 for every digit (fa = fb = 32 n).
+constexpr int kTermBatch = 8;
+template <typename R>
+struct alignas(16) GTerm {
+  Cx<R> c;
+  int off;
+  int ab;      // site a | site b << 8
+  int fa, fb;
+};
+
+// Tables of the general-radix direct gather, one after the other (byte offsets,
+// multiples of 16): pair terms, hoff [n][4][16], the
+// diagonal's z-z coupling zz [n][n] (upper triangle read), czp and czm [n][n]
+// (only with has_z), hdiag [n][16], mval [n][16], the ladder factors gp [n][16],
+// gm [n][16], 16 zeros, and per site (stride, radix, bit 0: has single flips, bit
+// 1: some of them by 2).
+template <typename R>
+struct GenBlob {
+  int pair, hoff, zz, czp, czm, hd, m, f, site, total;
+  __host__ __device__ GenBlob(int n, int has_z, int n_gpair) {
+    int o = 0;
+    auto take = [&](size_t b) {
+      const int at = o;
+      o += (int)((b + 15) & ~size_t(15));
+      return at;
+    };
+    pair = take(sizeof(GTerm<R>) * n_gpair);
+    hoff = take(sizeof(Cx<R>) * 64 * n);
+    zz = take(sizeof(R) * n * n);
+    czp = take(has_z ? sizeof(Cx<R>) * n * n : 0);
+    czm = take(has_z ? sizeof(Cx<R>) * n * n : 0);
+    hd = take(sizeof(R) * 16 * n);
+    m = take(sizeof(R) * 16 * n);
+    f = take(sizeof(R) * (32 * n + 16));
+    site = take(sizeof(int4) * n);
+    total = o;
+  }
+};
+
 // ---------------------------------------------------------------------------
 // Device tables.  All pointers refer to one contiguous device allocation
 // owned by the handle.  Real = double for the complex128 path, float for the
@@ -96,6 +139,8 @@ struct DevTables {
   const Cx<R> *hflip;      // [k][2]: h_k[b][1-b]
   const Cx<R> *cz_half;    // [k][l][2]: row bit b_k selects C^{-z} (b=0) or C^{+z} (b=1)
   const Cx<R> *lowf;       // [k][2][256]: sum_{l<8, l!=k} cz_half[k][l][sel] m_l(t)
+  // general-radix direct gather: its tables in the order of GenBlob, copied to LDS
+  const uint4 *gblob;
 };
 
 struct HamGeom {
@@ -103,10 +148,12 @@ struct HamGeom {
   int n_ll, n_lh;          // spin-1/2: pairs sorted inside | mixed | outside the 11-bit tile
   int mx_off[kMaxSites + 1];  // mixed pairs with outer site a occupy [mx_off[a], mx_off[a+1])
   uint32_t single_mask;       // bit k: site k has non-zero single-site flip elements
+  int n_gpair;                // terms of the general-radix pair list (padded)
   uint32_t dim;
   int radix[kMaxSites];
   uint32_t stride[kMaxSites];
   float s[kMaxSites];
+  double rinv[kMaxSites];     // 1 / radix
 };
 
 // One pass of the windowed H*v: the "active" sites span a window of rows that
@@ -327,7 +374,7 @@ int launch_stream(const DevHam &dh, int precision, const HvParams &P, int cap, i
 // first use).  Synchronous.
 int build_pass_records(DevHam &dh, std::string &err);
 void free_pass_records(DevHam &dh);
-int hv_grid_blocks(const DevHam &dh, const HvLaunch &L, int *gx, int *gy, int *kc);
+int hv_grid_blocks(const DevHam &dh, const HvLaunch &L, int *gx, int *gy, int *kc, int *lpr);
 
 int launch_gaussian(uint64_t seed, uint32_t inst, uint32_t field, uint32_t r0, int K,
                     uint32_t dim, int precision, void *out, double *part, unsigned *counter,

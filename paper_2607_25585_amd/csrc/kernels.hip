@@ -901,27 +901,52 @@ __global__ __launch_bounds__(kBlock) void hv_pass(HamGeom g, DevTables<R> tb, Pa
   if (D.last) hv_finish<1>(P, red);
 }
 
-// General mixed-radix systems (any 2 s_i <= 15, N <= 32).
-template <typename R, int KC>
-__global__ __launch_bounds__(kBlock) void hv_gen(HamGeom g, DevTables<R> tb, const Cx<R> *__restrict__ pcg,
-                                                 const Cx<R> *__restrict__ czp, const Cx<R> *__restrict__ czm,
-                                                 const int2 *__restrict__ pij, const R *__restrict__ pzz,
-                                                 HvParams P) {
+// General mixed-radix systems (any 2 s_i <= 15, N <= 32): LPR lanes per row and
+// group of KC columns; the groups of a row and the rows follow each other over the
+// lanes, so that a wave's loads of a term are contiguous whatever the number of
+// columns (with a row per lane a load of a block of 16 or 20 columns touched a
+// cache line per lane).  On the small vectors that take this kernel the time is
+// latency, of three kinds.  Terms one after the other: LPR lanes share a row's
+// sites and pair terms (lane s takes sites s, s + LPR, ... and terms likewise) and
+// add their sums at the end, and a site's four moves, or NB pair terms, load all
+// their partner rows before the first FMA (a lane whose move leaves a digit's
+// range loads nothing and adds nothing).  Tables read entry by entry: they are one
+// block of memory, copied to LDS with all of its loads in flight at once.
+// Instruction fetches: 20 KB of unrolled code took longer than its data, so the
+// loops are short.
+// Against one lane per row, columns strided over the waves (us, complex128): 6 s=1
+// sites, all pairs, one column: 21 -> 8; 8 s=1 sites, 20 columns: 27 -> 13; 8 s=3/2
+// sites, 20 columns: 92 -> 61 (complex64: 68 -> 35).
+template <typename R, int KC, int LPR>
+__global__ __launch_bounds__(kBlock) void hv_gen(HamGeom g, const uint4 *__restrict__ blob, HvParams P) {
+  constexpr int NB = KC >= 8 ? 2 : 4;  // pair terms whose loads are in flight together
+  static_assert(kTermBatch % NB == 0, "the pair list is padded to kTermBatch");
   extern __shared__ __align__(16) unsigned char smem[];
   const int n = g.n;
-  Cx<R> *s_hoff = reinterpret_cast<Cx<R> *>(smem);  // [n][4][16]
-  R *s_hd = reinterpret_cast<R *>(s_hoff + n * 64);  // [n][16]
-  R *s_gp = s_hd + n * 16;
-  R *s_gm = s_gp + n * 16;
-  R *s_m = s_gm + n * 16;
-  const int t = threadIdx.x;
-  const int c0 = blockIdx.y * KC;
-  for (int i = t; i < n * 64; i += kBlock) s_hoff[i] = tb.hoff[i];
-  for (int i = t; i < n * 16; i += kBlock) {
-    s_hd[i] = tb.hdiag[i];
-    s_gp[i] = tb.gp[i];
-    s_gm[i] = tb.gm[i];
-    s_m[i] = tb.mval[i];
+  const GenBlob<R> L(n, g.has_z, g.n_gpair);
+  const GTerm<R> *pair = reinterpret_cast<const GTerm<R> *>(smem + L.pair);
+  const Cx<R> *s_hoff = reinterpret_cast<const Cx<R> *>(smem + L.hoff);
+  const R *zz = reinterpret_cast<const R *>(smem + L.zz);
+  const Cx<R> *czp = reinterpret_cast<const Cx<R> *>(smem + L.czp);
+  const Cx<R> *czm = reinterpret_cast<const Cx<R> *>(smem + L.czm);
+  const R *s_hd = reinterpret_cast<const R *>(smem + L.hd);
+  const R *s_m = reinterpret_cast<const R *>(smem + L.m);
+  const R *s_f = reinterpret_cast<const R *>(smem + L.f);
+  const int4 *s_site = reinterpret_cast<const int4 *>(smem + L.site);
+  const int t = threadIdx.x, s = t & (LPR - 1);
+  const int ncg = P.K / KC, RPB = kBlock / (LPR * ncg);  // column groups, rows per tile
+  const int rt = (t / LPR) / ncg, cg = (t / LPR) - rt * ncg, c0 = cg * KC;
+  {
+    uint4 *dst = reinterpret_cast<uint4 *>(smem);
+    const int nq = L.total / 16;
+    for (int i0 = t; i0 < nq; i0 += 8 * kBlock) {
+      uint4 x[8];
+#pragma unroll
+      for (int u = 0; u < 8; u++) x[u] = blob[min(i0 + u * kBlock, nq - 1)];
+#pragma unroll
+      for (int u = 0; u < 8; u++)
+        if (i0 + u * kBlock < nq) dst[i0 + u * kBlock] = x[u];
+    }
   }
   __syncthreads();
   const Cx<R> *__restrict__ v = reinterpret_cast<const Cx<R> *>(P.v) + c0;
@@ -930,17 +955,22 @@ __global__ __launch_bounds__(kBlock) void hv_gen(HamGeom g, DevTables<R> tb, con
   for (int a = 0; a < 3; a++)
 #pragma unroll
     for (int q = 0; q < KC; q++) red[a][q] = 0.0;
+  // with one lane per row a term is the same in every lane: scalar registers
+  auto uni = [](int x) -> int { return LPR == 1 ? __builtin_amdgcn_readfirstlane(x) : x; };
 
   for (uint32_t tile = blockIdx.x; tile < P.ntile; tile += gridDim.x) {
-    const uint32_t row = tile * kBlock + t;
-    if (row >= g.dim) continue;
-    // digits, 4 bits each: sites 0..15 in dlo, 16..31 in dhi
+    // (the LPR lanes of a row agree on the bounds; 64 bits: the last tile may pass 2^32)
+    const uint64_t row64 = (uint64_t)tile * (unsigned)RPB + (unsigned)rt;
+    if (rt >= RPB || row64 >= g.dim) continue;
+    const uint32_t row = (uint32_t)row64;
+    // digits, 4 bits each: sites 0..15 in dlo, 16..31 in dhi.  The quotients are
+    // exact: (rem + 1/2) / r is at least 1 / (2 r) away from an integer
     uint64_t dlo = 0, dhi = 0;
     {
       uint32_t rem = row;
       for (int k = 0; k < n; k++) {
         const uint32_t r = (uint32_t)g.radix[k];
-        const uint32_t q = rem / r;
+        const uint32_t q = (uint32_t)(((double)rem + 0.5) * g.rinv[k]);
         const uint64_t dk = rem - q * r;
         rem = q;
         if (k < 16) dlo |= dk << (4 * k);
@@ -950,74 +980,124 @@ __global__ __launch_bounds__(kBlock) void hv_gen(HamGeom g, DevTables<R> tb, con
     auto digit = [&](int k) -> int {
       return (int)(((k < 16) ? (dlo >> (4 * k)) : (dhi >> (4 * (k - 16)))) & 15u);
     };
-    R diag = 0;
-    for (int k = 0; k < n; k++) diag += s_hd[k * 16 + digit(k)];
-    for (int p = 0; p < g.npair; p++) {
-      const int2 ij = pij[p];
-      diag = fma(pzz[p], s_m[ij.x * 16 + digit(ij.x)] * s_m[ij.y * 16 + digit(ij.y)], diag);
-    }
     Acc<R, KC> acc;
     acc_zero(acc);
     const Cx<R> *own = v + (size_t)row * P.K;
-    mac_real(acc, diag, own);
-    for (int k = 0; k < n; k++) {
-      const int dk = digit(k), rk = g.radix[k];
-      const uint32_t st = g.stride[k];
-      R fpr = 0, fpi = 0, fmr = 0, fmi = 0;
+    // c[u] times the row's partner of move u, the partners loaded first
+    auto batch = [&](const auto &c, const auto &ok, const auto &off) {
+      constexpr int M = sizeof(ok) / sizeof(ok[0]);
+      Cx<R> x[M][KC];
+#pragma unroll
+      for (int u = 0; u < M; u++) {
+#pragma unroll
+        for (int q = 0; q < KC; q++) x[u][q] = Cx<R>{0, 0};
+        if (ok[u]) {
+          const Cx<R> *px = v + (size_t)(row + (uint32_t)off[u]) * P.K;
+#pragma unroll
+          for (int q = 0; q < KC; q++) x[u][q] = px[q];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < M; u++)
+#pragma unroll
+        for (int q = 0; q < KC; q++) {
+          acc.re[q] = fma(c[u].re, x[u][q].re, acc.re[q]);
+          acc.re[q] = fma(-c[u].im, x[u][q].im, acc.re[q]);
+          acc.im[q] = fma(c[u].re, x[u][q].im, acc.im[q]);
+          acc.im[q] = fma(c[u].im, x[u][q].re, acc.im[q]);
+        }
+    };
+    R diag = 0;
+#pragma unroll 1
+    for (int k = s; k < n; k += LPR) {
+      const int4 site = s_site[k];
+      const int dk = digit(k), rk = uni(site.y), st = uni(site.x), has = uni(site.z);
+      const Cx<R> *ho = s_hoff + k * 64 + dk;
+      // the sites' z-components: the z-z coupling of k to the sites above it, and
+      // the field of its s+- s^z pieces
+      R ph = 0, fpr = 0, fpi = 0, fmr = 0, fmi = 0;
       if (g.has_z) {
-        for (int l = 0; l < n; l++) {
-          if (l == k) continue;
+#pragma unroll 2
+        for (int l = 0; l < n; l++) {  // (the couplings of k with itself are 0)
           const R ml = s_m[l * 16 + digit(l)];
           const Cx<R> cp = czp[k * n + l], cm = czm[k * n + l];
+          ph = fma(l > k ? zz[k * n + l] : R(0), ml, ph);
           fpr = fma(cp.re, ml, fpr);
           fpi = fma(cp.im, ml, fpi);
           fmr = fma(cm.re, ml, fmr);
           fmi = fma(cm.im, ml, fmi);
         }
+      } else {
+#pragma unroll 4
+        for (int l = k + 1; l < n; l++) ph = fma(zz[k * n + l], s_m[l * 16 + digit(l)], ph);
       }
-#pragma unroll
-      for (int di = 0; di < 4; di++) {
-        const int D = (di < 2) ? di - 2 : di - 1;  // -2,-1,+1,+2
-        const int nd = dk + D;
-        if (nd < 0 || nd >= rk) continue;
-        Cx<R> c = s_hoff[(k * 4 + di) * 16 + dk];
-        if (D == -1) {
-          const R gg = s_gp[k * 16 + dk];
-          c.re = fma(gg, fpr, c.re);
-          c.im = fma(gg, fpi, c.im);
-        } else if (D == 1) {
-          const R gg = s_gm[k * 16 + dk];
-          c.re = fma(gg, fmr, c.re);
-          c.im = fma(gg, fmi, c.im);
-        }
-        const uint32_t partner = row + (uint32_t)(D * (int)st);
-        mac(acc, c, v + (size_t)partner * P.K);
+      diag += fma(s_m[k * 16 + dk], ph, s_hd[k * 16 + dk]);
+      if (!has) continue;
+      const R gp = s_f[k * 16 + dk], gm = s_f[(n + k) * 16 + dk];
+      const Cx<R> lo = ho[16], hi = ho[32];  // moves by -1, +1
+      const Cx<R> c1[2] = {{fma(gp, fpr, lo.re), fma(gp, fpi, lo.im)}, {fma(gm, fmr, hi.re), fma(gm, fmi, hi.im)}};
+      if (has & 2) {
+        const Cx<R> c[4] = {ho[0], c1[0], c1[1], ho[48]};
+        const bool ok[4] = {dk >= 2, dk >= 1, dk + 1 < rk, dk + 2 < rk};
+        const int off[4] = {-2 * st, -st, st, 2 * st};
+        batch(c, ok, off);
+      } else {
+        const bool ok[2] = {dk >= 1, dk + 1 < rk};
+        const int off[2] = {-st, st};
+        batch(c1, ok, off);
       }
     }
-    for (int p = 0; p < g.npair; p++) {
-      const int2 ij = pij[p];
-      const int di = digit(ij.x), dj = digit(ij.y);
-      const int ri = g.radix[ij.x], rj = g.radix[ij.y];
-      const uint32_t si = g.stride[ij.x], sj = g.stride[ij.y];
-      const R gpi = s_gp[ij.x * 16 + di], gmi = s_gm[ij.x * 16 + di];
-      const R gpj = s_gp[ij.y * 16 + dj], gmj = s_gm[ij.y * 16 + dj];
-      const Cx<R> *pc = pcg + 4 * p;
+    mac_real(acc, diag, own);
+#pragma unroll 1
+    for (int e = s; e < g.n_gpair; e += NB * LPR) {
+      Cx<R> c[NB];
+      bool ok[NB];
+      int off[NB];
 #pragma unroll
-      for (int q = 0; q < 4; q++) {
-        const Cx<R> cq = pc[q];
-        if (cq.re == R(0) && cq.im == R(0)) continue;
-        const bool im_ = (q >> 1) != 0, jm = (q & 1) != 0;  // '-' ladder on site i / j
-        const bool vi = im_ ? (di <= ri - 2) : (di >= 1);
-        const bool vj = jm ? (dj <= rj - 2) : (dj >= 1);
-        if (!(vi && vj)) continue;
-        const R f = (im_ ? gmi : gpi) * (jm ? gmj : gpj);
-        const uint32_t partner = row + (im_ ? si : (uint32_t)(-(int)si)) + (jm ? sj : (uint32_t)(-(int)sj));
-        mac(acc, Cx<R>{cq.re * f, cq.im * f}, v + (size_t)partner * P.K);
+      for (int u = 0; u < NB; u++) {
+        const int eu = e + u * LPR;
+        const bool in = LPR == 1 || eu < g.n_gpair;
+        const GTerm<R> &G = pair[in ? eu : s];
+        const int ab = uni(G.ab);
+        const R f = s_f[uni(G.fa) + digit(ab & 255)] * s_f[uni(G.fb) + digit(ab >> 8)];
+        c[u] = Cx<R>{G.c.re * f, G.c.im * f};
+        ok[u] = in && f != R(0);
+        off[u] = uni(G.off);
       }
+      batch(c, ok, off);
+    }
+    if (LPR > 1) {
+#pragma unroll
+      for (int q = 0; q < KC; q++)
+#pragma unroll
+        for (int m = 1; m < LPR; m *= 2) {
+          acc.re[q] += __shfl_xor(acc.re[q], m, 64);
+          acc.im[q] += __shfl_xor(acc.im[q], m, 64);
+        }
+      if (s != 0) continue;
     }
     hv_epilogue<R, KC>(P, row, c0, acc, own, red);
   }
-  hv_finish<KC>(P, red);
+  if (!P.lanczos) return;
+  // per-column sums over the tile's rows: a fixed tree over the row index
+  __shared__ double sum[kBlock * KC];
+  int top = 1;
+  while (top < RPB) top *= 2;
+  for (int a = 0; a < 3; a++) {
+    __syncthreads();
+    if (s == 0) {
+#pragma unroll
+      for (int q = 0; q < KC; q++) sum[(t / LPR) * KC + q] = red[a][q];
+    }
+    __syncthreads();
+    for (int w = top / 2; w > 0; w /= 2) {
+      if (s == 0 && rt < w && rt + w < RPB)
+#pragma unroll
+        for (int q = 0; q < KC; q++) sum[(t / LPR) * KC + q] += sum[((rt + w) * ncg + cg) * KC + q];
+      __syncthreads();
+    }
+    if (t < P.K) P.part[(((size_t)(t / KC) * gridDim.x + blockIdx.x) * 3 + a) * KC + t % KC] = sum[t];
+  }
 }
 
 // ------------------------------------------------------------------ L2-window passes
@@ -1948,9 +2028,7 @@ static size_t hv_tile_smem(const HamGeom &g) {
 
 template <typename R>
 static size_t hv_smem(const HamGeom &g) {
-  if (g.spin_half && g.n >= kLowBits)
-    return sizeof(Cx<R>) * (4 * (size_t)g.npair + 4 * g.n) + sizeof(R) * (3 * g.n + 8);
-  return sizeof(Cx<R>) * 64 * (size_t)g.n + sizeof(R) * 64 * g.n;
+  return sizeof(Cx<R>) * (4 * (size_t)g.npair + 4 * g.n) + sizeof(R) * (3 * g.n + 8);
 }
 
 static int pick_kc(int K, int want) {
@@ -1960,12 +2038,40 @@ static int pick_kc(int K, int want) {
   return 1;
 }
 
-int hv_grid_blocks(const DevHam &dh, const HvLaunch &L, int *gx, int *gy, int *kc) {
+// Lanes per row and column group of the general-radix direct gather (1 for the
+// other kernels): a row's terms are shared where rows and groups leave the chip
+// idle.  Measured (us, K columns in groups of kc):
+//   rows x groups       1 lane   2      4      8
+//   729                 19.3     12.0   8.9    8.2   (6 s=1 sites, all pairs; K = 1)
+//   32,805              14.5     9.8    8.7    11.4  (8 s=1 sites, K = 20, complex64)
+//   65,610              15.1     12.6   16.0   17.3  (8 s=1 sites, K = 20, complex128)
+//   295,245             41.4     38.5   52.7   65.3  (10 s=1 sites, K = 20, complex64)
+//   655,360             60.6     64.2   89.6   120.8 (8 s=3/2 sites, K = 20, complex128)
+static int gen_lanes(const HamGeom &g, int K, int kc) {
+  if (g.spin_half) return 1;
+  const int ncg = K / kc;
+  const uint64_t items = (uint64_t)g.dim * ncg;
+  int lpr = items <= 16384 ? 8 : items <= 49152 ? 4 : items <= 393216 ? 2 : 1;
+  while (lpr * ncg > kBlock) lpr /= 2;
+  return lpr;
+}
+
+// 256-lane tiles of the direct kernels.
+static uint32_t direct_tiles(const HamGeom &g, int K, int kc, int lpr) {
+  if (g.spin_half) return g.dim >> kLowBits;
+  const uint32_t rows = (uint32_t)(kBlock / (lpr * (K / kc)));
+  return (uint32_t)(((uint64_t)g.dim + rows - 1) / rows);
+}
+
+int hv_grid_blocks(const DevHam &dh, const HvLaunch &L, int *gx, int *gy, int *kc, int *lpr) {
   const HamGeom &g = dh.geom;
-  int want = L.kc > 0 ? L.kc : 8;
+  // columns per lane, general radix: 32 bytes (the coefficient work is shared by
+  // the group, the loads stay contiguous; 10 s=1 sites, 20 columns, complex64:
+  // 89, 48, 41 us at 1, 2, 4; complex128: 103, 67, 67)
+  const int want = L.kc > 0 ? L.kc : g.spin_half ? 8 : L.precision == FTLM_C64 ? 4 : 2;
   int k = pick_kc(L.K, want);
-  uint32_t ntile = (g.spin_half && g.n >= kLowBits) ? (g.dim >> kLowBits)
-                                                     : (uint32_t)(((uint64_t)g.dim + kBlock - 1) / kBlock);
+  *lpr = gen_lanes(g, L.K, k);
+  uint32_t ntile = direct_tiles(g, L.K, k, *lpr);
   if (use_tile(g, L.K)) {
     ntile = g.dim >> kTileBits;
     k = 1;
@@ -1979,21 +2085,39 @@ int hv_grid_blocks(const DevHam &dh, const HvLaunch &L, int *gx, int *gy, int *k
   return FTLM_OK;
 }
 
+template <typename R, int KC, int LPR>
+static void launch_gen(const HamGeom &g, const DevTables<R> &tb, const HvParams &P, dim3 grid, hipStream_t s) {
+  const size_t sm = (size_t)GenBlob<R>(g.n, g.has_z, g.n_gpair).total;  // up to 137 KB: 31 sites, all pairs
+  static std::atomic<size_t> granted{64 * 1024};  // per instantiation: largest dynamic LDS size requested so far
+  if (sm > granted.load()) {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&hv_gen<R, KC, LPR>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
+    granted.store(sm);
+  }
+  hipLaunchKernelGGL((hv_gen<R, KC, LPR>), grid, dim3(kBlock), sm, s, g, tb.gblob, P);
+}
+
 template <typename R, int KC>
-static void launch_hv_t(const DevHam &dh, const DevTables<R> &tb, const HvParams &P, dim3 grid,
+static void launch_hv_t(const DevHam &dh, const DevTables<R> &tb, const HvParams &P, dim3 grid, int lpr,
                         hipStream_t s) {
   const HamGeom &g = dh.geom;
-  const size_t sm = hv_smem<R>(g);
-  const UniformTabs<R> U = uniform_tabs(tb, false);
-  if (g.spin_half && g.n >= kLowBits)
-    hipLaunchKernelGGL((hv_half<R, KC>), grid, dim3(kBlock), sm, s, g, tb, U.pij, U.pzz, P);
-  else
-    hipLaunchKernelGGL((hv_gen<R, KC>), grid, dim3(kBlock), sm, s, g, tb, U.pc, U.czp, U.czm, U.pij, U.pzz, P);
+  if (g.spin_half && g.n >= kLowBits) {
+    const UniformTabs<R> U = uniform_tabs(tb, false);
+    hipLaunchKernelGGL((hv_half<R, KC>), grid, dim3(kBlock), hv_smem<R>(g), s, g, tb, U.pij, U.pzz, P);
+  } else if (lpr == 8) {
+    launch_gen<R, KC, 8>(g, tb, P, grid, s);
+  } else if (lpr == 4) {
+    launch_gen<R, KC, 4>(g, tb, P, grid, s);
+  } else if (lpr == 2) {
+    launch_gen<R, KC, 2>(g, tb, P, grid, s);
+  } else {
+    launch_gen<R, KC, 1>(g, tb, P, grid, s);
+  }
 }
 
 template <typename R>
 static void launch_hv_r(const DevHam &dh, const DevTables<R> &tb, const HvParams &P, dim3 grid,
-                        int kc, hipStream_t s) {
+                        int kc, int lpr, hipStream_t s) {
   if (use_tile(dh.geom, P.K)) {
     const size_t sm = hv_tile_smem<R>(dh.geom);
     static size_t granted = 0;  // per instantiation: largest dynamic LDS size requested so far
@@ -2006,10 +2130,10 @@ static void launch_hv_r(const DevHam &dh, const DevTables<R> &tb, const HvParams
     return;
   }
   switch (kc) {
-    case 8: launch_hv_t<R, 8>(dh, tb, P, grid, s); break;
-    case 4: launch_hv_t<R, 4>(dh, tb, P, grid, s); break;
-    case 2: launch_hv_t<R, 2>(dh, tb, P, grid, s); break;
-    default: launch_hv_t<R, 1>(dh, tb, P, grid, s); break;
+    case 8: launch_hv_t<R, 8>(dh, tb, P, grid, lpr, s); break;
+    case 4: launch_hv_t<R, 4>(dh, tb, P, grid, lpr, s); break;
+    case 2: launch_hv_t<R, 2>(dh, tb, P, grid, lpr, s); break;
+    default: launch_hv_t<R, 1>(dh, tb, P, grid, lpr, s); break;
   }
 }
 
@@ -2124,14 +2248,12 @@ int launch_hv(const DevHam &dh, const HvLaunch &Lin, hipStream_t s) {
     else if (!tw.passes.empty()) L.variant = 5;
   }
   g_variant = L.variant;
-  int gx, gy, kc;
-  const int rcg = hv_grid_blocks(dh, L, &gx, &gy, &kc);
+  int gx, gy, kc, lpr;
+  const int rcg = hv_grid_blocks(dh, L, &gx, &gy, &kc, &lpr);
   if (rcg) return rcg;
   HvParams P{};
   P.K = L.K;
-  P.ntile = (dh.geom.spin_half && dh.geom.n >= kLowBits)
-                ? (dh.geom.dim >> kLowBits)
-                : (uint32_t)(((uint64_t)dh.geom.dim + kBlock - 1) / kBlock);
+  P.ntile = direct_tiles(dh.geom, L.K, kc, lpr);
   P.v = L.v;
   P.w = L.w;
   P.scale = L.scale;
@@ -2181,9 +2303,10 @@ int launch_hv(const DevHam &dh, const HvLaunch &Lin, hipStream_t s) {
     fin_gy = (unsigned)L.K;
     fin_kc = 1;
   } else {
-    dim3 grid(gx, gy);
-    if (L.precision == FTLM_C64) launch_hv_r<float>(dh, dh.t32, P, grid, kc, s);
-    else launch_hv_r<double>(dh, dh.t64, P, grid, kc, s);
+    // (the general-radix kernel's blocks hold every column group)
+    dim3 grid(gx, dh.geom.spin_half ? gy : 1);
+    if (L.precision == FTLM_C64) launch_hv_r<float>(dh, dh.t32, P, grid, kc, lpr, s);
+    else launch_hv_r<double>(dh, dh.t64, P, grid, kc, lpr, s);
     if (use_tile(dh.geom, L.K)) fin_kc = 1;
   }
   if (rc) return rc;
