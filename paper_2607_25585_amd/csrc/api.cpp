@@ -298,6 +298,13 @@ uint64_t launch_signature(const DevHam &dh) {
     f.pod(sp->d_pzz);
     f.pod(sp->d_tdiag);
   }
+  for (const SweepPlan *sw : {&dh.sw64, &dh.sw32}) {
+    f.vec(sw->passes);
+    f.pod(sw->cplx);
+    f.pod(sw->tab.d_pij);
+    f.pod(sw->tab.d_pc);
+    f.pod(sw->tab.d_tdiag);
+  }
   f.pod(dh.block);
   return f.h;
 }
@@ -414,6 +421,23 @@ int upload_tables(const HostHam &hh, DevHam &dh, std::string &err) {
       }
     }
   }
+  plan_sweep(hh, sizeof(Cx<double>), 65536 / sizeof(Cx<double>), dh.sw64);
+  plan_sweep(hh, sizeof(Cx<float>), 65536 / sizeof(Cx<float>), dh.sw32);
+  size_t off_w[2][3] = {{0}};
+  for (int q = 0; q < 2; q++) {
+    const SweepPlan &sw = q ? dh.sw32 : dh.sw64;
+    off_w[q][0] = b.add(sw.pij.data(), sw.pij.size() * sizeof(int4));
+    if (q == 0) {
+      off_w[q][1] = b.add(sw.pc.data(), sw.pc.size() * sizeof(Cx<double>));
+      off_w[q][2] = b.add(sw.tdiag.data(), sw.tdiag.size() * sizeof(double));
+    } else {
+      std::vector<Cx<float>> c32;
+      for (const Cx<double> &c : sw.pc) c32.push_back(Cx<float>{(float)c.re, (float)c.im});
+      const std::vector<float> t32(sw.tdiag.begin(), sw.tdiag.end());
+      off_w[q][1] = b.add(c32.data(), c32.size() * sizeof(Cx<float>));
+      off_w[q][2] = b.add(t32.data(), t32.size() * sizeof(float));
+    }
+  }
   const size_t bytes = (b.bytes.size() + 255) & ~size_t(255);
   if (dh.block && dh.block_bytes != bytes) {
     (void)hipFree(dh.block);
@@ -449,6 +473,10 @@ int upload_tables(const HostHam &hh, DevHam &dh, std::string &err) {
       sps[q]->d_pc = base + off_s[q][1];
       sps[q]->d_pzz = base + off_s[q][2];
       sps[q]->d_tdiag = base + off_s[q][3];
+      SweepTables &tab = (q ? dh.sw32 : dh.sw64).tab;
+      tab.d_pij = reinterpret_cast<const int4 *>(base + off_w[q][0]);
+      tab.d_pc = base + off_w[q][1];
+      tab.d_tdiag = base + off_w[q][2];
     }
   }
   HamGeom &g = dh.geom;

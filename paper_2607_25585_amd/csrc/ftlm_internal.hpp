@@ -275,6 +275,38 @@ struct StreamPlan {
 // Host part of the stream plan for tiles of at most tile_rows rows.
 void plan_stream(const HostHam &hh, uint32_t tile_rows, StreamPlan &pl);
 
+// Tile sweep (sweep.hip): one column, general radix, has_z == 0.  Sites by position:
+// tile sites 0..t-1, lowest first, the top one (whose digits a thread holds) at t-1;
+// then the outer sites in the order of the tile index's digits.
+struct SweepPass {
+  int n, t, rtop;           // sites, tile sites, rows per thread (radix of the top site)
+  uint32_t Q, ntile, chunk; // threads with rows, tiles, tiles per XCD chunk (0: the launch's choice)
+  int first, last, diag;    // passes after the first add to w, the last runs the epilogue
+  int np, np_low, np_out;   // pairs of the pass: two lower | lower and top | mixed, by outer site | two outer
+  int p0;                   // its first pair in the plan's lists
+  uint32_t smask, smask2;   // positions whose single flips the pass applies; that move by 2
+  int site[kMaxSites], radix[kMaxSites];
+  uint32_t st[kMaxSites], wst[kMaxSites];  // strides in the basis / (tile positions) in the tile
+  float s[kMaxSites];
+  int ptop[kMaxSites];      // pair (lower position, top) or -1
+  int mx[kMaxSites + 1];    // mixed pairs of outer position t + k: [mx[k], mx[k + 1])
+};
+struct SweepTables {        // device copies (inside the handle's table block), in the plan's precision
+  const int4 *d_pij = nullptr;   // [np] (position a, position b, non-zero types)
+  const void *d_pc = nullptr;    // [np][a up][b up]
+  const void *d_tdiag = nullptr; // [T]
+};
+struct SweepPlan {
+  std::vector<SweepPass> passes;  // empty: the kernel does not apply
+  bool cplx = true;
+  std::vector<int4> pij;
+  std::vector<Cx<double>> pc;
+  std::vector<double> tdiag;
+  SweepTables tab;
+};
+// Plan for vectors of es bytes per element and tiles of at most tile_rows rows.
+void plan_sweep(const HostHam &hh, size_t es, uint32_t tile_rows, SweepPlan &pl);
+
 struct DevHam {
   HamGeom geom;
   HvTuning tune[2][65];  // [precision][columns]
@@ -284,6 +316,7 @@ struct DevHam {
   WinPlan win64, win32;     // L2-window plans for complex128 / complex64
   WinPlan tw64, tw32;       // L2-window plans of the LDS tile kernel (spin 1/2, N >= 12)
   StreamPlan sp64, sp32;    // single-pass tile plans (complex128 / complex64)
+  SweepPlan sw64, sw32;     // tile sweep plans
   // key of the plans above (recomputed only when it changes)
   bool plan_valid = false;
   uint32_t plan_smask = 0;
@@ -370,6 +403,10 @@ struct HvParams;
 // the tiles per XCD chunk, bit 8 the LDS staging of the mixed pairs' partner tiles.
 int launch_stream(const DevHam &dh, int precision, const HvParams &P, int cap, int kc, unsigned *gx,
                   hipStream_t s);
+// Variant 6 where a tile sweep plan exists (sweep.hip); kc: bits 4..7 as above, bit 8
+// stages every group's partner tile.
+int launch_sweep(const DevHam &dh, int precision, const HvParams &P, int cap, int kc, unsigned *gx,
+                 hipStream_t s);
 // (Re)computes the per-window records of both pass plans (allocates rec_block on
 // first use).  Synchronous.
 int build_pass_records(DevHam &dh, std::string &err);
