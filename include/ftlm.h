@@ -111,7 +111,9 @@ int ftlm_apply(const ftlm_hamiltonian *h, int32_t precision, int32_t n_cols, con
  * tiles per XCD chunk in bits 4..7, and in bit 8 whether the partner tiles of
  * the pairs with one tile site are staged in LDS, one per outer site and move,
  * instead of read directly; not for systems of spins 1/2 only, where a launch
- * with bit 8 set fails with FTLM_EINVAL), each at 512, 1024, 2048 and 4096 blocks (variants 4, 5, 6: at most
+ * with bit 8 set fails with FTLM_EINVAL; general-radix systems of 2^16 rows and
+ * more whose top tile site has 3 to 6 values take only the chunk bits: their
+ * block follows from the tile and every partner tile is staged), each at 512, 1024, 2048 and 4096 blocks (variants 4, 5, 6: at most
  * 2048) --
  * with HIP events on the stream (blocking): three launches each, then the four
  * fastest again with ten launches each.  Stores the fastest of that second

@@ -299,7 +299,8 @@ uint64_t launch_signature(const DevHam &dh) {
     f.pod(sp->d_tdiag);
   }
   for (const SweepPlan *sw : {&dh.sw64, &dh.sw32}) {
-    f.vec(sw->passes);
+    f.pod(sw->ok);
+    f.pod(sw->pass);
     f.pod(sw->cplx);
     f.pod(sw->tab.d_pij);
     f.pod(sw->tab.d_pc);

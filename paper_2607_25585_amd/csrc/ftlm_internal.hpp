@@ -275,29 +275,27 @@ struct StreamPlan {
 // Host part of the stream plan for tiles of at most tile_rows rows.
 void plan_stream(const HostHam &hh, uint32_t tile_rows, StreamPlan &pl);
 
-// Tile sweep (sweep.hip): one column, general radix, has_z == 0.  Sites by position:
-// tile sites 0..t-1, lowest first, the top one (whose digits a thread holds) at t-1;
-// then the outer sites in the order of the tile index's digits.
+// Tile sweep (sweep.hip): one column, general radix, has_z == 0.  Tile sites 0..t-1,
+// the top one (whose digits a thread holds) at t-1; the others are outer sites.
 struct SweepPass {
   int n, t, rtop;           // sites, tile sites, rows per thread (radix of the top site)
-  uint32_t Q, ntile, chunk; // threads with rows, tiles, tiles per XCD chunk (0: the launch's choice)
-  int first, last, diag;    // passes after the first add to w, the last runs the epilogue
-  int np, np_low, np_out;   // pairs of the pass: two lower | lower and top | mixed, by outer site | two outer
-  int p0;                   // its first pair in the plan's lists
-  uint32_t smask, smask2;   // positions whose single flips the pass applies; that move by 2
-  int site[kMaxSites], radix[kMaxSites];
-  uint32_t st[kMaxSites], wst[kMaxSites];  // strides in the basis / (tile positions) in the tile
+  uint32_t Q, ntile;        // threads with rows, tiles
+  int np, np_low, np_out;   // pairs: two lower | lower and top | mixed, by outer site | two outer
+  uint32_t smask, smask2;   // sites with single flips; that move by 2
+  int radix[kMaxSites];
+  uint32_t st[kMaxSites], wst[kMaxSites];  // strides in the basis / (tile sites) in the tile
   float s[kMaxSites];
-  int ptop[kMaxSites];      // pair (lower position, top) or -1
-  int mx[kMaxSites + 1];    // mixed pairs of outer position t + k: [mx[k], mx[k + 1])
+  int ptop[kMaxSites];      // pair (lower site, top) or -1
+  int mx[kMaxSites + 1];    // mixed pairs of outer site t + k: [mx[k], mx[k + 1])
 };
 struct SweepTables {        // device copies (inside the handle's table block), in the plan's precision
-  const int4 *d_pij = nullptr;   // [np] (position a, position b, non-zero types)
+  const int4 *d_pij = nullptr;   // [np] (site a, site b, non-zero types)
   const void *d_pc = nullptr;    // [np][a up][b up]
   const void *d_tdiag = nullptr; // [T]
 };
 struct SweepPlan {
-  std::vector<SweepPass> passes;  // empty: the kernel does not apply
+  bool ok = false;          // the kernel applies
+  SweepPass pass{};
   bool cplx = true;
   std::vector<int4> pij;
   std::vector<Cx<double>> pc;
@@ -403,8 +401,8 @@ struct HvParams;
 // the tiles per XCD chunk, bit 8 the LDS staging of the mixed pairs' partner tiles.
 int launch_stream(const DevHam &dh, int precision, const HvParams &P, int cap, int kc, unsigned *gx,
                   hipStream_t s);
-// Variant 6 where a tile sweep plan exists (sweep.hip); kc: bits 4..7 as above, bit 8
-// stages every group's partner tile.
+// Variant 6 where a tile sweep plan exists (sweep.hip); cap: 0 takes the blocks
+// resident at once; kc: bits 4..7 as above (every group's partner tile is staged).
 int launch_sweep(const DevHam &dh, int precision, const HvParams &P, int cap, int kc, unsigned *gx,
                  hipStream_t s);
 // (Re)computes the per-window records of both pass plans (allocates rec_block on

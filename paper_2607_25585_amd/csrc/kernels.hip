@@ -2279,8 +2279,8 @@ int launch_hv(const DevHam &dh, const HvLaunch &Lin, hipStream_t s) {
     if (L.K != 1) return FTLM_EINVAL;
     const int cap = L.grid_cap > 0 ? std::min(L.grid_cap, 2048) : 2048;
     const SweepPlan &sw = L.precision == FTLM_C64 ? dh.sw32 : dh.sw64;
-    rc = sw.passes.empty() ? launch_stream(dh, L.precision, P, cap, L.kc, &fin_gx, s)
-                           : launch_sweep(dh, L.precision, P, cap, L.kc, &fin_gx, s);
+    rc = sw.ok ? launch_sweep(dh, L.precision, P, L.grid_cap, L.kc, &fin_gx, s)
+               : launch_stream(dh, L.precision, P, cap, L.kc, &fin_gx, s);
     fin_gy = 1;
     fin_kc = 1;
   } else if (L.variant == 5) {

@@ -1,8 +1,8 @@
 // Tile sweep: H*v for one column of a general-radix system without s+- s^z pair
 // pieces (Sec. 2.1, Eq. mce-hamop, in the ladder form of ftlm_internal.hpp), in one
-// or several passes over the rows.
+// pass over the rows.
 //
-// A pass has a list of tile sites; the rows that share the digits of every other
+// The low sites are tile sites; the rows that share the digits of every other
 // ("outer") site are a tile, staged in LDS by one block.  Thread q owns the rows of
 // one value of the lower tile sites' digits and ALL digits d of the top tile site:
 // every digit but d is the thread's own for the whole launch, so a term's validity,
@@ -14,24 +14,27 @@
 //   - one outer site j and one move of it: the partner tile's rows come straight from
 //     v (coalesced, the same offset for every row) and serve j's single flip and its
 //     pairs with the top site from registers; the pairs with lower sites read them
-//     shifted, from LDS (the tile's own rows are not needed there any more) or, where
-//     a group has at most kDirect of them, from v;
+//     shifted, from LDS (the tile's own rows are not needed there any more; shifted
+//     reads from v instead, for groups of up to two, gave 6.80 -> 7.24 ms on 3^17 rows
+//     and 11.4 -> 11.5 on 5^12, nn + nnn);
 //   - two outer sites, and single flips by two: one coefficient per tile, partners
 //     from v, two terms in flight.
-// The passes after the first add to w; the last one runs the Lanczos epilogue.
 //
 // Tile walk: with a grid that is a multiple of 8, block b runs on XCD b % 8; chunks of
 // consecutive tiles go to the XCDs in turn and each XCD's blocks walk its chunks in
-// order.  The outer digits of a tile index run over the pass's window sites first, so
-// that a chunk of a multi-pass plan is one window, whose rows stay in the XCD's L2.
+// order.  The default grid is the blocks that are resident at once: with more, the
+// blocks of an XCD drift apart and the partner tiles leave its L2 in between.
 //
 // Measured (one product, complex128 / complex64), against the earlier mapping of rows to
 // threads (row = thread + k * block: digits, validity and ladder factors per row):
-//   6 x 5^8 rows, 20 nonzeros per row    223 -> 132 us / 138 -> 104 us
-//   5^12 rows, all pairs (204 per row)   71 -> 50 ms / 42.2 -> 30.4 ms
-//   5^12 rows, nn + nnn (32 per row)     13.8 -> 12.5 ms / 9.6 -> 9.2 ms
-// What bounds it now is the partner tiles that come from beyond L2 (about 65 vector
-// reads per product with all pairs).
+//   6 x 5^8 rows, 20 nonzeros per row    223 -> 121 / 138 -> 74 us
+//   5^12 rows, all pairs (204 per row)   71 -> 39.8 / 42.2 -> 21.6 ms
+//   5^12 rows, nn + nnn (32 per row)     13.8 -> 10.9 / 9.6 -> 5.8 ms
+// What bounds it now is the partner tiles that come from beyond L2 (all pairs, complex128:
+// 141 GB fetched of the 65 vector reads' 254 GB, 3.5 TB/s; nn + nnn 39 GB).  Passes over
+// subsets of the sites whose windows fit an XCD's L2 read a third of that, but took
+// longer (nn + nnn 12.1 -> 13.7 ms at complex128, all pairs 30 -> 35 at complex64):
+// every pass pays the own tile, the tables and a read-add of w.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -48,7 +51,15 @@ namespace ftlm {
 
 namespace {
 
-constexpr int kDirect = 2;  // shifted reads of a group that are taken from v directly
+// Waves per SIMD that the registers are allocated for.  The kernel waits for partner
+// tiles, so more waves help until the rows in flight spill: complex64 rows take half the
+// registers.  5^12 rows, all pairs: complex128 3 waves 46.7 ms, 4 50.9; complex64
+// 4 waves 30.4 ms, 6 25.3, 8 26.8.  4^13 rows, nn + nnn, complex64: 6 2.16 ms, 8 1.75.
+constexpr int sweep_waves(size_t real_bytes, int rpt) {
+  return rpt >= 5 ? (real_bytes == 8 ? 3 : 6) : real_bytes == 8 ? 4 : 8;
+}
+// Threads of a block at most: with RPT 5 and 6 (3 waves per SIMD) one block is what a CU holds.
+constexpr int sweep_threads(int rpt) { return rpt >= 5 ? 768 : 1024; }
 
 // LDS layout (offsets 16-byte aligned).
 template <typename R>
@@ -69,7 +80,7 @@ struct SweepLds {
     gp = take(rs * 16 * n);
     gm = take(rs * 16 * n);
     hd = take(rs * 16 * n);
-    zz = take(G.diag ? rs * n * n : 0);
+    zz = take(rs * n * n);
     phi = take(rs * n);
     pij = take(sizeof(int4) * np);
     ooff = take(sizeof(int64_t) * no);
@@ -110,38 +121,35 @@ __device__ __forceinline__ int append(bool valid, int count, int *pos) {
 }
 
 template <typename R, int RPT, bool CPLX>
-__global__ __launch_bounds__(1024) void hv_sweep(SweepPass G, DevTables<R> tb, const int4 *__restrict__ pij,
-                                                 const Cx<R> *__restrict__ pcs, const R *__restrict__ tdiag,
-                                                 uint32_t chunk, int stage_all,
-                                                 HvParams P) {
+__global__ __launch_bounds__(sweep_threads(RPT), sweep_waves(sizeof(R), RPT)) void hv_sweep(
+    SweepPass G, DevTables<R> tb, const int4 *__restrict__ pij, const Cx<R> *__restrict__ pcs,
+    const R *__restrict__ tdiag, uint32_t chunk, HvParams P) {
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr int SP = RPT | 1;
   const SweepLds<R> L(G);
   Cx<R> *tile = reinterpret_cast<Cx<R> *>(smem + L.tile);
-  Cx<R> *s_hoff = reinterpret_cast<Cx<R> *>(smem + L.hoff);  // [position][4][16], tile positions, then outer ones
+  Cx<R> *s_hoff = reinterpret_cast<Cx<R> *>(smem + L.hoff);  // [site][4][16]
   Cx<R> *s_pc = reinterpret_cast<Cx<R> *>(smem + L.pc);      // [np][4]
-  R *s_gp = reinterpret_cast<R *>(smem + L.gp);              // [position][16]
+  R *s_gp = reinterpret_cast<R *>(smem + L.gp);              // [site][16]
   R *s_gm = reinterpret_cast<R *>(smem + L.gm);
   R *s_hd = reinterpret_cast<R *>(smem + L.hd);
-  R *s_zz = reinterpret_cast<R *>(smem + L.zz);              // [position][position]
+  R *s_zz = reinterpret_cast<R *>(smem + L.zz);              // [site][site]
   R *s_phi = reinterpret_cast<R *>(smem + L.phi);
-  int4 *s_pij = reinterpret_cast<int4 *>(smem + L.pij);      // (position a, position b, non-zero types, 0)
+  int4 *s_pij = reinterpret_cast<int4 *>(smem + L.pij);      // (site a, site b, non-zero types, 0)
   int64_t *s_ooff = reinterpret_cast<int64_t *>(smem + L.ooff);
   Cx<R> *s_oc = reinterpret_cast<Cx<R> *>(smem + L.oc);
   int *s_cnt = reinterpret_cast<int *>(smem + L.cnt);
   const int t = G.t, n = G.n, top = t - 1, tid = threadIdx.x, NT = blockDim.x;
   const uint32_t Q = G.Q;
-  for (int i = tid; i < 64 * n; i += NT) s_hoff[i] = tb.hoff[G.site[i >> 6] * 64 + (i & 63)];
+  for (int i = tid; i < 64 * n; i += NT) s_hoff[i] = tb.hoff[i];
   for (int i = tid; i < 16 * n; i += NT) {
-    const int k = G.site[i >> 4] * 16 + (i & 15);
-    s_gp[i] = tb.gp[k];
-    s_gm[i] = tb.gm[k];
-    s_hd[i] = tb.hdiag[k];
+    s_gp[i] = tb.gp[i];
+    s_gm[i] = tb.gm[i];
+    s_hd[i] = tb.hdiag[i];
   }
   for (int i = tid; i < 4 * G.np; i += NT) s_pc[i] = pcs[i];
   for (int i = tid; i < G.np; i += NT) s_pij[i] = pij[i];
-  if (G.diag)
-    for (int i = tid; i < n * n; i += NT) s_zz[i] = tb.zz[G.site[i / n] * n + G.site[i % n]];
+  for (int i = tid; i < n * n; i += NT) s_zz[i] = tb.zz[i];
   // the thread's lower digits (4 bits each, at most 8 lower tile sites) and the
   // offset of its rows within the basis; threads past Q repeat the last one's reads
   const bool act = (uint32_t)tid < Q;
@@ -159,7 +167,6 @@ __global__ __launch_bounds__(1024) void hv_sweep(SweepPass G, DevTables<R> tb, c
   auto digit = [&](int i) -> int { return (int)((dig >> (4 * i)) & 15u); };
   const uint32_t stt = G.st[top];
   const Cx<R> *__restrict__ v = reinterpret_cast<const Cx<R> *>(P.v);
-  Cx<R> *w = reinterpret_cast<Cx<R> *>(P.w);
   double red[3][1] = {{0.0}, {0.0}, {0.0}};
   __syncthreads();
   // the top site's ladder factors
@@ -248,7 +255,7 @@ __global__ __launch_bounds__(1024) void hv_sweep(SweepPass G, DevTables<R> tb, c
         }
       }
       if (tid == 0) *s_cnt = no;
-    } else if (G.diag && tid < 64 + n) {
+    } else if (tid < 64 + n) {
       // wave 1: for a tile site, the field of the outer sites' z-components; for an
       // outer site, its own diagonal element and its coupling to the later ones
       const int i = tid - 64;
@@ -260,7 +267,7 @@ __global__ __launch_bounds__(1024) void hv_sweep(SweepPass G, DevTables<R> tb, c
     Cx<R> acc[RPT];
 #pragma unroll
     for (int d = 0; d < RPT; d++) acc[d] = Cx<R>{0, 0};
-    if (G.diag) {
+    {
       R dq = 0;
       for (int k = t; k < n; k++) dq += s_phi[k];
       for (int i = 0; i < top; i++) dq = fma((R)digit(i) - (R)G.s[i], s_phi[i], dq);
@@ -299,7 +306,7 @@ __global__ __launch_bounds__(1024) void hv_sweep(SweepPass G, DevTables<R> tb, c
     // lower sites: single flips and pairs with the top site
 #pragma unroll 1
     for (int i = 0; i < top; i++) {
-      const int pt = G.ptop[i];  // the pair (i, top) of this pass, or -1
+      const int pt = G.ptop[i];  // the pair (i, top), or -1
       const bool sg = (G.smask >> i) & 1u;
       if (!sg && pt < 0) continue;
       const int di = digit(i), rd = G.radix[i], ws = (int)G.wst[i];
@@ -376,12 +383,12 @@ __global__ __launch_bounds__(1024) void hv_sweep(SweepPass G, DevTables<R> tb, c
         }
         // pairs with the top site first, then with lower sites; coefficient index
         // [tile move up][outer move up]
-        int low = 0;
+        bool low = false;
         for (int p = m0; p < m1; p++) {
           const int4 ab = s_pij[p];
           const int a = uni(ab.x), nz = uni(ab.z);
           if (a != top) {
-            low += ((nz >> up) & 1) + ((nz >> (2 + up)) & 1);
+            low = low || ((nz >> up) & 5);
             continue;
           }
 #pragma unroll
@@ -391,15 +398,12 @@ __global__ __launch_bounds__(1024) void hv_sweep(SweepPass G, DevTables<R> tb, c
               top_move(Cx<R>{c.re * fk, c.im * fk}, tu != 0, z);
             }
         }
-        if (low == 0) continue;
-        const bool staged = stage_all || low > kDirect;
-        if (staged) {
-          __syncthreads();
-          if (act)
+        if (!low) continue;
+        __syncthreads();
+        if (act)
 #pragma unroll
-            for (int d = 0; d < RPT; d++) tile[q * SP + d] = z[d];
-          __syncthreads();
-        }
+          for (int d = 0; d < RPT; d++) tile[q * SP + d] = z[d];
+        __syncthreads();
 #pragma unroll 1
         for (int p = m0; p < m1; p++) {
           const int4 ab = s_pij[p];
@@ -412,12 +416,8 @@ __global__ __launch_bounds__(1024) void hv_sweep(SweepPass G, DevTables<R> tb, c
             const R fa = (au ? s_gm : s_gp)[a * 16 + da];
             const Cx<R> c = unic(s_pc[4 * p + 2 * au + up]);
             Cx<R> y[RPT];
-            if (staged) {
-              const int ws = (int)G.wst[a];
-              lds_rows(y, fa != R(0) ? (int)q + (au ? ws : -ws) : (int)q);
-            } else {
-              rows(y, shift, fa != R(0) ? goff + (au ? G.st[a] : 0u - G.st[a]) * (uint32_t)sizeof(Cx<R>) : goff);
-            }
+            const int ws = (int)G.wst[a];
+            lds_rows(y, fa != R(0) ? (int)q + (au ? ws : -ws) : (int)q);
             const R f = fa * fk;
             const Cx<R> cc{c.re * f, c.im * f};
 #pragma unroll
@@ -446,7 +446,7 @@ __global__ __launch_bounds__(1024) void hv_sweep(SweepPass G, DevTables<R> tb, c
     if (act) {
       // (the own rows are read again: held through the terms they cost registers)
       Cx<R> x[RPT];
-      if (G.last && P.lanczos) {
+      if (P.lanczos) {
         rows(x, 0, goff);
       } else {
 #pragma unroll
@@ -455,24 +455,15 @@ __global__ __launch_bounds__(1024) void hv_sweep(SweepPass G, DevTables<R> tb, c
 #pragma unroll
       for (int d = 0; d < RPT; d++) {
         const uint32_t row = base + goff / (uint32_t)sizeof(Cx<R>) + (uint32_t)d * stt;
-        if (!G.first) {
-          const Cx<R> o = ld_stream(w + row);
-          acc[d].re += o.re;
-          acc[d].im += o.im;
-        }
-        if (G.last) {
-          Acc<R, 1> a;
-          a.re[0] = acc[d].re;
-          a.im[0] = acc[d].im;
-          hv_epilogue<R, 1, true>(P, row, 0, a, &x[d], red);
-        } else {
-          st_stream(w + row, acc[d]);
-        }
+        Acc<R, 1> a;
+        a.re[0] = acc[d].re;
+        a.im[0] = acc[d].im;
+        hv_epilogue<R, 1, true>(P, row, 0, a, &x[d], red);
       }
     }
     __syncthreads();  // the next tile overwrites the LDS
   }
-  if (!G.last || !P.lanczos) return;
+  if (!P.lanczos) return;
   // (the block's size is the plan's: sum over its waves in order)
   __shared__ double part[16][3];
 #pragma unroll
@@ -490,7 +481,7 @@ __global__ __launch_bounds__(1024) void hv_sweep(SweepPass G, DevTables<R> tb, c
 
 template <typename R, int RPT, bool CPLX>
 void launch_t(const SweepPass &G, const SweepTables &S, const DevTables<R> &tb, const HvParams &P, unsigned gx,
-              uint32_t chunk, int stage_all, hipStream_t s) {
+              uint32_t chunk, hipStream_t s) {
   static std::atomic<size_t> granted{64 * 1024};  // per instantiation: largest dynamic LDS size requested so far
   const size_t sm = SweepLds<R>(G).total;
   if (sm > granted.load()) {
@@ -499,18 +490,17 @@ void launch_t(const SweepPass &G, const SweepTables &S, const DevTables<R> &tb, 
     granted.store(sm);
   }
   hipLaunchKernelGGL((hv_sweep<R, RPT, CPLX>), dim3(gx), dim3((G.Q + 63) / 64 * 64), sm, s, G, tb,
-                     S.d_pij + G.p0, reinterpret_cast<const Cx<R> *>(S.d_pc) + 4 * (size_t)G.p0,
-                     reinterpret_cast<const R *>(S.d_tdiag), chunk, stage_all, P);
+                     S.d_pij, reinterpret_cast<const Cx<R> *>(S.d_pc), reinterpret_cast<const R *>(S.d_tdiag), chunk, P);
 }
 
 template <typename R, bool CPLX>
 int launch_rpt(const SweepPass &G, const SweepTables &S, const DevTables<R> &tb, const HvParams &P, unsigned gx,
-               uint32_t chunk, int stage_all, hipStream_t s) {
+               uint32_t chunk, hipStream_t s) {
   switch (G.rtop) {
-    case 3: launch_t<R, 3, CPLX>(G, S, tb, P, gx, chunk, stage_all, s); break;
-    case 4: launch_t<R, 4, CPLX>(G, S, tb, P, gx, chunk, stage_all, s); break;
-    case 5: launch_t<R, 5, CPLX>(G, S, tb, P, gx, chunk, stage_all, s); break;
-    case 6: launch_t<R, 6, CPLX>(G, S, tb, P, gx, chunk, stage_all, s); break;
+    case 3: launch_t<R, 3, CPLX>(G, S, tb, P, gx, chunk, s); break;
+    case 4: launch_t<R, 4, CPLX>(G, S, tb, P, gx, chunk, s); break;
+    case 5: launch_t<R, 5, CPLX>(G, S, tb, P, gx, chunk, s); break;
+    case 6: launch_t<R, 6, CPLX>(G, S, tb, P, gx, chunk, s); break;
     default: return FTLM_EINVAL;
   }
   return FTLM_OK;
@@ -519,25 +509,28 @@ int launch_rpt(const SweepPass &G, const SweepTables &S, const DevTables<R> &tb,
 template <typename R>
 int launch_r(const SweepPlan &sp, const DevTables<R> &tb, const HvParams &P, int cap, int kc, unsigned *gx_out,
              hipStream_t s) {
-  if (sp.passes.empty() || !sp.tab.d_pij) return FTLM_EINVAL;
-  for (const SweepPass &G : sp.passes) {
-    HvParams Pp = P;
-    if (!G.last) Pp.lanczos = 0;
-    uint32_t gx = G.ntile < (uint32_t)cap ? G.ntile : (uint32_t)cap;
-    if (gx >= 8) gx &= ~7u;
-    const uint32_t chunk = G.chunk ? G.chunk : 1u << ((kc >> 4) & 15);
-    const int rc = sp.cplx ? launch_rpt<R, true>(G, sp.tab, tb, Pp, gx, chunk, (kc >> 8) & 1, s)
-                           : launch_rpt<R, false>(G, sp.tab, tb, Pp, gx, chunk, (kc >> 8) & 1, s);
-    if (rc) return rc;
-    *gx_out = gx;
+  if (!sp.ok || !sp.tab.d_pij) return FTLM_EINVAL;
+  const SweepPass &G = sp.pass;
+  if (cap <= 0) {
+    // the blocks resident at once on 256 CUs, by registers and by LDS
+    const int wv = (int)(G.Q + 63) / 64;
+    const int regs = 4 * sweep_waves(sizeof(R), G.rtop) / wv;
+    const int lds = (int)(160 * 1024 / (SweepLds<R>(G).total + 1024));
+    cap = 256 * std::max(1, std::min(regs, lds));
   }
-  return FTLM_OK;
+  cap = std::min(cap, 2048);
+  uint32_t gx = G.ntile < (uint32_t)cap ? G.ntile : (uint32_t)cap;
+  if (gx >= 8) gx &= ~7u;
+  *gx_out = gx;
+  const uint32_t chunk = 1u << ((kc >> 4) & 15);
+  return sp.cplx ? launch_rpt<R, true>(G, sp.tab, tb, P, gx, chunk, s)
+                 : launch_rpt<R, false>(G, sp.tab, tb, P, gx, chunk, s);
 }
 
 }  // namespace
 
-// Host plan: one pass whose tile takes the low sites while its rows fit tile_rows and
-// the values of the sites below the top one fit the block's 1024 threads.
+// Host plan: the tile takes the low sites while its rows fit tile_rows and the values of
+// the sites below the top one fit the block's threads.
 void plan_sweep(const HostHam &hh, size_t es, uint32_t tile_rows, SweepPlan &pl) {
   const SweepTables keep = pl.tab;
   pl = SweepPlan();
@@ -546,41 +539,35 @@ void plan_sweep(const HostHam &hh, size_t es, uint32_t tile_rows, SweepPlan &pl)
   if (hh.has_z || hh.spin_half || hh.dim < (1u << 16)) return;
   int t = 0;
   uint64_t T = 1;
-  while (t < n && t < 9 && T <= 1024 && T * (uint64_t)hh.radix[t] <= tile_rows) T *= (uint64_t)hh.radix[t++];
+  while (t < n && t < 9 && T <= (uint64_t)sweep_threads(hh.radix[t]) && T * (uint64_t)hh.radix[t] <= tile_rows)
+    T *= (uint64_t)hh.radix[t++];
   if (t < 2 || n - t > 16 || n - t < 1) return;
-  std::vector<int> tiles, outer;
-  for (int k = 0; k < n; k++) (k < t ? tiles : outer).push_back(k);
   const int rtop = hh.radix[t - 1];
   if (rtop < 3 || rtop > 6) return;  // the instantiated rows per thread
   SweepPass G{};
-  G.first = G.last = G.diag = 1;
   G.n = n;
   G.t = t;
   G.rtop = rtop;
   G.Q = (uint32_t)(T / rtop);
   G.ntile = (uint32_t)(hh.dim / T);
-  int pos[kMaxSites];
-  for (int i = 0; i < n; i++) {
-    const int k = i < t ? tiles[i] : outer[i - t];
-    pos[k] = i;
-    G.site[i] = k;
-    G.radix[i] = hh.radix[k];
-    G.st[i] = hh.stride[k];
-    G.wst[i] = i == 0 ? 1u : G.wst[i - 1] * (uint32_t)G.radix[i - 1];
-    G.s[i] = 0.5f * (float)hh.two_s[k];
-    if (site_has_singles(hh, k)) G.smask |= 1u << i;
+  for (int k = 0; k < n; k++) {
+    G.radix[k] = hh.radix[k];
+    G.st[k] = hh.stride[k];
+    G.wst[k] = k == 0 ? 1u : G.wst[k - 1] * (uint32_t)G.radix[k - 1];
+    G.s[k] = 0.5f * (float)hh.two_s[k];
+    if (site_has_singles(hh, k)) G.smask |= 1u << k;
     for (int d = 0; d + 2 < hh.radix[k]; d++) {
       const Cx<double> up = hh.h[(size_t)k * 256 + d * 16 + d + 2], dn = hh.h[(size_t)k * 256 + (d + 2) * 16 + d];
-      if (up.re != 0.0 || up.im != 0.0 || dn.re != 0.0 || dn.im != 0.0) G.smask2 |= 1u << i;
+      if (up.re != 0.0 || up.im != 0.0 || dn.re != 0.0 || dn.im != 0.0) G.smask2 |= 1u << k;
     }
   }
-  // pairs as positions (a, b): both lower | lower a, top b | tile a, outer b (by b) | outer
+  // pairs of sites (a, b): both lower | lower a, top b | tile a, outer b (by b) | outer
   struct E {
     int cls, a, b, p;
   };
   std::vector<E> es_;
   for (int p = 0; p < hh.npair; p++) {
-    int a = pos[hh.pi[p]], b = pos[hh.pj[p]];
+    int a = hh.pi[p], b = hh.pj[p];
     if (a > b) std::swap(a, b);
     es_.push_back({b >= t ? (a >= t ? 3 : 2) : (b == t - 1 ? 1 : 0), a, b, p});
   }
@@ -593,7 +580,7 @@ void plan_sweep(const HostHam &hh, size_t es, uint32_t tile_rows, SweepPlan &pl)
   bool cplx = false;
   for (int e = 0; e < G.np; e++) {
     const E &x = es_[e];
-    const bool swapped = pos[hh.pi[x.p]] != x.a;
+    const bool swapped = hh.pi[x.p] != x.a;
     int nz = 0;
     for (int qa = 0; qa < 2; qa++)
       for (int qb = 0; qb < 2; qb++) {
@@ -628,17 +615,17 @@ void plan_sweep(const HostHam &hh, size_t es, uint32_t tile_rows, SweepPlan &pl)
     for (int i = 0; i < t; i++) {
       d[i] = (int)(rem % (uint32_t)G.radix[i]);
       rem /= (uint32_t)G.radix[i];
-      const int k = G.site[i];
-      sum += hh.h[(size_t)k * 256 + d[i] * 16 + d[i]].re;
+      sum += hh.h[(size_t)i * 256 + d[i] * 16 + d[i]].re;
       for (int j = 0; j < i; j++)
-        sum += hh.zz[(size_t)k * n + G.site[j]] * (d[i] - 0.5 * hh.two_s[k]) * (d[j] - 0.5 * hh.two_s[G.site[j]]);
+        sum += hh.zz[(size_t)i * n + j] * (d[i] - 0.5 * hh.two_s[i]) * (d[j] - 0.5 * hh.two_s[j]);
     }
     pl.tdiag[r] = sum;
   }
   // a thread's byte offset in its tile has 32 bits; the block's tables and tile share the LDS
   const size_t lds = es == 16 ? SweepLds<double>(G).total : SweepLds<float>(G).total;
   if (lds > 159 * 1024) return;  // 1 KB for static LDS
-  pl.passes.push_back(G);
+  pl.pass = G;
+  pl.ok = true;
 }
 
 int launch_sweep(const DevHam &dh, int precision, const HvParams &P, int cap, int kc, unsigned *gx, hipStream_t s) {
