@@ -101,8 +101,9 @@ int ftlm_apply(const ftlm_hamiltonian *h, int32_t precision, int32_t n_cols, con
  * the caller's device buffers v, w ([dim][n_cols], as ftlm_apply) -- variants
  * 1 = direct gather (columns per lane 1, 2, 4, 8), 2 = windowed LDS passes,
  * 3 = LDS tile (spin 1/2, N >= 11), 4 = L2-window passes (one column), 5 = LDS
- * tile walked over L2 windows (spin 1/2, N >= 12; 256, 512 or 1024 threads per
- * tile, given in the columns-per-lane field as 1, 2 or 4 row groups), 6 = single pass
+ * tile walked over L2 windows (spin 1/2, N >= 12; with several columns 256, 512 or
+ * 1024 threads per tile, given in the columns-per-lane field as 1, 2 or 4 row groups;
+ * one column takes 256 threads and ignores the field), 6 = single pass
  * over LDS tiles of the low digits with coalesced partner reads for the terms
  * on outer sites (one column; Hamiltonians without s+- s^z pair pieces, i.e.
  * whose single-flip coefficients do not depend on the other sites; the
@@ -320,8 +321,8 @@ int ftlm_adam_step(int64_t n, float *p, const float *grad, float *m, float *v, u
  * described) afterwards; 0 selects the default.  pass_kb: LDS windows of the
  * multi-pass kernel (variant 2; 4..128, default 64).  l2_kb: L2 windows of the
  * window kernels of variant 4 (4..65536, default 1024).  tile_kb: L2 windows of
- * the tile-window kernel (variant 5; 4..65536, default 2048, or a single window
- * when the vector is at most 160 MB).  Existing handles keep their plans.  The
+ * the tile-window kernels (variant 5; 4..65536, default 8192, or a single window
+ * when the vector is at most 96 MB).  Existing handles keep their plans.  The
  * setting is process-wide; calls concurrent with handle creation race.
  * FTLM_EINVAL (settings unchanged) for a value outside its range. */
 int ftlm_set_plan_windows(int32_t pass_kb, int32_t l2_kb, int32_t tile_kb);

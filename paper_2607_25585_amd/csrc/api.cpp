@@ -286,6 +286,11 @@ uint64_t launch_signature(const DevHam &dh) {
     f.vec(pl->passes);
     f.pod(pl->d_plist);
     f.pod(pl->d_pcoef);
+    f.pod(pl->half.d_grp);
+    f.pod(pl->half.d_msk);
+    f.pod(pl->half.d_gco);
+    f.pod(pl->half.d_mco);
+    f.pod(pl->half.d_tdiag);
   }
   for (const StreamPlan *sp : {&dh.sp64, &dh.sp32}) {
     f.pod(sp->ok);
@@ -387,6 +392,28 @@ int upload_tables(const HostHam &hh, DevHam &dh, std::string &err) {
   const std::vector<Cx<float>> tc32 = plist_coefs<float>(hh, perm, dh.tw32.plist);
   const size_t off_c64 = b.add(tc64.data(), tc64.size() * sizeof(Cx<double>));
   const size_t off_c32 = b.add(tc32.data(), tc32.size() * sizeof(Cx<float>));
+  size_t off_h[2][5] = {{0}};
+  for (int q = 0; q < 2; q++) {
+    WinPlan &tw = q ? dh.tw32 : dh.tw64;
+    if (tw.passes.empty()) continue;
+    plan_half(hh, q ? plist_coefs<double>(hh, perm, tw.plist) : tc64, tw);
+    const HalfTables &H = tw.half;
+    off_h[q][0] = b.add(H.grp.data(), H.grp.size() * sizeof(uint32_t));
+    off_h[q][1] = b.add(H.msk.data(), H.msk.size() * sizeof(uint32_t));
+    if (q == 0) {
+      off_h[q][2] = b.add(H.gco.data(), H.gco.size() * sizeof(Cx<double>));
+      off_h[q][3] = b.add(H.mco.data(), H.mco.size() * sizeof(Cx<double>));
+      off_h[q][4] = b.add(H.tdiag.data(), H.tdiag.size() * sizeof(double));
+    } else {
+      std::vector<Cx<float>> g32, m32;
+      for (const Cx<double> &c : H.gco) g32.push_back(Cx<float>{(float)c.re, (float)c.im});
+      for (const Cx<double> &c : H.mco) m32.push_back(Cx<float>{(float)c.re, (float)c.im});
+      const std::vector<float> t32(H.tdiag.begin(), H.tdiag.end());
+      off_h[q][2] = b.add(g32.data(), g32.size() * sizeof(Cx<float>));
+      off_h[q][3] = b.add(m32.data(), m32.size() * sizeof(Cx<float>));
+      off_h[q][4] = b.add(t32.data(), t32.size() * sizeof(float));
+    }
+  }
   // single-pass tile plans (64 KB tiles); field dependent (single flips,
   // complex coefficients, the tile diagonal)
   plan_stream(hh, 65536 / sizeof(Cx<double>), dh.sp64);
@@ -465,6 +492,15 @@ int upload_tables(const HostHam &hh, DevHam &dh, std::string &err) {
   dh.win32.d_plist = reinterpret_cast<const int4 *>(base + off_w32);
   dh.tw64.d_plist = dh.tw64.plist.empty() ? nullptr : reinterpret_cast<const int4 *>(base + off_t64);
   dh.tw32.d_plist = dh.tw32.plist.empty() ? nullptr : reinterpret_cast<const int4 *>(base + off_t32);
+  for (int q = 0; q < 2; q++) {
+    WinPlan &tw = q ? dh.tw32 : dh.tw64;
+    const bool ok = !tw.passes.empty();
+    tw.half.d_grp = ok ? reinterpret_cast<const uint32_t *>(base + off_h[q][0]) : nullptr;
+    tw.half.d_msk = ok ? reinterpret_cast<const uint32_t *>(base + off_h[q][1]) : nullptr;
+    tw.half.d_gco = ok ? base + off_h[q][2] : nullptr;
+    tw.half.d_mco = ok ? base + off_h[q][3] : nullptr;
+    tw.half.d_tdiag = ok ? base + off_h[q][4] : nullptr;
+  }
   dh.tw64.d_pcoef = dh.tw64.plist.empty() ? nullptr : base + off_c64;
   dh.tw32.d_pcoef = dh.tw32.plist.empty() ? nullptr : base + off_c32;
   {

@@ -219,6 +219,20 @@ struct WinPass {
   int na, ni;
   int act[kMaxSites], wrad[kMaxSites];
   int inact[kMaxSites], irad[kMaxSites];
+  // half sweep: the in-tile groups of layout L are [hg[L], hg[L + 1]); first outer-site record
+  int hg[5], hm0;
+};
+
+// Tables of the half sweep (half_sweep.hip) for a tile plan.
+struct HalfTables {
+  std::vector<uint32_t> grp;      // member mask | (lane site + 1, or 0) << 3; at most 19 per pass
+  std::vector<Cx<double>> gco;    // [group][member][4]
+  std::vector<uint32_t> msk;      // [outer site of a pass]: tile sites coupled to it
+  std::vector<Cx<double>> mco;    // [outer site of a pass][its bit][tile site][the site's bit]
+  std::vector<double> tdiag;      // [2048] diagonal over the tile's sites
+  const uint32_t *d_grp = nullptr;  // device copies (inside the handle's table block)
+  const uint32_t *d_msk = nullptr;
+  const void *d_gco = nullptr, *d_mco = nullptr, *d_tdiag = nullptr;  // in the plan's precision
 };
 
 struct WinPlan {
@@ -232,7 +246,10 @@ struct WinPlan {
   // row bits b_i << 1 | b_j) in plist order, in the plan's precision, so that
   // an entry's coefficients are addressed by its position alone
   const void *d_pcoef = nullptr;
+  HalfTables half;  // tile plans
 };
+// Fills plan.half and the passes' records of it; pcoef: the coefficients in plist order.
+void plan_half(const HostHam &hh, const std::vector<Cx<double>> &pcoef, WinPlan &plan);
 
 // Single-pass H*v for one column ("stream" kernel, variant 6).  Rows are walked
 // in tiles of the low digits: a tile is the T = st_t consecutive rows that share
@@ -405,6 +422,8 @@ int launch_stream(const DevHam &dh, int precision, const HvParams &P, int cap, i
 // resident at once; kc: bits 4..7 as above (every group's partner tile is staged).
 int launch_sweep(const DevHam &dh, int precision, const HvParams &P, int cap, int kc, unsigned *gx,
                  hipStream_t s);
+// Variant 5, one column (half_sweep.hip).
+int launch_half_sweep(const DevHam &dh, int precision, const HvParams &P, int cap, unsigned *gx, hipStream_t s);
 // (Re)computes the per-window records of both pass plans (allocates rec_block on
 // first use).  Synchronous.
 int build_pass_records(DevHam &dh, std::string &err);

@@ -18,6 +18,7 @@
 
 #include "device_reduce.hpp"
 #include "ftlm_internal.hpp"
+#include "half_win.hpp"
 #include "hv_common.hpp"
 
 namespace ftlm {
@@ -1101,40 +1102,6 @@ __global__ __launch_bounds__(kBlock) void hv_gen(HamGeom g, const uint4 *__restr
 }
 
 // ------------------------------------------------------------------ L2-window passes
-// Scatters the low bits of x to the set bits of mask (ascending).
-__device__ __forceinline__ uint32_t scatter_bits(uint32_t x, uint32_t mask) {
-  uint32_t r = 0;
-  while (mask) {
-    const uint32_t low = mask & (0u - mask);
-    if (x & 1u) r |= low;
-    x >>= 1;
-    mask &= mask - 1u;
-  }
-  return r;
-}
-
-// Work-item walk of one L2-window pass.  With at least 8 windows and a grid that
-// is a multiple of 8, block b runs on XCD b % 8 (workgroups are dispatched to the
-// XCDs round robin); XCD x owns windows x, x+8, ... and its blocks walk the
-// items of those windows in order, so the windows an XCD works on at any time
-// are consecutive in its list and their rows stay in that XCD's L2 (as many
-// windows are in flight as the XCD's blocks cover: nb / nin).  Otherwise the
-// items are walked flat.  body(win, item) is called for every item of the pass.
-template <typename F>
-__device__ __forceinline__ void win_walk(const WinPass &W, F &&body) {
-  const bool xcd = W.nwin >= 8 && (gridDim.x & 7u) == 0;
-  const uint32_t x = xcd ? (blockIdx.x & 7u) : 0u;
-  const uint64_t nwx = xcd ? (uint64_t)((W.nwin - x + 7u) >> 3) : (uint64_t)W.nwin;
-  const uint64_t jn = nwx * W.nin;
-  const uint64_t jstart = xcd ? (blockIdx.x >> 3) : blockIdx.x;
-  const uint64_t jstep = xcd ? (gridDim.x >> 3) : gridDim.x;
-  for (uint64_t j = jstart; j < jn; j += jstep) {
-    const uint32_t wl = (uint32_t)(j / W.nin);
-    const uint32_t item = (uint32_t)(j - (uint64_t)wl * W.nin);
-    body(xcd ? x + 8u * wl : wl, item);
-  }
-}
-
 // Adds the earlier passes' partial sum, then stores the raw partial (not the
 // last pass) or runs the epilogue (last pass).  KC columns from c0.
 template <typename R, int KC>
@@ -2178,8 +2145,7 @@ static size_t hv_tile_win_smem(const HamGeom &g, const WinPass &W) {
 // Threads per tile-window block: 256 G (G groups of rows on one LDS tile).
 // want = 1, 2 or 4 (the tuned choice), else 2: the tile's LDS allows two blocks per
 // CU at complex128, so a second group doubles the resident waves.  At complex64
-// four 256-thread blocks fit and G = 1 is faster once there are four tiles per CU
-// (2^21 rows: 143 us against 188; 2^20: 106 against 88).
+// four 256-thread blocks fit and G = 1 is faster once there are four tiles per CU.
 static int tile_win_groups(int want, bool f32, uint32_t dim) {
   if (want == 1 || want == 2 || want == 4) return want;
   return f32 && dim >= (1u << 21) ? 1 : 2;
@@ -2234,13 +2200,13 @@ int launch_hv(const DevHam &dh, const HvLaunch &Lin, hipStream_t s) {
   // it beat the multi-pass and tile kernels on every such workload measured
   if (!L.variant && L.K == 1 && dh.geom.dim >= (1u << 20) && (L.precision == FTLM_C64 ? dh.sp32 : dh.sp64).ok)
     L.variant = 6;
-  // spin-1/2 systems with those pieces: the LDS tile kernel over L2 windows from
-  // 2^19 rows, below that the direct gather.  Measured with all pairs coupled
-  // (us, complex128 / complex64):
-  //   rows            2^17       2^18       2^19       2^20       2^22       2^24
-  //   direct gather   29 / 26    49 / 39    96 / 85    181 / 163  882 / 762  4619 / 3633
-  //   LDS tile        98 / 71    120 / 78   142 / 92   159 / 109  792 / 405  3759 / 1850
-  //   over windows    54 / 48    78 / 53    91 / 73    117 / 88   544 / 298  2660 / 1454
+  // spin-1/2 systems with those pieces: the half sweep over L2 windows from 2^19 rows,
+  // below that the direct gather.  Measured with all pairs coupled (us, complex128 /
+  // complex64):
+  //   rows            2^18       2^19       2^20       2^22       2^24
+  //   direct gather   49 / 39    96 / 85    181 / 163  882 / 762  4619 / 3633
+  //   LDS tile        120 / 78   142 / 92   159 / 109  792 / 405  3759 / 1850
+  //   half sweep      47 / 38    55 / 46    81 / 60    402 / 211  2210 / 1177
   // (a tile walks its pairs serially, so a vector of few tiles leaves the chip idle)
   if (!L.variant && L.K == 1 && dh.geom.spin_half) {
     const WinPlan &tw = L.precision == FTLM_C64 ? dh.tw32 : dh.tw64;
@@ -2285,8 +2251,10 @@ int launch_hv(const DevHam &dh, const HvLaunch &Lin, hipStream_t s) {
     fin_kc = 1;
   } else if (L.variant == 5) {
     const int cap = L.grid_cap > 0 ? std::min(L.grid_cap, 2048) : 2048;
-    // (the columns-per-lane field carries the row groups per tile)
-    rc = (L.precision == FTLM_C64) ? launch_tile_win<float>(dh, dh.t32, dh.tw32, P, cap, L.kc, &fin_gx, s)
+    // one column: the half sweep; more columns: the tile kernel, a column per grid row (the
+    // columns-per-lane field carries its row groups per tile)
+    if (L.K == 1) rc = launch_half_sweep(dh, L.precision, P, L.grid_cap, &fin_gx, s);
+    else rc = (L.precision == FTLM_C64) ? launch_tile_win<float>(dh, dh.t32, dh.tw32, P, cap, L.kc, &fin_gx, s)
                                    : launch_tile_win<double>(dh, dh.t64, dh.tw64, P, cap, L.kc, &fin_gx, s);
     fin_gy = (unsigned)L.K;
     fin_kc = 1;
