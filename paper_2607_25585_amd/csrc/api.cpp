@@ -282,7 +282,8 @@ uint64_t launch_signature(const DevHam &dh) {
     f.vec(pl->base_off);
     f.vec(pl->lane_off);
   }
-  for (const WinPlan *pl : {&dh.win64, &dh.win32, &dh.tw64, &dh.tw32}) {
+  for (const WinPlan *pl : {&dh.win64, &dh.win32, &dh.tw64, &dh.tw32, &dh.twc[0][0], &dh.twc[0][1], &dh.twc[0][2],
+                            &dh.twc[1][0], &dh.twc[1][1], &dh.twc[1][2]}) {
     f.vec(pl->passes);
     f.pod(pl->d_plist);
     f.pod(pl->d_pcoef);
@@ -392,28 +393,44 @@ int upload_tables(const HostHam &hh, DevHam &dh, std::string &err) {
   const std::vector<Cx<float>> tc32 = plist_coefs<float>(hh, perm, dh.tw32.plist);
   const size_t off_c64 = b.add(tc64.data(), tc64.size() * sizeof(Cx<double>));
   const size_t off_c32 = b.add(tc32.data(), tc32.size() * sizeof(Cx<float>));
-  size_t off_h[2][5] = {{0}};
-  for (int q = 0; q < 2; q++) {
-    WinPlan &tw = q ? dh.tw32 : dh.tw64;
-    if (tw.passes.empty()) continue;
-    plan_half(hh, q ? plist_coefs<double>(hh, perm, tw.plist) : tc64, tw);
-    const HalfTables &H = tw.half;
-    off_h[q][0] = b.add(H.grp.data(), H.grp.size() * sizeof(uint32_t));
-    off_h[q][1] = b.add(H.msk.data(), H.msk.size() * sizeof(uint32_t));
-    if (q == 0) {
-      off_h[q][2] = b.add(H.gco.data(), H.gco.size() * sizeof(Cx<double>));
-      off_h[q][3] = b.add(H.mco.data(), H.mco.size() * sizeof(Cx<double>));
-      off_h[q][4] = b.add(H.tdiag.data(), H.tdiag.size() * sizeof(double));
-    } else {
-      std::vector<Cx<float>> g32, m32;
-      for (const Cx<double> &c : H.gco) g32.push_back(Cx<float>{(float)c.re, (float)c.im});
-      for (const Cx<double> &c : H.mco) m32.push_back(Cx<float>{(float)c.re, (float)c.im});
-      const std::vector<float> t32(H.tdiag.begin(), H.tdiag.end());
-      off_h[q][2] = b.add(g32.data(), g32.size() * sizeof(Cx<float>));
-      off_h[q][3] = b.add(m32.data(), m32.size() * sizeof(Cx<float>));
-      off_h[q][4] = b.add(t32.data(), t32.size() * sizeof(float));
+  // the half sweep's tables: tile plans, and plans of 2, 4 and 8 columns from the size on
+  // where they are the built-in choice
+  struct HalfOff {
+    WinPlan *pl;
+    bool f32;
+    size_t off[7];
+  };
+  std::vector<HalfOff> halves;
+  for (int q = 0; q < 2; q++)
+    for (int f = 0; f < 4; f++) {
+      WinPlan &tw = f ? dh.twc[q][f - 1] : q ? dh.tw32 : dh.tw64;
+      if (f) {
+        tw = WinPlan();
+        if (hh.spin_half && n > kTileBits && (uint64_t)hh.dim << f >= kHalfColumnsRows) plan_columns(hh, spi, spj, f, tw);
+      }
+      if (tw.passes.empty()) continue;
+      const std::vector<Cx<double>> pc = plist_coefs<double>(hh, perm, tw.plist);
+      plan_half(hh, pc, f, tw);
+      const HalfTables &H = tw.half;
+      HalfOff h{&tw, q != 0, {}};
+      auto add_cx = [&](const std::vector<Cx<double>> &x) {
+        if (!q) return b.add(x.data(), x.size() * sizeof(Cx<double>));
+        std::vector<Cx<float>> y;
+        for (const Cx<double> &c : x) y.push_back(Cx<float>{(float)c.re, (float)c.im});
+        return b.add(y.data(), y.size() * sizeof(Cx<float>));
+      };
+      h.off[0] = b.add(H.grp.data(), H.grp.size() * sizeof(uint32_t));
+      h.off[1] = b.add(H.msk.data(), H.msk.size() * sizeof(uint32_t));
+      h.off[2] = add_cx(H.gco);
+      h.off[3] = add_cx(H.mco);
+      const std::vector<float> td(H.tdiag.begin(), H.tdiag.end());
+      h.off[4] = q ? b.add(td.data(), td.size() * sizeof(float)) : b.add(H.tdiag.data(), H.tdiag.size() * sizeof(double));
+      if (f) {
+        h.off[5] = b.add(tw.plist.data(), tw.plist.size() * sizeof(int4));
+        h.off[6] = add_cx(pc);
+      }
+      halves.push_back(h);
     }
-  }
   // single-pass tile plans (64 KB tiles); field dependent (single flips,
   // complex coefficients, the tile diagonal)
   plan_stream(hh, 65536 / sizeof(Cx<double>), dh.sp64);
@@ -492,14 +509,18 @@ int upload_tables(const HostHam &hh, DevHam &dh, std::string &err) {
   dh.win32.d_plist = reinterpret_cast<const int4 *>(base + off_w32);
   dh.tw64.d_plist = dh.tw64.plist.empty() ? nullptr : reinterpret_cast<const int4 *>(base + off_t64);
   dh.tw32.d_plist = dh.tw32.plist.empty() ? nullptr : reinterpret_cast<const int4 *>(base + off_t32);
-  for (int q = 0; q < 2; q++) {
-    WinPlan &tw = q ? dh.tw32 : dh.tw64;
-    const bool ok = !tw.passes.empty();
-    tw.half.d_grp = ok ? reinterpret_cast<const uint32_t *>(base + off_h[q][0]) : nullptr;
-    tw.half.d_msk = ok ? reinterpret_cast<const uint32_t *>(base + off_h[q][1]) : nullptr;
-    tw.half.d_gco = ok ? base + off_h[q][2] : nullptr;
-    tw.half.d_mco = ok ? base + off_h[q][3] : nullptr;
-    tw.half.d_tdiag = ok ? base + off_h[q][4] : nullptr;
+  dh.tw64.half.d_grp = dh.tw32.half.d_grp = nullptr;
+  for (const HalfOff &h : halves) {
+    HalfTables &H = h.pl->half;
+    H.d_grp = reinterpret_cast<const uint32_t *>(base + h.off[0]);
+    H.d_msk = reinterpret_cast<const uint32_t *>(base + h.off[1]);
+    H.d_gco = base + h.off[2];
+    H.d_mco = base + h.off[3];
+    H.d_tdiag = base + h.off[4];
+    if (h.off[5]) {
+      h.pl->d_plist = reinterpret_cast<const int4 *>(base + h.off[5]);
+      h.pl->d_pcoef = base + h.off[6];
+    }
   }
   dh.tw64.d_pcoef = dh.tw64.plist.empty() ? nullptr : base + off_c64;
   dh.tw32.d_pcoef = dh.tw32.plist.empty() ? nullptr : base + off_c32;

@@ -223,13 +223,16 @@ struct WinPass {
   int hg[5], hm0;
 };
 
+// Rows times columns from which several columns take the half sweep by default.
+constexpr uint64_t kHalfColumnsRows = 1ull << 19;
+
 // Tables of the half sweep (half_sweep.hip) for a tile plan.
 struct HalfTables {
   std::vector<uint32_t> grp;      // member mask | (lane site + 1, or 0) << 3; at most 19 per pass
   std::vector<Cx<double>> gco;    // [group][member][4]
   std::vector<uint32_t> msk;      // [outer site of a pass]: tile sites coupled to it
   std::vector<Cx<double>> mco;    // [outer site of a pass][its bit][tile site][the site's bit]
-  std::vector<double> tdiag;      // [2048] diagonal over the tile's sites
+  std::vector<double> tdiag;      // [2048 / columns] diagonal over the tile's sites
   const uint32_t *d_grp = nullptr;  // device copies (inside the handle's table block)
   const uint32_t *d_msk = nullptr;
   const void *d_gco = nullptr, *d_mco = nullptr, *d_tdiag = nullptr;  // in the plan's precision
@@ -249,7 +252,9 @@ struct WinPlan {
   HalfTables half;  // tile plans
 };
 // Fills plan.half and the passes' records of it; pcoef: the coefficients in plist order.
-void plan_half(const HostHam &hh, const std::vector<Cx<double>> &pcoef, WinPlan &plan);
+void plan_half(const HostHam &hh, const std::vector<Cx<double>> &pcoef, int f, WinPlan &plan);
+// The half sweep's plan for 2^f columns (f = 1, 2, 3).
+void plan_columns(const HostHam &hh, const std::vector<int> &pi, const std::vector<int> &pj, int f, WinPlan &plan);
 
 // Single-pass H*v for one column ("stream" kernel, variant 6).  Rows are walked
 // in tiles of the low digits: a tile is the T = st_t consecutive rows that share
@@ -330,6 +335,7 @@ struct DevHam {
   PassPlan plan64, plan32;  // windowed-pass plans for complex128 / complex64
   WinPlan win64, win32;     // L2-window plans for complex128 / complex64
   WinPlan tw64, tw32;       // L2-window plans of the LDS tile kernel (spin 1/2, N >= 12)
+  WinPlan twc[2][3];        // half sweep of 2, 4 and 8 columns [precision][log2 columns - 1]
   StreamPlan sp64, sp32;    // single-pass tile plans (complex128 / complex64)
   SweepPlan sw64, sw32;     // tile sweep plans
   // key of the plans above (recomputed only when it changes)
@@ -422,7 +428,7 @@ int launch_stream(const DevHam &dh, int precision, const HvParams &P, int cap, i
 // resident at once; kc: bits 4..7 as above (every group's partner tile is staged).
 int launch_sweep(const DevHam &dh, int precision, const HvParams &P, int cap, int kc, unsigned *gx,
                  hipStream_t s);
-// Variant 5, one column (half_sweep.hip).
+// Variant 5, 1, 2, 4 or 8 columns (half_sweep.hip).
 int launch_half_sweep(const DevHam &dh, int precision, const HvParams &P, int cap, unsigned *gx, hipStream_t s);
 // (Re)computes the per-window records of both pass plans (allocates rec_block on
 // first use).  Synchronous.

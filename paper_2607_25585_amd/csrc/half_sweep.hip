@@ -1,5 +1,6 @@
-// Half sweep: H*v for one column of a spin-1/2 system (variant 5), over L2 windows of
-// 2048-row tiles (Sec. 2.1, Eq. mce-hamop, with the flips of a site as XORs of row bits).
+// Half sweep: H*v for 1, 2, 4 or 8 columns of a spin-1/2 system (variant 5), over L2 windows
+// of 2048-row tiles (Sec. 2.1, Eq. mce-hamop, with the flips of a site as XORs of row bits).
+// Several columns are the lowest bits of the row number, which no term moves.
 //
 // A block of 256 threads holds a tile (row bits 0..10); a thread holds 8 rows, the values
 // of three row bits, in one of four layouts:
@@ -25,8 +26,10 @@
 //
 // Measured (one product, all pairs coupled, complex128 / complex64), against a tile of the
 // same size whose threads kept to layout 0 and read every flip of a lane's site from LDS:
-//   2^19 rows  91 -> 55 / 73 -> 46 us      2^22 rows  571 -> 402 / 298 -> 211 us
-//   2^20 rows  125 -> 81 / 90 -> 60 us     2^24 rows  2.67 -> 2.21 / 1.45 -> 1.18 ms
+//   2^19 rows  91 -> 52 / 73 -> 45 us      2^22 rows  571 -> 396 / 298 -> 207 us
+//   2^20 rows  125 -> 77 / 90 -> 58 us     2^24 rows  2.67 -> 2.28 / 1.45 -> 1.18 ms
+// and, with columns, against the direct gather: 2^19 rows x 4  375 -> 174 / 143 -> 107 us,
+// 2^21 x 8  6.6 -> 2.6 / 1.9 -> 1.1 ms.
 // What bounds it: latency.  At complex128 the four layouts' sums take the registers of two
 // waves per SIMD; 2^22 rows keep the vector units busy for a third of the time, the LDS for
 // an eighth.  Lists and coefficients read by scalar loads, with a wait each, and addresses
@@ -211,13 +214,15 @@ __device__ __forceinline__ void outer_pairs(Cx<R> (&acc)[kRows], uint32_t tile, 
   }
 }
 
-template <typename R>
+template <typename R, bool COLS>
 __global__ __launch_bounds__(kBlock, sizeof(R) == 8 ? 2 : 3) void hv_half_sweep(
     HamGeom g, DevTables<R> tb, WinPass W, const uint32_t *__restrict__ grp, const Cx<R> *__restrict__ gco,
     const uint32_t *__restrict__ msk, const Cx<R> *__restrict__ mco, const R *__restrict__ tdiag,
-    const int4 *__restrict__ plist, const Cx<R> *__restrict__ pcl, HvParams P) {
+    const int4 *__restrict__ plist, const Cx<R> *__restrict__ pcl, int log_cols, HvParams P) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const int n = g.n, ngrp = W.hg[4] - W.hg[0];
+  // sites are named by their row bits: site k is bit k + f, the bits below f the column
+  const int f = COLS ? log_cols : 0;
+  const int ns = g.n, n = ns + f, ngrp = W.hg[4] - W.hg[0];
   const HalfLds<R> L(n, ngrp);
   Cx<R> *buf = reinterpret_cast<Cx<R> *>(smem + L.buf);
   Cx<R> *s_gc = reinterpret_cast<Cx<R> *>(smem + L.gc);        // [group][member][4]
@@ -236,20 +241,20 @@ __global__ __launch_bounds__(kBlock, sizeof(R) == 8 ? 2 : 3) void hv_half_sweep(
   const int4 pair0 = lane < np_out ? pl[e_out + lane] : make_int4(0, 0, 0, 0);
   const Cx<R> *__restrict__ v = reinterpret_cast<const Cx<R> *>(P.v);
   for (int i = t; i < 12 * ngrp; i += kBlock) s_gc[i] = gco[12 * (size_t)W.hg[0] + i];
-  for (int i = t; i < 2 * n; i += kBlock) s_hd[i] = tb.hdiag[(i >> 1) * 16 + (i & 1)];
+  for (int i = t; i < 2 * n; i += kBlock) s_hd[i] = i < 2 * f ? R(0) : tb.hdiag[((i >> 1) - f) * 16 + (i & 1)];
   if (W.smask) {
     // the field that the slot bits (8..10) put on each site's flip
     for (int i = t; i < 16 * n; i += kBlock) {
       const int k = i >> 4, sel = (i >> 3) & 1, sl = i & 7;
-      Cx<R> f{0, 0};
+      Cx<R> fs{0, 0};
       for (int s = 0; s < 3; s++) {
-        if (kLowBits + s == k) continue;
-        const Cx<R> c = tb.cz_half[(k * n + kLowBits + s) * 2 + sel];
+        if (kLowBits + s == k || k < f) continue;
+        const Cx<R> c = tb.cz_half[((k - f) * ns + kLowBits + s - f) * 2 + sel];
         const R m = (sl >> s) & 1 ? R(0.5) : R(-0.5);
-        f.re = fma(c.re, m, f.re);
-        f.im = fma(c.im, m, f.im);
+        fs.re = fma(c.re, m, fs.re);
+        fs.im = fma(c.im, m, fs.im);
       }
-      s_fslot[i] = f;
+      s_fslot[i] = fs;
     }
   }
   double red[3][1] = {{0.0}, {0.0}, {0.0}};
@@ -280,31 +285,31 @@ __global__ __launch_bounds__(kBlock, sizeof(R) == 8 ? 2 : 3) void hv_half_sweep(
     __syncthreads();  // (the last tile's reads of the LDS)
     // per tile: the outer sites' field on every site's flip, and z-fields
     if (t < 2u * n) {
-      if (W.smask) {
+      if (W.smask && t >= 2u * f) {
         const int k = t >> 1, sel = t & 1;
-        Cx<R> f = tb.hflip[t];
+        Cx<R> fd = tb.hflip[t - 2 * f];
         if (g.has_z)
           for (int j0 = kTileBits; j0 < n; j0 += 7) {  // seven loads in flight; weight 0 past n
             Cx<R> c[7];
 #pragma unroll
-            for (int u = 0; u < 7; u++) c[u] = tb.cz_half[(k * n + (j0 + u < n ? j0 + u : n - 1)) * 2 + sel];
+            for (int u = 0; u < 7; u++) c[u] = tb.cz_half[((k - f) * ns + (j0 + u < n ? j0 + u : n - 1) - f) * 2 + sel];
 #pragma unroll
             for (int u = 0; u < 7; u++) {
               const int j = j0 + u;
               const R m = j == k || j >= n ? R(0) : mz(j);
-              f.re = fma(c[u].re, m, f.re);
-              f.im = fma(c[u].im, m, f.im);
+              fd.re = fma(c[u].re, m, fd.re);
+              fd.im = fma(c[u].im, m, fd.im);
             }
           }
-        s_fb[t] = f;
+        s_fb[t] = fd;
       }
     } else if (W.diag && t >= 64 && t < 64u + n) {
       const int i = t - 64;
       R ph = 0;
-      for (int j0 = i < kTileBits ? kTileBits : i + 1; j0 < n; j0 += 7) {
+      for (int j0 = i < f ? n : i < kTileBits ? kTileBits : i + 1; j0 < n; j0 += 7) {
         R c[7];
 #pragma unroll
-        for (int u = 0; u < 7; u++) c[u] = tb.zz[i * n + (j0 + u < n ? j0 + u : n - 1)];
+        for (int u = 0; u < 7; u++) c[u] = tb.zz[(i - f) * ns + (j0 + u < n ? j0 + u : n - 1) - f];
 #pragma unroll
         for (int u = 0; u < 7; u++) ph = fma(c[u], j0 + u < n ? mz(j0 + u) : R(0), ph);
       }
@@ -324,7 +329,7 @@ __global__ __launch_bounds__(kBlock, sizeof(R) == 8 ? 2 : 3) void hv_half_sweep(
       const R f0 = R(0.5) * s_phi[8], f1 = R(0.5) * s_phi[9], f2 = R(0.5) * s_phi[10];
 #pragma unroll
       for (int q = 0; q < kRows; q++) {
-        const R d = tdiag[q * kBlock + t] + (dg + ((q & 1 ? f0 : -f0) + ((q & 2 ? f1 : -f1) + (q & 4 ? f2 : -f2))));
+        const R d = tdiag[(q * kBlock + t) >> f] + (dg + ((q & 1 ? f0 : -f0) + ((q & 2 ? f1 : -f1) + (q & 4 ? f2 : -f2))));
         acc[q] = Cx<R>{d * z[q].re, d * z[q].im};
       }
     }
@@ -333,9 +338,15 @@ __global__ __launch_bounds__(kBlock, sizeof(R) == 8 ? 2 : 3) void hv_half_sweep(
       const Cx<R> a1 = s_fb[2 * k + b], a3 = s_fslot[(2 * k + b) * 8 + q];
       return Cx<R>{a1.re + a2.re + a3.re, a1.im + a2.im + a3.im};
     };
-    // (the next site's field is loaded ahead)
-    Cx<R> a2n{0, 0};
-    auto field = [&](int k, int b) -> Cx<R> { return tb.lowf[(k * 2 + b) * 256 + t]; };
+    // The field of the sites on row bits f..7.  The table holds that of the sites 0..7;
+    // the f highest of them, on bits 8 and up, drop out of the mean over both their values.
+    auto field = [&](int k, int b) -> Cx<R> {
+      const Cx<R> *e = tb.lowf + ((k - f) * 2 + b) * 256;
+      if (f == 0) return e[t];
+      const Cx<R> lo = e[t >> f], hi = e[(t >> f) | (255u & ~(255u >> f))];
+      return Cx<R>{R(0.5) * (lo.re + hi.re), R(0.5) * (lo.im + hi.im)};
+    };
+    Cx<R> a2n{0, 0};  // (the next site's field is loaded ahead)
     if (const uint32_t sm = W.smask & ((1u << kLowBits) - 1u)) a2n = field(__builtin_ctz(sm), (t >> __builtin_ctz(sm)) & 1);
 #pragma unroll 1
     for (uint32_t sm = W.smask & ((1u << kLowBits) - 1u); sm;) {
@@ -352,7 +363,7 @@ __global__ __launch_bounds__(kBlock, sizeof(R) == 8 ? 2 : 3) void hv_half_sweep(
     for (int s = 0; s < 3; s++) {
       const int k = kLowBits + s;
       if (!((W.smask >> k) & 1u)) continue;
-      const Cx<R> l0 = tb.lowf[(k * 2) * 256 + t], l1 = tb.lowf[(k * 2 + 1) * 256 + t];
+      const Cx<R> l0 = field(k, 0), l1 = field(k, 1);
 #pragma unroll
       for (int q = 0; q < kRows; q++) {
         const int b = (q >> s) & 1;
@@ -470,18 +481,40 @@ __global__ __launch_bounds__(kBlock, sizeof(R) == 8 ? 2 : 3) void hv_half_sweep(
       Acc<R, 1> a1;
       a1.re[0] = acc[q].re + wprev[q].re;
       a1.im[0] = acc[q].im + wprev[q].im;
-      if (W.last) hv_epilogue<R, 1, true>(P, base + q * kBlock + t, 0, a1, &z[q], red);
+      if (W.last) hv_epilogue<R, 1, true>(P, (base + q * kBlock + t) >> f, COLS ? (int)(t & (P.K - 1)) : 0, a1, &z[q], red);
       else st_stream(wt + q * kBlock + t, Cx<R>{a1.re[0], a1.im[0]});
     }
   }
-  if (W.last) hv_finish<1>(P, red);
+  if (!W.last || !P.lanczos) return;
+  if constexpr (!COLS) {
+    hv_finish<1>(P, red);
+    return;
+  }
+  // a thread's rows are of one column, its lowest f bits: sums over the other lane bits,
+  // then over the four waves in order
+  double *part = reinterpret_cast<double *>(smem);
+  __syncthreads();
+#pragma unroll
+  for (int a = 0; a < 3; a++) {
+    double s = red[a][0];
+    for (int m = 32; m >= P.K; m >>= 1) s += __shfl_xor(s, m);
+    if (lane < P.K) part[((threadIdx.x >> 6) * 3 + a) * P.K + lane] = s;
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < 3 * P.K) {
+    const int a = threadIdx.x / P.K, c = threadIdx.x % P.K;
+    double s = 0;
+    for (int wv = 0; wv < kBlock / 64; wv++) s += part[(wv * 3 + a) * P.K + c];
+    P.part[((size_t)c * gridDim.x + blockIdx.x) * 3 + a] = s;
+  }
 }
 
-template <typename R>
-int launch_r(const HamGeom &g, const DevTables<R> &tb, const WinPlan &plan, const HvParams &P, int cap,
+template <typename R, bool COLS>
+int launch_r(const HamGeom &g, const DevTables<R> &tb, const WinPlan &plan, int f, const HvParams &P, int cap,
              unsigned *last_gx, hipStream_t s) {
+  static std::atomic<size_t> granted{0};  // per instantiation: largest dynamic LDS size requested so far
   const HalfTables &H = plan.half;
-  if (!plan.d_plist || !plan.d_pcoef || !H.d_grp || plan.passes.empty() || P.K != 1) return FTLM_EINVAL;
+  if (!plan.d_plist || !plan.d_pcoef || !H.d_grp || plan.passes.empty()) return FTLM_EINVAL;
   // the blocks that are resident, but for a single pass of complex128 (2^22 rows: complex64
   // 213 us with 768 blocks, 226 with 2048; complex128 402 with 2048, 417 with 512; in
   // several passes, 2^24 rows: 2421 and 2275)
@@ -492,20 +525,25 @@ int launch_r(const HamGeom &g, const DevTables<R> &tb, const WinPlan &plan, cons
     if (W.nwin >= 8 && gx >= 8) gx &= ~7u;
     HvParams Pp = P;
     if (!W.last) Pp.lanczos = 0;
-    const size_t sm = HalfLds<R>(g.n, W.hg[4] - W.hg[0]).total;
-    static std::atomic<size_t> granted{0};  // per instantiation: largest dynamic LDS size requested so far
+    const size_t sm = HalfLds<R>(g.n + f, W.hg[4] - W.hg[0]).total;
     if (sm > granted.load()) {
-      (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&hv_half_sweep<R>),
+      (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&hv_half_sweep<R, COLS>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
       granted.store(sm);
     }
-    hipLaunchKernelGGL((hv_half_sweep<R>), dim3(gx), dim3(kBlock), sm, s, g, tb, W, H.d_grp,
+    hipLaunchKernelGGL((hv_half_sweep<R, COLS>), dim3(gx), dim3(kBlock), sm, s, g, tb, W, H.d_grp,
                        reinterpret_cast<const Cx<R> *>(H.d_gco), H.d_msk, reinterpret_cast<const Cx<R> *>(H.d_mco),
                        reinterpret_cast<const R *>(H.d_tdiag), plan.d_plist,
-                       reinterpret_cast<const Cx<R> *>(plan.d_pcoef), Pp);
+                       reinterpret_cast<const Cx<R> *>(plan.d_pcoef), f, Pp);
     *last_gx = gx;
   }
   return FTLM_OK;
+}
+
+template <typename R>
+int launch_f(const HamGeom &g, const DevTables<R> &tb, const WinPlan &plan, int f, const HvParams &P, int cap,
+             unsigned *gx, hipStream_t s) {
+  return f ? launch_r<R, true>(g, tb, plan, f, P, cap, gx, s) : launch_r<R, false>(g, tb, plan, 0, P, cap, gx, s);
 }
 
 int layout_of(int bit) { return bit >= 8 ? 0 : bit >= 5 ? 1 : bit >= 2 ? 2 : 3; }
@@ -516,7 +554,7 @@ int layout_base(int L) { return L == 0 ? 8 : L == 1 ? 5 : L == 2 ? 2 : 0; }
 // The in-tile pairs of every pass as groups (layout of the higher site j; the lower
 // site i when it is not a register bit of that layout), and the mixed pairs by outer
 // site; pcoef: four coefficients per list entry, by the row bits (i, j).
-void plan_half(const HostHam &hh, const std::vector<Cx<double>> &pcoef, WinPlan &plan) {
+void plan_half(const HostHam &hh, const std::vector<Cx<double>> &pcoef, int f, WinPlan &plan) {
   HalfTables &H = plan.half;
   H.grp.clear();
   H.gco.clear();
@@ -567,26 +605,65 @@ void plan_half(const HostHam &hh, const std::vector<Cx<double>> &pcoef, WinPlan 
     }
   }
   // diagonal over the tile's sites, each row from the one with its lowest set bit cleared
-  const int n = hh.n;
-  H.tdiag.assign(kTile, 0.0);
+  const int n = hh.n, nt = kTileBits - f;
+  H.tdiag.assign((size_t)1 << nt, 0.0);
   double d0 = 0;
-  for (int k = 0; k < kTileBits; k++) {
+  for (int k = 0; k < nt; k++) {
     d0 += hh.h[(size_t)k * 256].re;
     for (int j = 0; j < k; j++) d0 += 0.25 * hh.zz[(size_t)k * n + j];
   }
   H.tdiag[0] = d0;
-  for (int r = 1; r < kTile; r++) {
+  for (int r = 1; r < 1 << nt; r++) {
     const int k = __builtin_ctz((unsigned)r);
     double d = H.tdiag[r & (r - 1)] + (hh.h[(size_t)k * 256 + 17].re - hh.h[(size_t)k * 256].re);
-    for (int j = 0; j < kTileBits; j++)
+    for (int j = 0; j < nt; j++)
       if (j != k) d += hh.zz[(size_t)k * n + j] * ((r >> j) & 1 ? 0.5 : -0.5);
     H.tdiag[r] = d;
   }
 }
 
+// One pass over all rows for 2^f columns: row bits (site k on bit k + f), pairs in the
+// order of a window pass (both in the tile | one outer site, by that site | two outer).
+void plan_columns(const HostHam &hh, const std::vector<int> &pi, const std::vector<int> &pj, int f, WinPlan &plan) {
+  plan = WinPlan();
+  const int nb = hh.n + f;
+  if (hh.n < kTileBits || f < 1 || nb > 31) return;
+  std::vector<int> prs(pi.size());
+  for (size_t p = 0; p < prs.size(); p++) prs[p] = (int)p;
+  auto cls = [&](int p) { return (pi[p] + f >= kTileBits) + (pj[p] + f >= kTileBits); };
+  std::stable_sort(prs.begin(), prs.end(), [&](int a, int b) {
+    if (cls(a) != cls(b)) return cls(a) < cls(b);
+    return cls(a) > 0 && pj[a] < pj[b];
+  });
+  WinPass W;
+  std::memset(&W, 0, sizeof(W));
+  W.first = W.last = W.diag = 1;
+  W.np = (int)prs.size();
+  W.nwin = 1;
+  W.nin = 1u << (nb - kTileBits);
+  W.emask = (W.nin - 1u) << kTileBits;
+  for (int k = 0; k < hh.n; k++)
+    if (site_has_singles(hh, k)) W.smask |= 1u << (k + f);
+  W.xmask = W.smask >> kTileBits << kTileBits;
+  for (int p : prs) {
+    plan.plist.push_back(make_int4(p, pi[p] + f, pj[p] + f, 0));
+    if (cls(p) == 0) W.np_ll++;
+    if (cls(p) == 1) {
+      W.np_lh++;
+      W.xmask |= 1u << (pj[p] + f);
+    }
+  }
+  if (plan.plist.empty()) plan.plist.push_back(make_int4(0, 0, 0, 0));
+  plan.passes.push_back(W);
+}
+
 int launch_half_sweep(const DevHam &dh, int precision, const HvParams &P, int cap, unsigned *gx, hipStream_t s) {
-  return precision == FTLM_C64 ? launch_r<float>(dh.geom, dh.t32, dh.tw32, P, cap, gx, s)
-                               : launch_r<double>(dh.geom, dh.t64, dh.tw64, P, cap, gx, s);
+  const bool f32 = precision == FTLM_C64;
+  const int f = P.K == 1 ? 0 : P.K == 2 ? 1 : P.K == 4 ? 2 : P.K == 8 ? 3 : -1;
+  if (f < 0) return FTLM_EINVAL;
+  const WinPlan &plan = f ? dh.twc[f32][f - 1] : f32 ? dh.tw32 : dh.tw64;
+  return f32 ? launch_f<float>(dh.geom, dh.t32, plan, f, P, cap, gx, s)
+             : launch_f<double>(dh.geom, dh.t64, plan, f, P, cap, gx, s);
 }
 
 }  // namespace ftlm

@@ -2187,6 +2187,12 @@ static int launch_tile_win(const DevHam &dh, const DevTables<R> &tb, const WinPl
   return FTLM_OK;
 }
 
+// Does the half sweep have a plan for K > 1 columns (2, 4 or 8)?
+static bool half_columns(const DevHam &dh, int precision, int K) {
+  const int f = K == 2 ? 1 : K == 4 ? 2 : K == 8 ? 3 : 0;
+  return f && !dh.twc[precision == FTLM_C64][f - 1].passes.empty();
+}
+
 int launch_hv(const DevHam &dh, const HvLaunch &Lin, hipStream_t s) {
   HvLaunch L = Lin;
   if (L.K >= 1 && L.K <= 64 && (L.precision == 0 || L.precision == 1)) {
@@ -2195,24 +2201,43 @@ int launch_hv(const DevHam &dh, const HvLaunch &Lin, hipStream_t s) {
     if (!L.grid_cap) L.grid_cap = tn.grid_cap;
     if (!L.kc) L.kc = tn.kc;
   }
-  // built-in choice for one column of a vector beyond the caches: the
-  // single-pass tile kernel wherever its plan exists (no s+- s^z pair pieces);
-  // it beat the multi-pass and tile kernels on every such workload measured
-  if (!L.variant && L.K == 1 && dh.geom.dim >= (1u << 20) && (L.precision == FTLM_C64 ? dh.sp32 : dh.sp64).ok)
-    L.variant = 6;
-  // spin-1/2 systems with those pieces: the half sweep over L2 windows from 2^19 rows,
-  // below that the direct gather.  Measured with all pairs coupled (us, complex128 /
+  // built-in choice, one column.  Spins 1/2: the half sweep over L2 windows from 2^18
+  // rows, below that the direct gather; complex128 vectors of few pairs take the
+  // single-pass tile kernel instead, where its plan exists (no s+- s^z pair pieces): its
+  // time goes with the pairs, the half sweep's has a part that does not (2^22 rows: 152
+  // and 184 us with 2 pairs per site, 870 and 364 with 10).  Measured (us, complex128 /
   // complex64):
-  //   rows            2^18       2^19       2^20       2^22       2^24
-  //   direct gather   49 / 39    96 / 85    181 / 163  882 / 762  4619 / 3633
-  //   LDS tile        120 / 78   142 / 92   159 / 109  792 / 405  3759 / 1850
-  //   half sweep      47 / 38    55 / 46    81 / 60    402 / 211  2210 / 1177
+  //   rows                      2^18       2^19       2^20       2^22       2^24
+  //   all pairs  direct gather  49 / 39    96 / 85    181 / 163  882 / 762  4619 / 3633
+  //              LDS tile       120 / 78   142 / 92   159 / 109  792 / 405  3759 / 1850
+  //              half sweep     45 / 39    52 / 45    77 / 58    396 / 207  2280 / 1177
+  //   2 per site direct gather  22 / 17               76 / 60    317 / 255  1459 / 1188
+  //              single pass    29 / 44               38 / 48    152 / 106  638 / 423
+  //              half sweep     21 / 17               42 / 26    184 / 82   763 / 380
   // (a tile walks its pairs serially, so a vector of few tiles leaves the chip idle)
-  if (!L.variant && L.K == 1 && dh.geom.spin_half) {
-    const WinPlan &tw = L.precision == FTLM_C64 ? dh.tw32 : dh.tw64;
-    if (dh.geom.dim < (1u << 19)) L.variant = 1;
-    else if (!tw.passes.empty()) L.variant = 5;
+  if (!L.variant && L.K == 1) {
+    const bool f32 = L.precision == FTLM_C64, single = (f32 ? dh.sp32 : dh.sp64).ok;
+    const HamGeom &g = dh.geom;
+    if (g.spin_half && g.dim >= (1u << 18) && !(f32 ? dh.tw32 : dh.tw64).passes.empty() &&
+        (f32 || !single || g.npair > 3 * g.n || g.dim < (1u << 20)))
+      L.variant = 5;
+    // other vectors beyond the caches: the single-pass kernels beat the multi-pass ones on
+    // every such workload measured
+    else if (single && g.dim >= (1u << 20))
+      L.variant = 6;
+    else if (g.spin_half && g.dim < (1u << 18))
+      L.variant = 1;
   }
+  // 2, 4 and 8 columns of spins 1/2, all pairs coupled (us, direct gather / half sweep):
+  //   rows x columns   complex128                complex64
+  //   2^16 x 8         138 / 52                  49 / 39
+  //   2^17 x 4         91 / 54                   38 / 42
+  //   2^18 x 4         215 / 78                  67 / 57
+  //   2^19 x 4         375 / 174                 143 / 107
+  //   2^21 x 2         677 / 426                 396 / 220
+  if (!L.variant && half_columns(dh, L.precision, L.K) &&
+      (L.precision != FTLM_C64 || L.K == 8 || (uint64_t)dh.geom.dim * L.K >= 2 * kHalfColumnsRows))
+    L.variant = 5;
   g_variant = L.variant;
   int gx, gy, kc, lpr;
   const int rcg = hv_grid_blocks(dh, L, &gx, &gy, &kc, &lpr);
@@ -2251,9 +2276,10 @@ int launch_hv(const DevHam &dh, const HvLaunch &Lin, hipStream_t s) {
     fin_kc = 1;
   } else if (L.variant == 5) {
     const int cap = L.grid_cap > 0 ? std::min(L.grid_cap, 2048) : 2048;
-    // one column: the half sweep; more columns: the tile kernel, a column per grid row (the
-    // columns-per-lane field carries its row groups per tile)
-    if (L.K == 1) rc = launch_half_sweep(dh, L.precision, P, L.grid_cap, &fin_gx, s);
+    // 1, 2, 4 and 8 columns: the half sweep; else (and for 2 to 8 columns of few rows) the
+    // tile kernel, a column per grid row (the columns-per-lane field carries its row groups)
+    const bool half = L.K == 1 || half_columns(dh, L.precision, L.K);
+    if (half) rc = launch_half_sweep(dh, L.precision, P, L.grid_cap, &fin_gx, s);
     else rc = (L.precision == FTLM_C64) ? launch_tile_win<float>(dh, dh.t32, dh.tw32, P, cap, L.kc, &fin_gx, s)
                                    : launch_tile_win<double>(dh, dh.t64, dh.tw64, P, cap, L.kc, &fin_gx, s);
     fin_gy = (unsigned)L.K;

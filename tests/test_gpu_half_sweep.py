@@ -40,6 +40,33 @@ def test_more_outer_pairs_than_lanes():
     assert float((got - want).abs().max()) < 4e-5 * float(want.abs().max())
 
 
+@pytest.mark.parametrize("couple", ["dipolar", "chain", "far"])
+@pytest.mark.parametrize("n,K", [(16, 8), (17, 4), (18, 2), (18, 8)])
+def test_columns_match_oracle(n, K, couple):
+    """2, 4 and 8 columns as the lowest row bits, from the smallest size on."""
+    import paper_2607_25585_amd as F
+    sysm = _system(n, couple)
+    ham, ref = F.Hamiltonian(sysm), of.Ham(sysm)
+    rng = np.random.default_rng(n)
+    v = rng.standard_normal((ham.dim, K)) + 1j * rng.standard_normal((ham.dim, K))
+    want = np.stack([ref.apply(v[:, c]) for c in range(K)], axis=1)
+    for cap in (0, 5, 64):
+        print("case columns", couple, n, K, "grid", cap, flush=True)
+        for prec, dt, tol in ((F.FTLM_C128, torch.complex128, 1e-12), (F.FTLM_C64, torch.complex64, 2e-5)):
+            ham.set_tuning(prec, K, 5, cap)
+            got = ham.apply(torch.as_tensor(v, device="cuda").to(dt)).cpu().numpy()
+            assert np.max(np.abs(got - want)) < tol * np.max(np.abs(want))
+    T = np.array([1.0, 10.0])
+    ham.set_tuning(F.FTLM_C128, K, 0)
+    a = F.run(ham, K, 4, T, seed=3, columns=K, return_tridiagonals=True)
+    ham.set_tuning(F.FTLM_C128, K, 1)
+    b = F.run(ham, K, 4, T, seed=3, columns=K, return_tridiagonals=True)
+    scale = np.max(np.abs(b["alpha"])) + np.max(np.abs(b["beta"]))
+    for k in ("alpha", "beta"):
+        assert np.max(np.abs(a[k] - b[k])) < 1e-11 * scale
+    assert np.max(np.abs(a["M"] - b["M"])) < 1e-9 * np.max(np.abs(b["M"]))
+
+
 @pytest.mark.parametrize("tile_kb", [0, 128])
 @pytest.mark.parametrize("couple", ["dipolar", "exchange", "chain", "far"])
 @pytest.mark.parametrize("n", [12, 13, 16, 17])
