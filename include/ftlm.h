@@ -101,7 +101,7 @@ int ftlm_apply(const ftlm_hamiltonian *h, int32_t precision, int32_t n_cols, con
  * the caller's device buffers v, w ([dim][n_cols], as ftlm_apply) -- variants
  * 1 = direct gather (columns per lane 1, 2, 4, 8), 2 = windowed LDS passes,
  * 3 = LDS tile (spin 1/2, N >= 11), 4 = L2-window passes (one column), 5 = LDS
- * tile walked over L2 windows (spin 1/2, N >= 12; 1 column, and 2, 4 or 8 of at
+ * tile walked over L2 windows (spin 1/2, N >= 12; 1 column, and 2, 4, 8 or 16 of at
  * least 2^19 / n_cols rows, take 256 threads and ignore the columns-per-lane field;
  * with other columns it gives 256, 512 or 1024 threads per tile as 1, 2 or 4 row
  * groups), 6 = single pass

@@ -283,7 +283,7 @@ uint64_t launch_signature(const DevHam &dh) {
     f.vec(pl->lane_off);
   }
   for (const WinPlan *pl : {&dh.win64, &dh.win32, &dh.tw64, &dh.tw32, &dh.twc[0][0], &dh.twc[0][1], &dh.twc[0][2],
-                            &dh.twc[1][0], &dh.twc[1][1], &dh.twc[1][2]}) {
+                            &dh.twc[0][3], &dh.twc[1][0], &dh.twc[1][1], &dh.twc[1][2], &dh.twc[1][3]}) {
     f.vec(pl->passes);
     f.pod(pl->d_plist);
     f.pod(pl->d_pcoef);
@@ -393,7 +393,7 @@ int upload_tables(const HostHam &hh, DevHam &dh, std::string &err) {
   const std::vector<Cx<float>> tc32 = plist_coefs<float>(hh, perm, dh.tw32.plist);
   const size_t off_c64 = b.add(tc64.data(), tc64.size() * sizeof(Cx<double>));
   const size_t off_c32 = b.add(tc32.data(), tc32.size() * sizeof(Cx<float>));
-  // the half sweep's tables: tile plans, and plans of 2, 4 and 8 columns from the size on
+  // the half sweep's tables: tile plans, and plans of 2, 4, 8 and 16 columns from the size on
   // where they are the built-in choice
   struct HalfOff {
     WinPlan *pl;
@@ -402,7 +402,7 @@ int upload_tables(const HostHam &hh, DevHam &dh, std::string &err) {
   };
   std::vector<HalfOff> halves;
   for (int q = 0; q < 2; q++)
-    for (int f = 0; f < 4; f++) {
+    for (int f = 0; f < 5; f++) {
       WinPlan &tw = f ? dh.twc[q][f - 1] : q ? dh.tw32 : dh.tw64;
       if (f) {
         tw = WinPlan();

@@ -253,7 +253,7 @@ struct WinPlan {
 };
 // Fills plan.half and the passes' records of it; pcoef: the coefficients in plist order.
 void plan_half(const HostHam &hh, const std::vector<Cx<double>> &pcoef, int f, WinPlan &plan);
-// The half sweep's plan for 2^f columns (f = 1, 2, 3).
+// The half sweep's plan for 2^f columns (f = 1 to 4).
 void plan_columns(const HostHam &hh, const std::vector<int> &pi, const std::vector<int> &pj, int f, WinPlan &plan);
 
 // Single-pass H*v for one column ("stream" kernel, variant 6).  Rows are walked
@@ -335,7 +335,7 @@ struct DevHam {
   PassPlan plan64, plan32;  // windowed-pass plans for complex128 / complex64
   WinPlan win64, win32;     // L2-window plans for complex128 / complex64
   WinPlan tw64, tw32;       // L2-window plans of the LDS tile kernel (spin 1/2, N >= 12)
-  WinPlan twc[2][3];        // half sweep of 2, 4 and 8 columns [precision][log2 columns - 1]
+  WinPlan twc[2][4];        // half sweep of 2, 4, 8 and 16 columns [precision][log2 columns - 1]
   StreamPlan sp64, sp32;    // single-pass tile plans (complex128 / complex64)
   SweepPlan sw64, sw32;     // tile sweep plans
   // key of the plans above (recomputed only when it changes)
@@ -428,7 +428,7 @@ int launch_stream(const DevHam &dh, int precision, const HvParams &P, int cap, i
 // resident at once; kc: bits 4..7 as above (every group's partner tile is staged).
 int launch_sweep(const DevHam &dh, int precision, const HvParams &P, int cap, int kc, unsigned *gx,
                  hipStream_t s);
-// Variant 5, 1, 2, 4 or 8 columns (half_sweep.hip).
+// Variant 5, 1, 2, 4, 8 or 16 columns (half_sweep.hip).
 int launch_half_sweep(const DevHam &dh, int precision, const HvParams &P, int cap, unsigned *gx, hipStream_t s);
 // (Re)computes the per-window records of both pass plans (allocates rec_block on
 // first use).  Synchronous.

@@ -1,4 +1,4 @@
-// Half sweep: H*v for 1, 2, 4 or 8 columns of a spin-1/2 system (variant 5), over L2 windows
+// Half sweep: H*v for 1, 2, 4, 8 or 16 columns of a spin-1/2 system (variant 5), over L2 windows
 // of 2048-row tiles (Sec. 2.1, Eq. mce-hamop, with the flips of a site as XORs of row bits).
 // Several columns are the lowest bits of the row number, which no term moves.
 //
@@ -659,7 +659,7 @@ void plan_columns(const HostHam &hh, const std::vector<int> &pi, const std::vect
 
 int launch_half_sweep(const DevHam &dh, int precision, const HvParams &P, int cap, unsigned *gx, hipStream_t s) {
   const bool f32 = precision == FTLM_C64;
-  const int f = P.K == 1 ? 0 : P.K == 2 ? 1 : P.K == 4 ? 2 : P.K == 8 ? 3 : -1;
+  const int f = P.K == 1 ? 0 : P.K == 2 ? 1 : P.K == 4 ? 2 : P.K == 8 ? 3 : P.K == 16 ? 4 : -1;
   if (f < 0) return FTLM_EINVAL;
   const WinPlan &plan = f ? dh.twc[f32][f - 1] : f32 ? dh.tw32 : dh.tw64;
   return f32 ? launch_f<float>(dh.geom, dh.t32, plan, f, P, cap, gx, s)

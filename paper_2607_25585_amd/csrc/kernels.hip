@@ -2187,9 +2187,9 @@ static int launch_tile_win(const DevHam &dh, const DevTables<R> &tb, const WinPl
   return FTLM_OK;
 }
 
-// Does the half sweep have a plan for K > 1 columns (2, 4 or 8)?
+// Does the half sweep have a plan for K > 1 columns (2, 4, 8 or 16)?
 static bool half_columns(const DevHam &dh, int precision, int K) {
-  const int f = K == 2 ? 1 : K == 4 ? 2 : K == 8 ? 3 : 0;
+  const int f = K == 2 ? 1 : K == 4 ? 2 : K == 8 ? 3 : K == 16 ? 4 : 0;
   return f && !dh.twc[precision == FTLM_C64][f - 1].passes.empty();
 }
 
@@ -2228,7 +2228,7 @@ int launch_hv(const DevHam &dh, const HvLaunch &Lin, hipStream_t s) {
     else if (g.spin_half && g.dim < (1u << 18))
       L.variant = 1;
   }
-  // 2, 4 and 8 columns of spins 1/2, all pairs coupled (us, direct gather / half sweep):
+  // 2, 4, 8 and 16 columns of spins 1/2, all pairs coupled (us, direct gather / half sweep):
   //   rows x columns   complex128                complex64
   //   2^16 x 8         138 / 52                  49 / 39
   //   2^17 x 4         91 / 54                   38 / 42
@@ -2236,7 +2236,7 @@ int launch_hv(const DevHam &dh, const HvLaunch &Lin, hipStream_t s) {
   //   2^19 x 4         375 / 174                 143 / 107
   //   2^21 x 2         677 / 426                 396 / 220
   if (!L.variant && half_columns(dh, L.precision, L.K) &&
-      (L.precision != FTLM_C64 || L.K == 8 || (uint64_t)dh.geom.dim * L.K >= 2 * kHalfColumnsRows))
+      (L.precision != FTLM_C64 || L.K >= 8 || (uint64_t)dh.geom.dim * L.K >= 2 * kHalfColumnsRows))
     L.variant = 5;
   g_variant = L.variant;
   int gx, gy, kc, lpr;
@@ -2276,7 +2276,7 @@ int launch_hv(const DevHam &dh, const HvLaunch &Lin, hipStream_t s) {
     fin_kc = 1;
   } else if (L.variant == 5) {
     const int cap = L.grid_cap > 0 ? std::min(L.grid_cap, 2048) : 2048;
-    // 1, 2, 4 and 8 columns: the half sweep; else (and for 2 to 8 columns of few rows) the
+    // 1, 2, 4, 8 and 16 columns: the half sweep; else (and for several columns of few rows) the
     // tile kernel, a column per grid row (the columns-per-lane field carries its row groups)
     const bool half = L.K == 1 || half_columns(dh, L.precision, L.K);
     if (half) rc = launch_half_sweep(dh, L.precision, P, L.grid_cap, &fin_gx, s);

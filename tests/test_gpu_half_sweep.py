@@ -41,9 +41,9 @@ def test_more_outer_pairs_than_lanes():
 
 
 @pytest.mark.parametrize("couple", ["dipolar", "chain", "far"])
-@pytest.mark.parametrize("n,K", [(16, 8), (17, 4), (18, 2), (18, 8)])
+@pytest.mark.parametrize("n,K", [(16, 8), (17, 4), (18, 2), (18, 8), (15, 16), (16, 16)])
 def test_columns_match_oracle(n, K, couple):
-    """2, 4 and 8 columns as the lowest row bits, from the smallest size on."""
+    """2, 4, 8 and 16 columns as the lowest row bits, from the smallest size on."""
     import paper_2607_25585_amd as F
     sysm = _system(n, couple)
     ham, ref = F.Hamiltonian(sysm), of.Ham(sysm)
