@@ -306,7 +306,7 @@ uint64_t launch_signature(const DevHam &dh) {
   }
   for (const SweepPlan *sw : {&dh.sw64, &dh.sw32}) {
     f.pod(sw->ok);
-    f.pod(sw->pass);
+    if (sw->ok) f.pod(sw->pass);
     f.pod(sw->cplx);
     f.pod(sw->tab.d_pij);
     f.pod(sw->tab.d_pc);
@@ -381,6 +381,7 @@ int upload_tables(const HostHam &hh, DevHam &dh, std::string &err) {
   dh.plan32.rec_block = rec32;
   dh.plan32.rec_bytes = rb32;
   Blob b;
+  b.bytes.reserve(64 * 1024);
   TableOffsets<double> o64 = pack_tables<double>(hh, perm, b);
   TableOffsets<float> o32 = pack_tables<float>(hh, perm, b);
   const size_t off_p64 = b.add(dh.plan64.pairs.data(), dh.plan64.pairs.size() * sizeof(int4));

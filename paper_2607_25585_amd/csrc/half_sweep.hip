@@ -604,21 +604,23 @@ void plan_half(const HostHam &hh, const std::vector<Cx<double>> &pcoef, int f, W
       H.mco.insert(H.mco.end(), c, c + 4 * kTileBits);
     }
   }
-  // diagonal over the tile's sites, each row from the one with its lowest set bit cleared
+  // diagonal over the tile's sites, doubled site by site: raising site k adds its own
+  // difference and the z-field g of the others, g itself doubled over the sites below k
   const int n = hh.n, nt = kTileBits - f;
   H.tdiag.assign((size_t)1 << nt, 0.0);
-  double d0 = 0;
+  std::vector<double> g((size_t)1 << nt);
   for (int k = 0; k < nt; k++) {
-    d0 += hh.h[(size_t)k * 256].re;
-    for (int j = 0; j < k; j++) d0 += 0.25 * hh.zz[(size_t)k * n + j];
+    H.tdiag[0] += hh.h[(size_t)k * 256].re;
+    for (int j = 0; j < k; j++) H.tdiag[0] += 0.25 * hh.zz[(size_t)k * n + j];
   }
-  H.tdiag[0] = d0;
-  for (int r = 1; r < 1 << nt; r++) {
-    const int k = __builtin_ctz((unsigned)r);
-    double d = H.tdiag[r & (r - 1)] + (hh.h[(size_t)k * 256 + 17].re - hh.h[(size_t)k * 256].re);
+  for (int k = 0; k < nt; k++) {
+    const double *z = &hh.zz[(size_t)k * n];
+    g[0] = hh.h[(size_t)k * 256 + 17].re - hh.h[(size_t)k * 256].re;
     for (int j = 0; j < nt; j++)
-      if (j != k) d += hh.zz[(size_t)k * n + j] * ((r >> j) & 1 ? 0.5 : -0.5);
-    H.tdiag[r] = d;
+      if (j != k) g[0] -= 0.5 * z[j];
+    for (int j = 0; j < k; j++)
+      for (int r = 0; r < 1 << j; r++) g[r + (1 << j)] = g[r] + z[j];
+    for (int r = 0; r < 1 << k; r++) H.tdiag[r + (1 << k)] = H.tdiag[r] + g[r];
   }
 }
 

@@ -2235,6 +2235,8 @@ int launch_hv(const DevHam &dh, const HvLaunch &Lin, hipStream_t s) {
   //   2^18 x 4         215 / 78                  67 / 57
   //   2^19 x 4         375 / 174                 143 / 107
   //   2^21 x 2         677 / 426                 396 / 220
+  //   2^15 x 16        124 / 48                  69 / 37
+  //   2^19 x 16        2796 / 959                1641 / 465
   if (!L.variant && half_columns(dh, L.precision, L.K) &&
       (L.precision != FTLM_C64 || L.K >= 8 || (uint64_t)dh.geom.dim * L.K >= 2 * kHalfColumnsRows))
     L.variant = 5;
