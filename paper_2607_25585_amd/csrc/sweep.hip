@@ -61,6 +61,11 @@ constexpr int sweep_waves(size_t real_bytes, int rpt) {
 // Threads of a block at most: with RPT 5 and 6 (3 waves per SIMD) one block is what a CU holds.
 constexpr int sweep_threads(int rpt) { return rpt >= 5 ? 768 : 1024; }
 
+// Threads of a plan's block: the values below the top tile site in whole waves, and two
+// waves at the least: per tile, the first lists the outer terms while the second makes
+// the outer sites' fields.
+inline int sweep_block(const SweepPass &G) { return std::max(128, (int)((G.Q + 63) / 64 * 64)); }
+
 // LDS layout (offsets 16-byte aligned).
 template <typename R>
 struct SweepLds {
@@ -489,7 +494,7 @@ void launch_t(const SweepPass &G, const SweepTables &S, const DevTables<R> &tb, 
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
     granted.store(sm);
   }
-  hipLaunchKernelGGL((hv_sweep<R, RPT, CPLX>), dim3(gx), dim3((G.Q + 63) / 64 * 64), sm, s, G, tb,
+  hipLaunchKernelGGL((hv_sweep<R, RPT, CPLX>), dim3(gx), dim3(sweep_block(G)), sm, s, G, tb,
                      S.d_pij, reinterpret_cast<const Cx<R> *>(S.d_pc), reinterpret_cast<const R *>(S.d_tdiag), chunk, P);
 }
 
@@ -513,7 +518,7 @@ int launch_r(const SweepPlan &sp, const DevTables<R> &tb, const HvParams &P, int
   const SweepPass &G = sp.pass;
   if (cap <= 0) {
     // the blocks resident at once on 256 CUs, by registers and by LDS
-    const int wv = (int)(G.Q + 63) / 64;
+    const int wv = sweep_block(G) / 64;
     const int regs = 4 * sweep_waves(sizeof(R), G.rtop) / wv;
     const int lds = (int)(160 * 1024 / (SweepLds<R>(G).total + 1024));
     cap = 256 * std::max(1, std::min(regs, lds));
