@@ -1101,6 +1101,131 @@ __global__ __launch_bounds__(kBlock) void hv_gen(HamGeom g, const uint4 *__restr
   }
 }
 
+// The same products with a lane per row, KC columns per lane, and the column groups on
+// blockIdx.y.  A move that leaves a digit's range is a branch not taken, and the pair
+// list comes by scalar loads, so that a row pays for its valid moves alone; what bounds
+// it is one partner after the other, which the rows of a large vector hide.  hv_gen
+// works through every move of every lane: on sites of two values, of whose pair moves one
+// in four is valid, that costs more than it hides (17 sites, 1.97e5 rows, all pairs with
+// s+- s^z pieces, complex128: one column 168 us here, 234 there; 4 columns 247 and 509).
+template <typename R, int KC>
+__global__ __launch_bounds__(kBlock) void hv_rows(HamGeom g, DevTables<R> tb, const Cx<R> *__restrict__ pcg,
+                                                 const Cx<R> *__restrict__ czp, const Cx<R> *__restrict__ czm,
+                                                 const int2 *__restrict__ pij, const R *__restrict__ pzz,
+                                                 HvParams P) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int n = g.n;
+  Cx<R> *s_hoff = reinterpret_cast<Cx<R> *>(smem);  // [n][4][16]
+  R *s_hd = reinterpret_cast<R *>(s_hoff + n * 64);  // [n][16]
+  R *s_gp = s_hd + n * 16;
+  R *s_gm = s_gp + n * 16;
+  R *s_m = s_gm + n * 16;
+  const int t = threadIdx.x;
+  const int c0 = blockIdx.y * KC;
+  for (int i = t; i < n * 64; i += kBlock) s_hoff[i] = tb.hoff[i];
+  for (int i = t; i < n * 16; i += kBlock) {
+    s_hd[i] = tb.hdiag[i];
+    s_gp[i] = tb.gp[i];
+    s_gm[i] = tb.gm[i];
+    s_m[i] = tb.mval[i];
+  }
+  __syncthreads();
+  const Cx<R> *__restrict__ v = reinterpret_cast<const Cx<R> *>(P.v) + c0;
+  double red[3][KC];
+#pragma unroll
+  for (int a = 0; a < 3; a++)
+#pragma unroll
+    for (int q = 0; q < KC; q++) red[a][q] = 0.0;
+
+  for (uint32_t tile = blockIdx.x; tile < P.ntile; tile += gridDim.x) {
+    const uint32_t row = tile * kBlock + t;
+    if (row >= g.dim) continue;
+    // digits, 4 bits each: sites 0..15 in dlo, 16..31 in dhi
+    uint64_t dlo = 0, dhi = 0;
+    {
+      uint32_t rem = row;
+      for (int k = 0; k < n; k++) {
+        const uint32_t r = (uint32_t)g.radix[k];
+        const uint32_t q = rem / r;
+        const uint64_t dk = rem - q * r;
+        rem = q;
+        if (k < 16) dlo |= dk << (4 * k);
+        else dhi |= dk << (4 * (k - 16));
+      }
+    }
+    auto digit = [&](int k) -> int {
+      return (int)(((k < 16) ? (dlo >> (4 * k)) : (dhi >> (4 * (k - 16)))) & 15u);
+    };
+    R diag = 0;
+    for (int k = 0; k < n; k++) diag += s_hd[k * 16 + digit(k)];
+    for (int p = 0; p < g.npair; p++) {
+      const int2 ij = pij[p];
+      diag = fma(pzz[p], s_m[ij.x * 16 + digit(ij.x)] * s_m[ij.y * 16 + digit(ij.y)], diag);
+    }
+    Acc<R, KC> acc;
+    acc_zero(acc);
+    const Cx<R> *own = v + (size_t)row * P.K;
+    mac_real(acc, diag, own);
+    for (int k = 0; k < n; k++) {
+      const int dk = digit(k), rk = g.radix[k];
+      const uint32_t st = g.stride[k];
+      R fpr = 0, fpi = 0, fmr = 0, fmi = 0;
+      if (g.has_z) {
+        for (int l = 0; l < n; l++) {
+          if (l == k) continue;
+          const R ml = s_m[l * 16 + digit(l)];
+          const Cx<R> cp = czp[k * n + l], cm = czm[k * n + l];
+          fpr = fma(cp.re, ml, fpr);
+          fpi = fma(cp.im, ml, fpi);
+          fmr = fma(cm.re, ml, fmr);
+          fmi = fma(cm.im, ml, fmi);
+        }
+      }
+#pragma unroll
+      for (int di = 0; di < 4; di++) {
+        const int D = (di < 2) ? di - 2 : di - 1;  // -2,-1,+1,+2
+        const int nd = dk + D;
+        if (nd < 0 || nd >= rk) continue;
+        Cx<R> c = s_hoff[(k * 4 + di) * 16 + dk];
+        if (D == -1) {
+          const R gg = s_gp[k * 16 + dk];
+          c.re = fma(gg, fpr, c.re);
+          c.im = fma(gg, fpi, c.im);
+        } else if (D == 1) {
+          const R gg = s_gm[k * 16 + dk];
+          c.re = fma(gg, fmr, c.re);
+          c.im = fma(gg, fmi, c.im);
+        }
+        const uint32_t partner = row + (uint32_t)(D * (int)st);
+        mac(acc, c, v + (size_t)partner * P.K);
+      }
+    }
+    for (int p = 0; p < g.npair; p++) {
+      const int2 ij = pij[p];
+      const int di = digit(ij.x), dj = digit(ij.y);
+      const int ri = g.radix[ij.x], rj = g.radix[ij.y];
+      const uint32_t si = g.stride[ij.x], sj = g.stride[ij.y];
+      const R gpi = s_gp[ij.x * 16 + di], gmi = s_gm[ij.x * 16 + di];
+      const R gpj = s_gp[ij.y * 16 + dj], gmj = s_gm[ij.y * 16 + dj];
+      const Cx<R> *pc = pcg + 4 * p;
+#pragma unroll
+      for (int q = 0; q < 4; q++) {
+        const Cx<R> cq = pc[q];
+        if (cq.re == R(0) && cq.im == R(0)) continue;
+        const bool im_ = (q >> 1) != 0, jm = (q & 1) != 0;  // '-' ladder on site i / j
+        const bool vi = im_ ? (di <= ri - 2) : (di >= 1);
+        const bool vj = jm ? (dj <= rj - 2) : (dj >= 1);
+        if (!(vi && vj)) continue;
+        const R f = (im_ ? gmi : gpi) * (jm ? gmj : gpj);
+        const uint32_t partner = row + (im_ ? si : (uint32_t)(-(int)si)) + (jm ? sj : (uint32_t)(-(int)sj));
+        mac(acc, Cx<R>{cq.re * f, cq.im * f}, v + (size_t)partner * P.K);
+      }
+    }
+    hv_epilogue<R, KC>(P, row, c0, acc, own, red);
+  }
+  hv_finish<KC>(P, red);
+}
+
 // ------------------------------------------------------------------ L2-window passes
 // Adds the earlier passes' partial sum, then stores the raw partial (not the
 // last pass) or runs the epilogue (last pass).  KC columns from c0.
@@ -2005,40 +2130,59 @@ static int pick_kc(int K, int want) {
   return 1;
 }
 
-// Lanes per row and column group of the general-radix direct gather (1 for the
-// other kernels): a row's terms are shared where rows and groups leave the chip
-// idle.  Measured (us, K columns in groups of kc):
+// The direct gather's launch: columns per lane and lanes per row and column group (0: the
+// lane-per-row kernel of the general radices; 1 for spins 1/2, whose kernel has no other).
+struct Direct {
+  int kc, lpr;
+};
+
+// General radices.  hv_gen takes 32 bytes of columns per lane (the coefficient work is
+// shared by the group, the loads stay contiguous; 10 s=1 sites, 20 columns, complex64:
+// 89, 48, 41 us at 1, 2, 4; complex128: 103, 67, 67) and shares a row's terms between
+// lanes where rows and groups leave the chip idle.  Measured (us, K columns in groups of kc):
 //   rows x groups       1 lane   2      4      8
 //   729                 19.3     12.0   8.9    8.2   (6 s=1 sites, all pairs; K = 1)
 //   32,805              14.5     9.8    8.7    11.4  (8 s=1 sites, K = 20, complex64)
 //   65,610              15.1     12.6   16.0   17.3  (8 s=1 sites, K = 20, complex128)
 //   295,245             41.4     38.5   52.7   65.3  (10 s=1 sites, K = 20, complex64)
 //   655,360             60.6     64.2   89.6   120.8 (8 s=3/2 sites, K = 20, complex128)
-static int gen_lanes(const HamGeom &g, int K, int kc) {
-  if (g.spin_half) return 1;
+// (columns one by one, as 3 are, leave off sharing sooner: 65,536 rows x 3, complex128,
+// 8 s=3/2 ring sites: 18.4 us with 1 lane, 20.7 with 2.)
+// From 98,304 rows the lane-per-row kernel is at least as fast for the columns that one of
+// its lanes takes (1, 2, 4 or 8: a wave's loads are contiguous; 262,144 rows, 9 s=3/2 ring
+// sites, complex128: one column 20.6 us against 28.0), and from as many rows x groups
+// for any columns where the mean number of values per site is below 2.6, so that most pair
+// moves are not valid (98,304 rows, 16 sites, 20 columns, all pairs: 745 us against 1102).
+// Below, and for other columns, hv_gen is: 59,049 rows of 10 s=1 sites, all pairs, 59 us
+// against 31; 177,147 rows of 11, 20 columns, 1378 and 753.
+static Direct direct_launch(const HamGeom &g, int K, int want, int precision) {
+  if (g.spin_half) return Direct{pick_kc(K, want > 0 ? want : 8), 1};
+  constexpr uint64_t kRowsFrom = 98304;
+  const int kr = pick_kc(K, want > 0 ? want : 8);
+  const int kc = pick_kc(K, want > 0 ? want : precision == FTLM_C64 ? 4 : 2);
   const int ncg = K / kc;
   const uint64_t items = (uint64_t)g.dim * ncg;
-  int lpr = items <= 16384 ? 8 : items <= 49152 ? 4 : items <= 393216 ? 2 : 1;
+  if (kr == K && g.dim >= kRowsFrom) return Direct{kr, 0};
+  if (items >= kRowsFrom && std::log2((double)g.dim) < std::log2(2.6) * g.n) return Direct{kr, 0};
+  const uint64_t two = kc == 1 && K > 1 ? 98304 : 393216;
+  int lpr = items <= 16384 ? 8 : items <= 49152 ? 4 : items <= two ? 2 : 1;
   while (lpr * ncg > kBlock) lpr /= 2;
-  return lpr;
+  return Direct{kc, lpr};
 }
 
 // 256-lane tiles of the direct kernels.
-static uint32_t direct_tiles(const HamGeom &g, int K, int kc, int lpr) {
+static uint32_t direct_tiles(const HamGeom &g, int K, const Direct &d) {
   if (g.spin_half) return g.dim >> kLowBits;
-  const uint32_t rows = (uint32_t)(kBlock / (lpr * (K / kc)));
+  const uint32_t rows = d.lpr ? (uint32_t)(kBlock / (d.lpr * (K / d.kc))) : (uint32_t)kBlock;
   return (uint32_t)(((uint64_t)g.dim + rows - 1) / rows);
 }
 
 int hv_grid_blocks(const DevHam &dh, const HvLaunch &L, int *gx, int *gy, int *kc, int *lpr) {
   const HamGeom &g = dh.geom;
-  // columns per lane, general radix: 32 bytes (the coefficient work is shared by
-  // the group, the loads stay contiguous; 10 s=1 sites, 20 columns, complex64:
-  // 89, 48, 41 us at 1, 2, 4; complex128: 103, 67, 67)
-  const int want = L.kc > 0 ? L.kc : g.spin_half ? 8 : L.precision == FTLM_C64 ? 4 : 2;
-  int k = pick_kc(L.K, want);
-  *lpr = gen_lanes(g, L.K, k);
-  uint32_t ntile = direct_tiles(g, L.K, k, *lpr);
+  const Direct d = direct_launch(g, L.K, L.kc, L.precision);
+  int k = d.kc;
+  *lpr = d.lpr;
+  uint32_t ntile = direct_tiles(g, L.K, d);
   if (use_tile(g, L.K)) {
     ntile = g.dim >> kTileBits;
     k = 1;
@@ -2071,6 +2215,10 @@ static void launch_hv_t(const DevHam &dh, const DevTables<R> &tb, const HvParams
   if (g.spin_half && g.n >= kLowBits) {
     const UniformTabs<R> U = uniform_tabs(tb, false);
     hipLaunchKernelGGL((hv_half<R, KC>), grid, dim3(kBlock), hv_smem<R>(g), s, g, tb, U.pij, U.pzz, P);
+  } else if (lpr == 0) {
+    const UniformTabs<R> U = uniform_tabs(tb, false);
+    const size_t sm = (sizeof(Cx<R>) + sizeof(R)) * 64 * (size_t)g.n;
+    hipLaunchKernelGGL((hv_rows<R, KC>), grid, dim3(kBlock), sm, s, g, tb, U.pc, U.czp, U.czm, U.pij, U.pzz, P);
   } else if (lpr == 8) {
     launch_gen<R, KC, 8>(g, tb, P, grid, s);
   } else if (lpr == 4) {
@@ -2246,7 +2394,7 @@ int launch_hv(const DevHam &dh, const HvLaunch &Lin, hipStream_t s) {
   if (rcg) return rcg;
   HvParams P{};
   P.K = L.K;
-  P.ntile = direct_tiles(dh.geom, L.K, kc, lpr);
+  P.ntile = direct_tiles(dh.geom, L.K, Direct{kc, lpr});
   P.v = L.v;
   P.w = L.w;
   P.scale = L.scale;
@@ -2301,8 +2449,8 @@ int launch_hv(const DevHam &dh, const HvLaunch &Lin, hipStream_t s) {
     fin_gy = (unsigned)L.K;
     fin_kc = 1;
   } else {
-    // (the general-radix kernel's blocks hold every column group)
-    dim3 grid(gx, dh.geom.spin_half ? gy : 1);
+    // (the blocks of hv_gen hold every column group)
+    dim3 grid(gx, dh.geom.spin_half || lpr == 0 ? gy : 1);
     if (L.precision == FTLM_C64) launch_hv_r<float>(dh, dh.t32, P, grid, kc, lpr, s);
     else launch_hv_r<double>(dh, dh.t64, P, grid, kc, lpr, s);
     if (use_tile(dh.geom, L.K)) fin_kc = 1;
