@@ -2341,6 +2341,46 @@ static bool half_columns(const DevHam &dh, int precision, int K) {
   return f && !dh.twc[precision == FTLM_C64][f - 1].passes.empty();
 }
 
+// Is the half sweep the faster launch for 2, 4, 8 or 16 columns?  All pairs coupled
+// (us, direct gather / half sweep):
+//   rows x columns   complex128                complex64
+//   2^16 x 8         138 / 52                  49 / 39
+//   2^17 x 4         91 / 54                   38 / 42
+//   2^18 x 4         215 / 78                  67 / 57
+//   2^19 x 4         375 / 174                 143 / 107
+//   2^21 x 2         677 / 426                 396 / 220
+//   2^15 x 16        124 / 48                  69 / 37
+//   2^19 x 16        2796 / 959                1641 / 465
+// Few pairs: the gather's time goes with the pairs, the half sweep's has a part that does
+// not, most of it single flips (a chain without them is faster in the half sweep at every
+// size: 2^18 x 2 25 / 20, 2^20 x 4 209 / 114).  With single flips, pairs per site:
+//   complex128        0          1          2          3
+//   2^18 x 2          16 / 28    25 / 36    31 / 40    38 / 43    (4: 44 / 48, 5: 52 / 50)
+//   2^21 x 2          115 / 142  177 / 207  246 / 262  293 / 308  (4: 341 / 345)
+//   2^17 x 4          19 / 27    29 / 35    40 / 40    48 / 42
+//   2^20 x 4          140 / 139  208 / 203  285 / 262  354 / 300
+//   2^16 x 8          23 / 26    39 / 34    54 / 39    70 / 42
+//   complex64
+//   2^19 x 2          17 / 24    29 / 32    38 / 37    47 / 42
+//   2^21 x 2          75 / 75    122 / 101  157 / 127  180 / 147
+//   2^18 x 4          15 / 24    24 / 31    30 / 36    37 / 41    (4: 44 / 45, 5: 50 / 48)
+//   2^20 x 4          51 / 73    82 / 99    112 / 123  134 / 143  (4: 157 / 161)
+//   2^16 x 8          9 / 17     14 / 21    22 / 28    27 / 30    (4: 32 / 33)
+//   2^18 x 8          36 / 42    62 / 56    80 / 67    98 / 77
+//   2^15 x 16         13 / 16    20 / 20    30 / 27    38 / 29
+static bool half_columns_pay(const HamGeom &g, int precision, int K) {
+  const uint64_t elems = (uint64_t)g.dim * K;
+  const bool f32 = precision == FTLM_C64, small = elems < 2 * kHalfColumnsRows;
+  if (f32 && K < 8 && small) return false;
+  if (!g.single_mask) return true;
+  int least;  // pairs per site
+  if (K == 2) least = f32 ? (elems < 8 * kHalfColumnsRows ? 2 : 0) : small ? 5 : 4;
+  else if (K == 4) least = f32 ? 4 : small ? 2 : 0;
+  else if (K == 8) least = f32 ? (small ? 4 : elems < 8 * kHalfColumnsRows ? 1 : 0) : small;
+  else least = small;
+  return 2 * g.npair > (2 * least - 1) * g.n;  // (open ends leave a few pairs out)
+}
+
 int launch_hv(const DevHam &dh, const HvLaunch &Lin, hipStream_t s) {
   HvLaunch L = Lin;
   if (L.K >= 1 && L.K <= 64 && (L.precision == 0 || L.precision == 1)) {
@@ -2376,18 +2416,7 @@ int launch_hv(const DevHam &dh, const HvLaunch &Lin, hipStream_t s) {
     else if (g.spin_half && g.dim < (1u << 18))
       L.variant = 1;
   }
-  // 2, 4, 8 and 16 columns of spins 1/2, all pairs coupled (us, direct gather / half sweep):
-  //   rows x columns   complex128                complex64
-  //   2^16 x 8         138 / 52                  49 / 39
-  //   2^17 x 4         91 / 54                   38 / 42
-  //   2^18 x 4         215 / 78                  67 / 57
-  //   2^19 x 4         375 / 174                 143 / 107
-  //   2^21 x 2         677 / 426                 396 / 220
-  //   2^15 x 16        124 / 48                  69 / 37
-  //   2^19 x 16        2796 / 959                1641 / 465
-  if (!L.variant && half_columns(dh, L.precision, L.K) &&
-      (L.precision != FTLM_C64 || L.K >= 8 || (uint64_t)dh.geom.dim * L.K >= 2 * kHalfColumnsRows))
-    L.variant = 5;
+  if (!L.variant && half_columns(dh, L.precision, L.K) && half_columns_pay(dh.geom, L.precision, L.K)) L.variant = 5;
   g_variant = L.variant;
   int gx, gy, kc, lpr;
   const int rcg = hv_grid_blocks(dh, L, &gx, &gy, &kc, &lpr);
