@@ -3,7 +3,8 @@
 // for symmetric matrices", Numer. Math. 11 (1968) 293-306 (tql2).
 //
 //  * tridiag_kernel : two rows of the eigenvector matrix (what the thermal sums
-//    of Eqs. (E-2-C) and (E-2-D) need), one wave per column;
+//    of Eqs. (E-2-C) and (E-2-D) need), one wave per column; tridiag_lanes_kernel :
+//    the same with a lane per column, for thousands of short columns;
 //  * tridiag_full_kernel : the whole eigenvector matrix (the double sum of
 //    Eq. (E-2-H)), one block per column.
 //
@@ -123,66 +124,119 @@ __device__ __forceinline__ int ql_sweep(double *d, double *e, size_t S, int l, i
 #undef AT
 }
 
-// One wave per column; Z = product of the plane rotations, of which only the rows
-// e_1^T Z (-> Q_1n) and y^T Z (-> sum_a y_a Q_an) are carried along.  The four
-// work arrays of the column are in LDS, or in the global scratch [4][nl][n_cols].
+// A sweep that carries the rows z1 = e_1^T Z and zy = y^T Z of Z, the product of the plane
+// rotations; rotated entries stay in registers for the next rotation, the entries of
+// index i - 1 are read one step ahead.
+__device__ __forceinline__ void ql_sweep_rows(double *d, double *e, double *z1, double *zy, size_t S, int l, int m) {
+  double a_hi = z1[(size_t)m * S], b_hi = zy[(size_t)m * S];
+  double a_i = z1[(size_t)(m - 1) * S], b_i = zy[(size_t)(m - 1) * S];
+  const int lo = ql_sweep(d, e, S, l, m, [&](int i, double c, double s) {
+    const int in = max(i - 1, l);
+    const double a_n = z1[(size_t)in * S], b_n = zy[(size_t)in * S];
+    z1[(size_t)(i + 1) * S] = fma(s, a_i, c * a_hi);
+    a_hi = fma(c, a_i, -s * a_hi);
+    zy[(size_t)(i + 1) * S] = fma(s, b_i, c * b_hi);
+    b_hi = fma(c, b_i, -s * b_hi);
+    a_i = a_n;
+    b_i = b_n;
+  });
+  z1[(size_t)lo * S] = a_hi;
+  zy[(size_t)lo * S] = b_hi;
+}
+
+struct TriArgs {
+  int n_cols, nl;
+  const int *n_used;
+  int used_stride, in_stride;
+  const double *alpha, *beta, *y;
+  double *eps, *q1, *qy;
+  int out_stride, out_col0;
+};
+
+// Column col's elements i0, i0 + di, ...: their largest size; scaled into the work arrays;
+// and the results.
+__device__ __forceinline__ double tri_big(const TriArgs &A, int col, int n, int i0, int di) {
+  double big = 0.0;
+  for (int i = i0; i < n; i += di) {
+    big = fmax(big, fabs(A.alpha[(size_t)i * A.in_stride + col]));
+    if (i + 1 < n) big = fmax(big, fabs(A.beta[(size_t)i * A.in_stride + col]));
+  }
+  return big;
+}
+__device__ __forceinline__ void tri_load(const TriArgs &A, int col, int n, int i0, int di, double sc, double *d, double *e,
+                                         double *z1, double *zy, size_t S) {
+  for (int i = i0; i < n; i += di) {
+    d[(size_t)i * S] = A.alpha[(size_t)i * A.in_stride + col] * sc;
+    e[(size_t)i * S] = (i + 1 < n) ? A.beta[(size_t)i * A.in_stride + col] * sc : 0.0;
+    z1[(size_t)i * S] = (i == 0) ? 1.0 : 0.0;
+    zy[(size_t)i * S] = A.y ? A.y[(size_t)i * A.in_stride + col] : 0.0;
+  }
+}
+__device__ __forceinline__ void tri_store(const TriArgs &A, int col, int n, int i0, int di, int ex, const double *d,
+                                          const double *z1, const double *zy, size_t S) {
+  for (int i = i0; i < A.nl; i += di) {
+    const bool ok = i < n;
+    const size_t o = (size_t)i * A.out_stride + A.out_col0 + col;
+    A.eps[o] = ok ? ldexp(d[(size_t)i * S], ex) : 0.0;
+    A.q1[o] = ok ? z1[(size_t)i * S] : 0.0;
+    A.qy[o] = ok ? zy[(size_t)i * S] : 0.0;
+  }
+}
+
+// One wave per column; the four work arrays of the column are in LDS, or in the global
+// scratch [4][nl][n_cols].
 // 100 steps, 20 columns: 6.2 ms as one lane per column with hypot and two
 // divisions per rotation, 2.6 ms so.
 template <bool LDS>
-__global__ __launch_bounds__(kWave) void tridiag_kernel(int n_cols, int nl, const int *n_used, int used_stride,
-                                                        int in_stride, const double *alpha, const double *beta,
-                                                        const double *y, double *eps, double *q1, double *qy,
-                                                        int out_stride, int out_col0, double *scratch) {
+__global__ __launch_bounds__(kWave) void tridiag_kernel(TriArgs A, double *scratch) {
   extern __shared__ double tri_sh[];
   const int col = blockIdx.x, lane = threadIdx.x;
-  const int n = n_used ? min(n_used[col * used_stride], nl) : nl;
-  const size_t S = LDS ? 1 : (size_t)n_cols;
+  const int n = A.n_used ? min(A.n_used[col * A.used_stride], A.nl) : A.nl;
+  const size_t S = LDS ? 1 : (size_t)A.n_cols;
   double *d = LDS ? tri_sh : scratch + col;
-  double *e = d + (size_t)nl * S, *z1 = e + (size_t)nl * S, *zy = z1 + (size_t)nl * S;
-  double big = 0.0;
-  for (int i = lane; i < n; i += kWave) {
-    big = fmax(big, fabs(alpha[(size_t)i * in_stride + col]));
-    if (i + 1 < n) big = fmax(big, fabs(beta[(size_t)i * in_stride + col]));
-  }
+  double *e = d + (size_t)A.nl * S, *z1 = e + (size_t)A.nl * S, *zy = z1 + (size_t)A.nl * S;
   int ex;
-  const double sc = norm_scale(wave_max(big), &ex);
-  for (int i = lane; i < n; i += kWave) {
-    d[(size_t)i * S] = alpha[(size_t)i * in_stride + col] * sc;
-    e[(size_t)i * S] = (i + 1 < n) ? beta[(size_t)i * in_stride + col] * sc : 0.0;
-    z1[(size_t)i * S] = (i == 0) ? 1.0 : 0.0;
-    zy[(size_t)i * S] = y ? y[(size_t)i * in_stride + col] : 0.0;
-  }
+  const double sc = norm_scale(wave_max(tri_big(A, col, n, lane, kWave)), &ex);
+  tri_load(A, col, n, lane, kWave, sc, d, e, z1, zy, S);
   __syncthreads();
   for (int l = 0; l < n; l++) {
     for (int iter = 0; iter < 100; iter++) {
       const int m = ql_block_end(d, e, S, l, n);
       if (m == l) break;
-      // rotated entries stay in registers for the next rotation, the entries of
-      // index i - 1 are read one step ahead
-      double a_hi = z1[(size_t)m * S], b_hi = zy[(size_t)m * S];
-      double a_i = z1[(size_t)(m - 1) * S], b_i = zy[(size_t)(m - 1) * S];
-      const int lo = ql_sweep(d, e, S, l, m, [&](int i, double c, double s) {
-        const int in = max(i - 1, l);
-        const double a_n = z1[(size_t)in * S], b_n = zy[(size_t)in * S];
-        z1[(size_t)(i + 1) * S] = fma(s, a_i, c * a_hi);
-        a_hi = fma(c, a_i, -s * a_hi);
-        zy[(size_t)(i + 1) * S] = fma(s, b_i, c * b_hi);
-        b_hi = fma(c, b_i, -s * b_hi);
-        a_i = a_n;
-        b_i = b_n;
-      });
-      z1[(size_t)lo * S] = a_hi;
-      zy[(size_t)lo * S] = b_hi;
+      ql_sweep_rows(d, e, z1, zy, S, l, m);
     }
   }
   __syncthreads();
-  const size_t os = (size_t)out_stride;
-  for (int i = lane; i < nl; i += kWave) {
-    const bool ok = i < n;
-    eps[(size_t)i * os + out_col0 + col] = ok ? ldexp(d[(size_t)i * S], ex) : 0.0;
-    q1[(size_t)i * os + out_col0 + col] = ok ? z1[(size_t)i * S] : 0.0;
-    qy[(size_t)i * os + out_col0 + col] = ok ? zy[(size_t)i * S] : 0.0;
+  tri_store(A, col, n, lane, kWave, ex, d, z1, zy, S);
+}
+
+// One lane per column, for columns enough that the rotations are not waited for but
+// issued: the work arrays [4][nl][blockDim] of a block's columns in LDS.  The same
+// rotations as a wave per column, to the bit.
+__global__ __launch_bounds__(kWave) void tridiag_lanes_kernel(TriArgs A) {
+  extern __shared__ double tri_sh[];
+  const int col = blockIdx.x * blockDim.x + threadIdx.x;
+  if (col >= A.n_cols) return;
+  const int n = A.n_used ? min(A.n_used[col * A.used_stride], A.nl) : A.nl;
+  const size_t S = blockDim.x;
+  double *d = tri_sh + threadIdx.x;
+  double *e = d + (size_t)A.nl * S, *z1 = e + (size_t)A.nl * S, *zy = z1 + (size_t)A.nl * S;
+  int ex;
+  const double sc = norm_scale(tri_big(A, col, n, 0, 1), &ex);
+  tri_load(A, col, n, 0, 1, sc, d, e, z1, zy, S);
+  for (int l = 0; l < n; l++) {
+    for (int iter = 0; iter < 100; iter++) {
+      int m = l;
+      for (double dm = fabs(d[(size_t)l * S]); m < n - 1; m++) {
+        const double dm1 = fabs(d[(size_t)(m + 1) * S]);
+        if (fabs(e[(size_t)m * S]) <= 2.220446049250313e-16 * (dm + dm1)) break;
+        dm = dm1;
+      }
+      if (m == l) break;
+      ql_sweep_rows(d, e, z1, zy, S, l, m);
+    }
   }
+  tri_store(A, col, n, 0, 1, ex, d, z1, zy, S);
 }
 
 // One block per column c: element j of alpha and beta at
@@ -267,6 +321,18 @@ __global__ __launch_bounds__(256) void tridiag_full_kernel(int nl, int nbuf, con
   }
 }
 
+// A lane per column instead of a wave?  Its time does not grow until the columns that 64 KB
+// of LDS hold are taken by every block that fits, the other's from about 2000 columns on.
+// Measured (us, wave / lane per column):
+//   steps   320 columns     4000            8000            32,000            128,000
+//   10      46 / 98         85 / 103        145 / 107       500 / 110         1735 / 133
+//   30      295 / 776       584 / 807       1027 / 801      3267 / 823        11813 / 3207
+//   60      1067 / 2970     2031 / 2849     3426 / 2836     11633 / 5756      43312 / 22543
+//   100     2729 / 7791     5107 / 8081     8839 / 7946     30572 / 28299     114929 / 93032
+//   120     3862 / 10898    7125 / 11332    12584 / 10837   43576 / 40922     (64,000: 83498 / 80126)
+//   160     6716 / 18450    12400 / 23136   21855 / 35013   75961 / 108008
+bool lanes_per_column_pay(int n_cols, int nl) { return n_cols >= 7168 && nl <= 128; }
+
 size_t full_smem(int nl, int nbuf) {
   return sizeof(double) * ((size_t)2 * nl + (size_t)2 * nl * nbuf + (size_t)nl * nl);
 }
@@ -278,12 +344,15 @@ int launch_tridiag(int n_cols, int n_lanczos, const int *n_used, int used_stride
                    double *q1, double *qy, int out_stride, int out_col0, double *scratch,
                    hipStream_t s) {
   const size_t lds = (size_t)32 * n_lanczos;  // the four work arrays
-  if (lds <= 64 * 1024)
-    hipLaunchKernelGGL(tridiag_kernel<true>, dim3(n_cols), dim3(kWave), lds, s, n_cols, n_lanczos, n_used,
-                       used_stride, in_stride, alpha, beta, y, eps, q1, qy, out_stride, out_col0, scratch);
-  else
-    hipLaunchKernelGGL(tridiag_kernel<false>, dim3(n_cols), dim3(kWave), 0, s, n_cols, n_lanczos, n_used,
-                       used_stride, in_stride, alpha, beta, y, eps, q1, qy, out_stride, out_col0, scratch);
+  const TriArgs A{n_cols, n_lanczos, n_used, used_stride, in_stride, alpha, beta, y, eps, q1, qy, out_stride, out_col0};
+  if (lanes_per_column_pay(n_cols, n_lanczos)) {
+    const int cpb = (int)std::min<size_t>(kWave, 64 * 1024 / lds);  // as many columns as 64 KB hold
+    hipLaunchKernelGGL(tridiag_lanes_kernel, dim3((n_cols + cpb - 1) / cpb), dim3(cpb), (size_t)cpb * lds, s, A);
+  } else if (lds <= 64 * 1024) {
+    hipLaunchKernelGGL(tridiag_kernel<true>, dim3(n_cols), dim3(kWave), lds, s, A, scratch);
+  } else {
+    hipLaunchKernelGGL(tridiag_kernel<false>, dim3(n_cols), dim3(kWave), 0, s, A, scratch);
+  }
   return hipGetLastError() == hipSuccess ? FTLM_OK : FTLM_EHIP;
 }
 
