@@ -154,6 +154,7 @@ static TableOffsets<R> pack_tables(const HostHam &hh, const std::vector<int> &pe
   o.hflip = b.add(hflip.data(), hflip.size() * sizeof(Cx<R>));
   o.cz_half = b.add(czh.data(), czh.size() * sizeof(Cx<R>));
   o.lowf = b.add(lowf.data(), lowf.size() * sizeof(Cx<R>));
+  if (hh.spin_half && n >= kLowBits) return o;  // (the direct gather of spins 1/2 has the tables above)
   const std::vector<GTerm<R>> pair = gen_terms<R>(hh, perm);
   const GenBlob<R> L(n, hh.has_z, (int)pair.size());
   std::vector<unsigned char> blob(L.total, 0);
@@ -253,12 +254,22 @@ void sort_pairs(const HostHam &hh, std::vector<int> &perm, int &n_ll, int &n_lh,
 }
 
 namespace {
-// FNV-1a over the bytes an H*v launch takes by value.
+// FNV-1a over what an H*v launch takes by value, eight bytes at a time (a field change
+// hashes some 20 KB); the high bits are folded in, as a multiplication never moves them down.
 struct Fnv {
   uint64_t h = 1469598103934665603ull;
+  void word(uint64_t x) {
+    h = (h ^ x) * 1099511628211ull;
+    h ^= h >> 32;
+  }
   void add(const void *p, size_t n) {
     const unsigned char *b = reinterpret_cast<const unsigned char *>(p);
-    for (size_t i = 0; i < n; i++) h = (h ^ b[i]) * 1099511628211ull;
+    for (; n >= 8; n -= 8, b += 8) {
+      uint64_t x;
+      std::memcpy(&x, b, 8);
+      word(x);
+    }
+    for (; n; n--, b++) word(*b);
   }
   template <typename T>
   void pod(const T &x) { add(&x, sizeof(T)); }
@@ -367,6 +378,17 @@ int upload_tables(const HostHam &hh, DevHam &dh, std::string &err) {
         dh.tw32 = WinPlan();
       }
     }
+    // the half sweep's pair tables, and its plans of 2, 4, 8 and 16 columns from the size
+    // on where they are the built-in choice (the same in both precisions)
+    for (int f = 1; f < 5; f++) {
+      WinPlan &tw = dh.twc[0][f - 1];
+      tw = WinPlan();
+      if (hh.spin_half && n > kTileBits && (uint64_t)hh.dim << f >= kHalfColumnsRows) plan_columns(hh, spi, spj, f, tw);
+      if (!tw.passes.empty()) plan_half(plist_coefs<double>(hh, perm, tw.plist), tw);
+      dh.twc[1][f - 1] = tw;
+    }
+    for (WinPlan *tw : {&dh.tw64, &dh.tw32})
+      if (!tw->passes.empty()) plan_half(plist_coefs<double>(hh, perm, tw->plist), *tw);
     dh.plan_valid = true;
     dh.plan_smask = smask;
     dh.plan_wb = wb;
@@ -394,24 +416,20 @@ int upload_tables(const HostHam &hh, DevHam &dh, std::string &err) {
   const std::vector<Cx<float>> tc32 = plist_coefs<float>(hh, perm, dh.tw32.plist);
   const size_t off_c64 = b.add(tc64.data(), tc64.size() * sizeof(Cx<double>));
   const size_t off_c32 = b.add(tc32.data(), tc32.size() * sizeof(Cx<float>));
-  // the half sweep's tables: tile plans, and plans of 2, 4, 8 and 16 columns from the size on
-  // where they are the built-in choice
+  // the half sweep's tables; the diagonal over a tile's sites is field dependent
   struct HalfOff {
     WinPlan *pl;
     bool f32;
     size_t off[7];
   };
   std::vector<HalfOff> halves;
-  for (int q = 0; q < 2; q++)
-    for (int f = 0; f < 5; f++) {
+  for (int f = 0; f < 5; f++) {
+    const std::vector<double> td = (f ? dh.twc[0][f - 1] : dh.tw64).passes.empty() ? std::vector<double>() : half_tile_diagonal(hh, f);
+    if (td.empty()) continue;
+    const std::vector<float> td32(td.begin(), td.end());
+    const std::vector<Cx<double>> pc = f ? plist_coefs<double>(hh, perm, dh.twc[0][f - 1].plist) : std::vector<Cx<double>>();
+    for (int q = 0; q < 2; q++) {
       WinPlan &tw = f ? dh.twc[q][f - 1] : q ? dh.tw32 : dh.tw64;
-      if (f) {
-        tw = WinPlan();
-        if (hh.spin_half && n > kTileBits && (uint64_t)hh.dim << f >= kHalfColumnsRows) plan_columns(hh, spi, spj, f, tw);
-      }
-      if (tw.passes.empty()) continue;
-      const std::vector<Cx<double>> pc = plist_coefs<double>(hh, perm, tw.plist);
-      plan_half(hh, pc, f, tw);
       const HalfTables &H = tw.half;
       HalfOff h{&tw, q != 0, {}};
       auto add_cx = [&](const std::vector<Cx<double>> &x) {
@@ -424,14 +442,14 @@ int upload_tables(const HostHam &hh, DevHam &dh, std::string &err) {
       h.off[1] = b.add(H.msk.data(), H.msk.size() * sizeof(uint32_t));
       h.off[2] = add_cx(H.gco);
       h.off[3] = add_cx(H.mco);
-      const std::vector<float> td(H.tdiag.begin(), H.tdiag.end());
-      h.off[4] = q ? b.add(td.data(), td.size() * sizeof(float)) : b.add(H.tdiag.data(), H.tdiag.size() * sizeof(double));
+      h.off[4] = q ? b.add(td32.data(), td32.size() * sizeof(float)) : b.add(td.data(), td.size() * sizeof(double));
       if (f) {
         h.off[5] = b.add(tw.plist.data(), tw.plist.size() * sizeof(int4));
         h.off[6] = add_cx(pc);
       }
       halves.push_back(h);
     }
+  }
   // single-pass tile plans (64 KB tiles); field dependent (single flips,
   // complex coefficients, the tile diagonal)
   plan_stream(hh, 65536 / sizeof(Cx<double>), dh.sp64);

@@ -232,10 +232,10 @@ struct HalfTables {
   std::vector<Cx<double>> gco;    // [group][member][4]
   std::vector<uint32_t> msk;      // [outer site of a pass]: tile sites coupled to it
   std::vector<Cx<double>> mco;    // [outer site of a pass][its bit][tile site][the site's bit]
-  std::vector<double> tdiag;      // [2048 / columns] diagonal over the tile's sites
   const uint32_t *d_grp = nullptr;  // device copies (inside the handle's table block)
   const uint32_t *d_msk = nullptr;
-  const void *d_gco = nullptr, *d_mco = nullptr, *d_tdiag = nullptr;  // in the plan's precision
+  const void *d_gco = nullptr, *d_mco = nullptr;  // in the plan's precision
+  const void *d_tdiag = nullptr;                  // [2048 / columns] diagonal over the tile's sites
 };
 
 struct WinPlan {
@@ -252,7 +252,9 @@ struct WinPlan {
   HalfTables half;  // tile plans
 };
 // Fills plan.half and the passes' records of it; pcoef: the coefficients in plist order.
-void plan_half(const HostHam &hh, const std::vector<Cx<double>> &pcoef, int f, WinPlan &plan);
+void plan_half(const std::vector<Cx<double>> &pcoef, WinPlan &plan);
+// Diagonal over the sites of a tile of 2^f columns.
+std::vector<double> half_tile_diagonal(const HostHam &hh, int f);
 // The half sweep's plan for 2^f columns (f = 1 to 4).
 void plan_columns(const HostHam &hh, const std::vector<int> &pi, const std::vector<int> &pj, int f, WinPlan &plan);
 

@@ -554,7 +554,7 @@ int layout_base(int L) { return L == 0 ? 8 : L == 1 ? 5 : L == 2 ? 2 : 0; }
 // The in-tile pairs of every pass as groups (layout of the higher site j; the lower
 // site i when it is not a register bit of that layout), and the mixed pairs by outer
 // site; pcoef: four coefficients per list entry, by the row bits (i, j).
-void plan_half(const HostHam &hh, const std::vector<Cx<double>> &pcoef, int f, WinPlan &plan) {
+void plan_half(const std::vector<Cx<double>> &pcoef, WinPlan &plan) {
   HalfTables &H = plan.half;
   H.grp.clear();
   H.gco.clear();
@@ -604,14 +604,16 @@ void plan_half(const HostHam &hh, const std::vector<Cx<double>> &pcoef, int f, W
       H.mco.insert(H.mco.end(), c, c + 4 * kTileBits);
     }
   }
-  // diagonal over the tile's sites, doubled site by site: raising site k adds its own
-  // difference and the z-field g of the others, g itself doubled over the sites below k
+}
+
+// Doubled site by site: raising site k adds its own difference and the z-field g of the
+// others, g itself doubled over the sites below k.
+std::vector<double> half_tile_diagonal(const HostHam &hh, int f) {
   const int n = hh.n, nt = kTileBits - f;
-  H.tdiag.assign((size_t)1 << nt, 0.0);
-  std::vector<double> g((size_t)1 << nt);
+  std::vector<double> tdiag((size_t)1 << nt, 0.0), g((size_t)1 << nt);
   for (int k = 0; k < nt; k++) {
-    H.tdiag[0] += hh.h[(size_t)k * 256].re;
-    for (int j = 0; j < k; j++) H.tdiag[0] += 0.25 * hh.zz[(size_t)k * n + j];
+    tdiag[0] += hh.h[(size_t)k * 256].re;
+    for (int j = 0; j < k; j++) tdiag[0] += 0.25 * hh.zz[(size_t)k * n + j];
   }
   for (int k = 0; k < nt; k++) {
     const double *z = &hh.zz[(size_t)k * n];
@@ -620,8 +622,9 @@ void plan_half(const HostHam &hh, const std::vector<Cx<double>> &pcoef, int f, W
       if (j != k) g[0] -= 0.5 * z[j];
     for (int j = 0; j < k; j++)
       for (int r = 0; r < 1 << j; r++) g[r + (1 << j)] = g[r] + z[j];
-    for (int r = 0; r < 1 << k; r++) H.tdiag[r + (1 << k)] = H.tdiag[r] + g[r];
+    for (int r = 0; r < 1 << k; r++) tdiag[r + (1 << k)] = tdiag[r] + g[r];
   }
+  return tdiag;
 }
 
 // One pass over all rows for 2^f columns: row bits (site k on bit k + f), pairs in the

@@ -611,20 +611,26 @@ void plan_sweep(const HostHam &hh, size_t es, uint32_t tile_rows, SweepPlan &pl)
       for (int b = 0; b < hh.radix[k]; b++)
         if (a != b) cplx = cplx || hh.h[(size_t)k * 256 + a * 16 + b].im != 0.0;
   pl.cplx = cplx;
-  // diagonal over the tile sites, per tile row
+  // diagonal over the tile sites, per tile row, built site by site: a value d of site k adds
+  // its own element and its moment times the z-field of the sites below (every row anew
+  // took 87 us of each field change of the centred cube, and this 5)
   pl.tdiag.assign(T, 0.0);
-  for (uint32_t r = 0; r < T; r++) {
-    double sum = 0;
-    int d[kMaxSites];
-    uint32_t rem = r;
-    for (int i = 0; i < t; i++) {
-      d[i] = (int)(rem % (uint32_t)G.radix[i]);
-      rem /= (uint32_t)G.radix[i];
-      sum += hh.h[(size_t)i * 256 + d[i] * 16 + d[i]].re;
-      for (int j = 0; j < i; j++)
-        sum += hh.zz[(size_t)i * n + j] * (d[i] - 0.5 * hh.two_s[i]) * (d[j] - 0.5 * hh.two_s[j]);
+  std::vector<double> zf(T);
+  uint32_t below = 1;  // rows of the sites below k
+  for (int k = 0; k < t; k++) {
+    zf[0] = 0.0;
+    uint32_t m = 1;
+    for (int j = 0; j < k; j++) {
+      const double z = hh.zz[(size_t)k * n + j];
+      for (int d = G.radix[j] - 1; d >= 0; d--)
+        for (uint32_t r = 0; r < m; r++) zf[r + d * m] = zf[r] + z * (d - 0.5 * hh.two_s[j]);
+      m *= (uint32_t)G.radix[j];
     }
-    pl.tdiag[r] = sum;
+    for (int d = G.radix[k] - 1; d >= 0; d--) {
+      const double own = hh.h[(size_t)k * 256 + d * 16 + d].re, mk = d - 0.5 * hh.two_s[k];
+      for (uint32_t r = 0; r < below; r++) pl.tdiag[r + d * below] = pl.tdiag[r] + (own + mk * zf[r]);
+    }
+    below *= (uint32_t)G.radix[k];
   }
   // a thread's byte offset in its tile has 32 bits; the block's tables and tile share the LDS
   const size_t lds = es == 16 ? SweepLds<double>(G).total : SweepLds<float>(G).total;
