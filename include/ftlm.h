@@ -97,40 +97,47 @@ int ftlm_hamiltonian_set_field(ftlm_hamiltonian *h, const double B[3]);
 int ftlm_apply(const ftlm_hamiltonian *h, int32_t precision, int32_t n_cols, const void *v,
                void *w, void *stream);
 
-/* Autotuner: times every admissible H*v configuration for (precision, n_cols) on
- * the caller's device buffers v, w ([dim][n_cols], as ftlm_apply) -- variants
- * 1 = direct gather (columns per lane 1, 2, 4, 8), 2 = windowed LDS passes,
- * 3 = LDS tile (spin 1/2, N >= 11), 4 = L2-window passes (one column), 5 = LDS
- * tile walked over L2 windows (spin 1/2, N >= 12; 1 column, and 2, 4, 8 or 16 of at
- * least 2^19 / n_cols rows, take 256 threads and ignore the columns-per-lane field;
- * with other columns it gives 256, 512 or 1024 threads per tile as 1, 2 or 4 row
- * groups), 6 = single pass
- * over LDS tiles of the low digits with coalesced partner reads for the terms
- * on outer sites (one column; Hamiltonians without s+- s^z pair pieces, i.e.
- * whose single-flip coefficients do not depend on the other sites; the
- * columns-per-lane field carries the block size in bits 0..3 -- 1: 256
- * threads for tiles of up to 4096 rows, else 1024 --, the log2 of the
- * tiles per XCD chunk in bits 4..7, and in bit 8 whether the partner tiles of
- * the pairs with one tile site are staged in LDS, one per outer site and move,
- * instead of read directly; not for systems of spins 1/2 only, where a launch
- * with bit 8 set fails with FTLM_EINVAL; general-radix systems of 2^16 rows and
- * more whose top tile site has 3 to 6 values take only the chunk bits: their
- * block follows from the tile and every partner tile is staged), each at 512, 1024, 2048 and 4096 blocks (variants 4, 5, 6: at most
- * 2048) --
- * with HIP events on the stream (blocking): three launches each, then the four
- * fastest again with ten launches each.  Stores the fastest of that second
- * round in the handle for later ftlm_apply / ftlm_run launches of the same
- * shape.  Outputs (may be NULL): the chosen variant, grid size, columns per
- * lane and its mean time over the ten launches. */
+/* Autotuner: times the built-in H*v launch and every admissible configuration for
+ * (precision, n_cols) on the caller's device buffers v, w ([dim][n_cols], as
+ * ftlm_apply) -- variants
+ * 1 = direct gather (columns per lane 1, 2, 4, 8);
+ * 2 = windowed LDS passes (one column);
+ * 3 = LDS tile (spin 1/2, N >= 11, one column);
+ * 4 = L2-window passes (timed for one column);
+ * 5 = LDS tile walked over L2 windows (spin 1/2, N >= 12; 1 column, and 2, 4, 8 or 16
+ *     of at least 2^19 / n_cols rows, take 256 threads and ignore the columns-per-lane
+ *     field; with other columns it gives 256, 512 or 1024 threads per tile as 1, 2 or 4
+ *     row groups, and is not timed);
+ * 6 = single pass over LDS tiles of the low digits with coalesced partner reads for the
+ *     terms on outer sites (one column; Hamiltonians without s+- s^z pair pieces, i.e.
+ *     whose single-flip coefficients do not depend on the other sites; the
+ *     columns-per-lane field carries the block size in bits 0..3 -- 1: 256 threads for
+ *     tiles of up to 4096 rows, else 1024 --, the log2 of the tiles per XCD chunk in
+ *     bits 4..7, and in bit 8 whether the partner tiles of the pairs with one tile site
+ *     are staged in LDS, one per outer site and move, instead of read directly; not for
+ *     systems of spins 1/2 only, where a launch with bit 8 set fails with FTLM_EINVAL;
+ *     general-radix systems of 2^16 rows and more whose top tile site has 3 to 6 values
+ *     take only the chunk bits: their block follows from the tile and every partner tile
+ *     is staged)
+ * -- each at 512, 1024, 2048 and 4096 blocks (variants 4, 5, 6: at most 2048; 5 and 6 also
+ * at the grid of their own that 0 stands for) with HIP events on the stream (blocking):
+ * three launches each, then the built-in launch and the four fastest others again with
+ * ten launches each.  Stores the fastest of that second round, or the built-in launch
+ * where no other is faster by 3 per cent, in the handle for later ftlm_apply / ftlm_run
+ * launches of the same shape.  Outputs (may be NULL): the chosen variant, grid size (0:
+ * the launch's own), columns per lane (0: the launch's own) and its mean time over the
+ * ten launches. */
 int ftlm_hamiltonian_autotune(ftlm_hamiltonian *h, int32_t precision, int32_t n_cols, const void *v,
                               void *w, void *stream, int32_t *variant, int32_t *grid_cap,
                               int32_t *kc, float *best_ms);
 /* Sets the H*v configuration for (precision, n_cols) directly (e.g. from a cache
- * of earlier autotune results); variant 0 restores the built-in heuristic: for
- * one column of at least 2^20 rows the single-pass tile kernel (variant 6) when
- * the Hamiltonian has no s+- s^z pair pieces; else, for spin 1/2, the LDS tile
- * over L2 windows (variant 5) from 2^19 rows and the direct gather below; other
- * spins the windowed passes from 2^20 rows; otherwise the direct gather. */
+ * of earlier autotune results); variant 0 restores the built-in choice.  One column of
+ * spins 1/2: variant 5 from 2^18 rows, but variant 6 for complex128 vectors of 2^20 rows
+ * and more with at most 3 pairs per site and no s+- s^z pair pieces, and variant 1 below
+ * 2^18 rows.  One column of other systems: from 2^20 rows variant 6 without s+- s^z pair
+ * pieces and variant 2 with them, variant 1 below.  2, 4, 8 or 16 columns of spins 1/2:
+ * variant 5 from 2^19 / n_cols rows (complex64, 2 or 4 columns: 2^20 / n_cols) unless the
+ * Hamiltonian has single flips and few pairs per site.  Else variant 1. */
 int ftlm_hamiltonian_set_tuning(ftlm_hamiltonian *h, int32_t precision, int32_t n_cols,
                                 int32_t variant, int32_t grid_cap, int32_t kc);
 

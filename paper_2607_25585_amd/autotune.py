@@ -1,8 +1,9 @@
 """Autotuning of the H*v launch and of the batched run, with a JSON cache.
 
 Plain H*v: the cache key is the spin list, the set of active Hamiltonian
-terms, the precision and the column count; its value is the configuration the
-library's autotuner measured fastest (variant, grid size, columns per lane).
+terms, the precision, the column count and the revision of the launches that the
+variants name; its value is the configuration the library's autotuner measured
+fastest (variant, grid size -- 0: the launch's own --, columns per lane).
 
 Batched run: the key is the sorted spin lists of the instances, their term
 sets, the precision and R; the value is the fastest (columns per item, grid
@@ -32,11 +33,16 @@ def cache_path() -> str:
     return os.path.join(os.path.expanduser("~"), ".cache", "ftlm_mi355x", "hv_tuning.json")
 
 
+# Raised when a variant comes to name other kernels, or the built-in choice does: a choice
+# timed among the earlier ones is then timed again.
+LAUNCHES = 2
+
+
 def tuning_key(ham, precision: int, n_cols: int) -> str:
     terms = "J%d-d%d-dip%d" % (ham._J is not None and bool(np.any(ham._J)),
                                ham._d is not None and bool(np.any(ham._d)), ham._pos is not None)
     spins = hashlib.sha1(np.asarray(ham._two_s).tobytes()).hexdigest()[:12]
-    return "n%d-s%s-%s-p%d-k%d" % (ham.n_sites, spins, terms, precision, n_cols)
+    return "n%d-s%s-%s-p%d-k%d-l%d" % (ham.n_sites, spins, terms, precision, n_cols, LAUNCHES)
 
 
 def _load():

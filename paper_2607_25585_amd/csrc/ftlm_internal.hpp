@@ -436,6 +436,9 @@ int launch_half_sweep(const DevHam &dh, int precision, const HvParams &P, int ca
 // first use).  Synchronous.
 int build_pass_records(DevHam &dh, std::string &err);
 void free_pass_records(DevHam &dh);
+// The launch of variant 0 for K columns, and whether variant 5 is the half sweep for them.
+int hv_builtin_variant(const DevHam &dh, int precision, int K);
+bool hv_half_sweeps(const DevHam &dh, int precision, int K);
 int hv_grid_blocks(const DevHam &dh, const HvLaunch &L, int *gx, int *gy, int *kc, int *lpr);
 
 int launch_gaussian(uint64_t seed, uint32_t inst, uint32_t field, uint32_t r0, int K,

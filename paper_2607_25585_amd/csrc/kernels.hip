@@ -2381,6 +2381,37 @@ static bool half_columns_pay(const HamGeom &g, int precision, int K) {
   return 2 * g.npair > (2 * least - 1) * g.n;  // (open ends leave a few pairs out)
 }
 
+bool hv_half_sweeps(const DevHam &dh, int precision, int K) {
+  return K == 1 ? !(precision == FTLM_C64 ? dh.tw32 : dh.tw64).passes.empty() : half_columns(dh, precision, K);
+}
+
+// One column.  Spins 1/2: the half sweep over L2 windows from 2^18 rows, below that the
+// direct gather; complex128 vectors of few pairs take the single-pass tile kernel instead,
+// where its plan exists (no s+- s^z pair pieces): its time goes with the pairs, the half
+// sweep's has a part that does not (2^22 rows: 152 and 184 us with 2 pairs per site, 870
+// and 364 with 10).  Measured (us, complex128 / complex64):
+//   rows                      2^18       2^19       2^20       2^22       2^24
+//   all pairs  direct gather  49 / 39    96 / 85    181 / 163  882 / 762  4619 / 3633
+//              LDS tile       120 / 78   142 / 92   159 / 109  792 / 405  3759 / 1850
+//              half sweep     45 / 39    52 / 45    77 / 58    396 / 207  2280 / 1177
+//   2 per site direct gather  22 / 17               76 / 60    317 / 255  1459 / 1188
+//              single pass    29 / 44               38 / 48    152 / 106  638 / 423
+//              half sweep     21 / 17               42 / 26    184 / 82   763 / 380
+// (a tile walks its pairs serially, so a vector of few tiles leaves the chip idle)
+// Other vectors beyond the caches: the single-pass kernels beat the multi-pass ones on
+// every such workload measured.
+int hv_builtin_variant(const DevHam &dh, int precision, int K) {
+  const bool f32 = precision == FTLM_C64, single = (f32 ? dh.sp32 : dh.sp64).ok;
+  const HamGeom &g = dh.geom;
+  if (K > 1) return half_columns(dh, precision, K) && half_columns_pay(g, precision, K) ? 5 : 1;
+  if (g.spin_half && g.dim >= (1u << 18) && hv_half_sweeps(dh, precision, 1) &&
+      (f32 || !single || g.npair > 3 * g.n || g.dim < (1u << 20)))
+    return 5;
+  if (single && g.dim >= (1u << 20)) return 6;
+  if (g.spin_half && g.dim < (1u << 18)) return 1;
+  return use_passes(g, K, 0) ? 2 : tile_ok(g, K) ? 3 : 1;
+}
+
 int launch_hv(const DevHam &dh, const HvLaunch &Lin, hipStream_t s) {
   HvLaunch L = Lin;
   if (L.K >= 1 && L.K <= 64 && (L.precision == 0 || L.precision == 1)) {
@@ -2389,34 +2420,7 @@ int launch_hv(const DevHam &dh, const HvLaunch &Lin, hipStream_t s) {
     if (!L.grid_cap) L.grid_cap = tn.grid_cap;
     if (!L.kc) L.kc = tn.kc;
   }
-  // built-in choice, one column.  Spins 1/2: the half sweep over L2 windows from 2^18
-  // rows, below that the direct gather; complex128 vectors of few pairs take the
-  // single-pass tile kernel instead, where its plan exists (no s+- s^z pair pieces): its
-  // time goes with the pairs, the half sweep's has a part that does not (2^22 rows: 152
-  // and 184 us with 2 pairs per site, 870 and 364 with 10).  Measured (us, complex128 /
-  // complex64):
-  //   rows                      2^18       2^19       2^20       2^22       2^24
-  //   all pairs  direct gather  49 / 39    96 / 85    181 / 163  882 / 762  4619 / 3633
-  //              LDS tile       120 / 78   142 / 92   159 / 109  792 / 405  3759 / 1850
-  //              half sweep     45 / 39    52 / 45    77 / 58    396 / 207  2280 / 1177
-  //   2 per site direct gather  22 / 17               76 / 60    317 / 255  1459 / 1188
-  //              single pass    29 / 44               38 / 48    152 / 106  638 / 423
-  //              half sweep     21 / 17               42 / 26    184 / 82   763 / 380
-  // (a tile walks its pairs serially, so a vector of few tiles leaves the chip idle)
-  if (!L.variant && L.K == 1) {
-    const bool f32 = L.precision == FTLM_C64, single = (f32 ? dh.sp32 : dh.sp64).ok;
-    const HamGeom &g = dh.geom;
-    if (g.spin_half && g.dim >= (1u << 18) && !(f32 ? dh.tw32 : dh.tw64).passes.empty() &&
-        (f32 || !single || g.npair > 3 * g.n || g.dim < (1u << 20)))
-      L.variant = 5;
-    // other vectors beyond the caches: the single-pass kernels beat the multi-pass ones on
-    // every such workload measured
-    else if (single && g.dim >= (1u << 20))
-      L.variant = 6;
-    else if (g.spin_half && g.dim < (1u << 18))
-      L.variant = 1;
-  }
-  if (!L.variant && half_columns(dh, L.precision, L.K) && half_columns_pay(dh.geom, L.precision, L.K)) L.variant = 5;
+  if (!L.variant) L.variant = hv_builtin_variant(dh, L.precision, L.K);
   g_variant = L.variant;
   int gx, gy, kc, lpr;
   const int rcg = hv_grid_blocks(dh, L, &gx, &gy, &kc, &lpr);

@@ -1,7 +1,8 @@
-// Autotuner of the H*v launch: times every admissible (variant, grid size,
-// columns per lane) on the caller's buffers with HIP events, times the four
-// fastest again with more launches, and keeps the fastest in the handle; subsequent ftlm_apply / ftlm_run launches with the same
-// precision and column count use it.
+// Autotuner of the H*v launch: times the built-in launch and every admissible (variant,
+// grid size, columns per lane) on the caller's buffers with HIP events, times the built-in
+// one and the four fastest again with more launches, and keeps the fastest in the handle
+// (the built-in one unless another is clearly faster); subsequent ftlm_apply / ftlm_run
+// launches with the same precision and column count use it.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -43,20 +44,30 @@ int ftlm_hamiltonian_autotune(ftlm_hamiltonian *h, int32_t precision, int32_t n_
   struct Cand {
     int variant, cap, kc;
   };
-  std::vector<Cand> cands;
-  const int caps[4] = {512, 1024, 2048, 4096};
+  // the built-in launch first, with its own grid
+  const int own = hv_builtin_variant(h->dev, precision, n_cols);
+  std::vector<Cand> cands{{own, 0, 0}};
+  const bool f32 = precision == FTLM_C64;
+  const bool sweep = (f32 ? h->dev.sw32 : h->dev.sw64).ok, single = (f32 ? h->dev.sp32 : h->dev.sp64).ok;
+  const bool half = hv_half_sweeps(h->dev, precision, n_cols);
+  if (own != 1) cands.push_back({1, 0, 0});
+  const int caps[5] = {0, 512, 1024, 2048, 4096};  // 0: the launch's own, of those that have one
   for (int cap : caps) {
+    // half sweep (its threads are fixed)
+    if (half && cap <= 2048 && (cap || own != 5)) cands.push_back({5, cap, 0});
+    // tile sweep: chunks of 1, 4, 16 or 64 tiles per XCD; its block follows from the tile
+    if (n_cols == 1 && cap <= 2048 && sweep)
+      for (int ch : {0, 2, 4, 6})
+        if (cap || ch || own != 6) cands.push_back({6, cap, ch << 4});
+    if (!cap) continue;
     for (int k : {1, 2, 4, 8})
       if (n_cols % k == 0) cands.push_back({1, cap, k});
     if (n_cols == 1) cands.push_back({2, cap, 0});
     if (n_cols == 1 && g.spin_half && g.n >= kTileBits) cands.push_back({3, cap, 0});
     if (n_cols == 1 && cap <= 2048) cands.push_back({4, cap, 0});
-    if (n_cols == 1 && cap <= 2048 && g.spin_half && g.n > kTileBits &&
-        !(precision == FTLM_C64 ? h->dev.tw32 : h->dev.tw64).passes.empty())
-      cands.push_back({5, cap, 0});
     // stream kernel: 1024 or 256 threads per block, chunks of 1, 4, 16 or 64 tiles per
     // XCD, the mixed pairs' partner tiles read directly or staged in LDS
-    if (n_cols == 1 && cap <= 2048 && (precision == FTLM_C64 ? h->dev.sp32 : h->dev.sp64).ok)
+    if (n_cols == 1 && cap <= 2048 && single && !sweep)
       for (int st : {0, 1})
         for (int nt : {0, 1})
           for (int ch : {0, 2, 4, 6}) cands.push_back({6, cap, nt | (ch << 4) | (st << 8)});
@@ -66,9 +77,11 @@ int ftlm_hamiltonian_autotune(ftlm_hamiltonian *h, int32_t precision, int32_t n_
     set_error("hipEventCreate failed");
     return FTLM_EHIP;
   }
+  // (an earlier choice would stand in for a candidate's zeros)
   const HvTuning saved = h->dev.tune[precision][n_cols];
+  h->dev.tune[precision][n_cols] = HvTuning{};
   float best = FLT_MAX;
-  Cand bestc{0, 0, 0};
+  int bestc = 0;
   int rc = FTLM_OK;
   // mean time of reps launches after one warm-up launch; < 0 if the shape is
   // inadmissible, NaN on a HIP error
@@ -89,9 +102,10 @@ int ftlm_hamiltonian_autotune(ftlm_hamiltonian *h, int32_t precision, int32_t n_
     (void)hipEventElapsedTime(&ms, e0, e1);
     return ms / (float)reps;
   };
-  // a quick pass over every candidate, then the four fastest again with more
-  // launches each (neighbouring grid sizes often differ by a few per cent,
-  // within the noise of three launches)
+  // a quick pass over every candidate, then the built-in launch and the four fastest others
+  // again with more launches each (neighbouring grid sizes often differ by a few per
+  // cent, within the noise of three launches; of grid sizes alone at most two, as those
+  // beyond a launch's tiles are one launch)
   std::vector<std::pair<float, int>> timed;
   for (size_t i = 0; i < cands.size() && !rc; i++) {
     const float ms = time_cand(cands[i], 3);
@@ -99,12 +113,21 @@ int ftlm_hamiltonian_autotune(ftlm_hamiltonian *h, int32_t precision, int32_t n_
     else if (ms >= 0) timed.push_back({ms, (int)i});
   }
   std::sort(timed.begin(), timed.end());
-  for (size_t r = 0; r < timed.size() && r < 4 && !rc; r++) {
-    const float ms = time_cand(cands[timed[r].second], 10);
+  std::vector<int> finals{0};
+  for (const auto &t : timed) {
+    const Cand &c = cands[t.second];
+    const int same = (int)std::count_if(finals.begin(), finals.end(),
+                                        [&](int i) { return cands[i].variant == c.variant && cands[i].kc == c.kc; });
+    if (t.second && same < 2 && finals.size() < 5) finals.push_back(t.second);
+  }
+  for (int i : finals) {
+    if (rc) break;
+    const float ms = time_cand(cands[i], 10);
     if (std::isnan(ms)) rc = FTLM_EHIP;
-    else if (ms >= 0 && ms < best) {
+    // (two means of ten launches differ by a few per cent by themselves)
+    else if (ms >= 0 && (best == FLT_MAX || ms < best * (bestc == 0 ? 0.97f : 1.0f))) {
       best = ms;
-      bestc = cands[timed[r].second];
+      bestc = i;
     }
   }
   (void)hipEventDestroy(e0);
@@ -115,16 +138,17 @@ int ftlm_hamiltonian_autotune(ftlm_hamiltonian *h, int32_t precision, int32_t n_
     return rc;
   }
   if (best == FLT_MAX) {
+    h->dev.tune[precision][n_cols] = saved;
     set_error("no admissible H*v configuration");
     return FTLM_EINVAL;
   }
   HvTuning &t = h->dev.tune[precision][n_cols];
-  t.variant = bestc.variant;
-  t.grid_cap = bestc.cap;
-  t.kc = bestc.kc;
-  if (variant) *variant = bestc.variant;
-  if (grid_cap) *grid_cap = bestc.cap;
-  if (kc) *kc = bestc.kc;
+  t.variant = cands[bestc].variant;
+  t.grid_cap = cands[bestc].cap;
+  t.kc = cands[bestc].kc;
+  if (variant) *variant = t.variant;
+  if (grid_cap) *grid_cap = t.grid_cap;
+  if (kc) *kc = t.kc;
   if (best_ms) *best_ms = best;
   return FTLM_OK;
 }
