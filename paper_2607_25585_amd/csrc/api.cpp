@@ -303,6 +303,8 @@ uint64_t launch_signature(const DevHam &dh) {
     f.pod(pl->half.d_gco);
     f.pod(pl->half.d_mco);
     f.pod(pl->half.d_tdiag);
+    f.pod(pl->half.d_plist);
+    f.pod(pl->half.d_pcoef);
   }
   for (const StreamPlan *sp : {&dh.sp64, &dh.sp32}) {
     f.pod(sp->ok);
@@ -427,7 +429,6 @@ int upload_tables(const HostHam &hh, DevHam &dh, std::string &err) {
     const std::vector<double> td = (f ? dh.twc[0][f - 1] : dh.tw64).passes.empty() ? std::vector<double>() : half_tile_diagonal(hh, f);
     if (td.empty()) continue;
     const std::vector<float> td32(td.begin(), td.end());
-    const std::vector<Cx<double>> pc = f ? plist_coefs<double>(hh, perm, dh.twc[0][f - 1].plist) : std::vector<Cx<double>>();
     for (int q = 0; q < 2; q++) {
       WinPlan &tw = f ? dh.twc[q][f - 1] : q ? dh.tw32 : dh.tw64;
       const HalfTables &H = tw.half;
@@ -443,10 +444,8 @@ int upload_tables(const HostHam &hh, DevHam &dh, std::string &err) {
       h.off[2] = add_cx(H.gco);
       h.off[3] = add_cx(H.mco);
       h.off[4] = q ? b.add(td32.data(), td32.size() * sizeof(float)) : b.add(td.data(), td.size() * sizeof(double));
-      if (f) {
-        h.off[5] = b.add(tw.plist.data(), tw.plist.size() * sizeof(int4));
-        h.off[6] = add_cx(pc);
-      }
+      h.off[5] = b.add(H.plist.data(), H.plist.size() * sizeof(int4));
+      h.off[6] = add_cx(plist_coefs<double>(hh, perm, H.plist));
       halves.push_back(h);
     }
   }
@@ -536,10 +535,8 @@ int upload_tables(const HostHam &hh, DevHam &dh, std::string &err) {
     H.d_gco = base + h.off[2];
     H.d_mco = base + h.off[3];
     H.d_tdiag = base + h.off[4];
-    if (h.off[5]) {
-      h.pl->d_plist = reinterpret_cast<const int4 *>(base + h.off[5]);
-      h.pl->d_pcoef = base + h.off[6];
-    }
+    H.d_plist = reinterpret_cast<const int4 *>(base + h.off[5]);
+    H.d_pcoef = base + h.off[6];
   }
   dh.tw64.d_pcoef = dh.tw64.plist.empty() ? nullptr : base + off_c64;
   dh.tw32.d_pcoef = dh.tw32.plist.empty() ? nullptr : base + off_c32;

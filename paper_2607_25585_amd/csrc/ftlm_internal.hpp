@@ -232,10 +232,13 @@ struct HalfTables {
   std::vector<Cx<double>> gco;    // [group][member][4]
   std::vector<uint32_t> msk;      // [outer site of a pass]: tile sites coupled to it
   std::vector<Cx<double>> mco;    // [outer site of a pass][its bit][tile site][the site's bit]
+  std::vector<int4> plist;        // the plan's list, a pass's pairs of two outer sites by (j, i)
   const uint32_t *d_grp = nullptr;  // device copies (inside the handle's table block)
   const uint32_t *d_msk = nullptr;
   const void *d_gco = nullptr, *d_mco = nullptr;  // in the plan's precision
   const void *d_tdiag = nullptr;                  // [2048 / columns] diagonal over the tile's sites
+  const int4 *d_plist = nullptr;
+  const void *d_pcoef = nullptr;  // the pairs' coefficients in the list's order
 };
 
 struct WinPlan {

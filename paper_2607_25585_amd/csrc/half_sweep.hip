@@ -514,7 +514,7 @@ int launch_r(const HamGeom &g, const DevTables<R> &tb, const WinPlan &plan, int 
              unsigned *last_gx, hipStream_t s) {
   static std::atomic<size_t> granted{0};  // per instantiation: largest dynamic LDS size requested so far
   const HalfTables &H = plan.half;
-  if (!plan.d_plist || !plan.d_pcoef || !H.d_grp || plan.passes.empty()) return FTLM_EINVAL;
+  if (!H.d_plist || !H.d_pcoef || !H.d_grp || plan.passes.empty()) return FTLM_EINVAL;
   // the blocks that are resident, but for a single pass of complex128 (2^22 rows: complex64
   // 213 us with 768 blocks, 226 with 2048; complex128 402 with 2048, 417 with 512; in
   // several passes, 2^24 rows: 2421 and 2275)
@@ -533,8 +533,8 @@ int launch_r(const HamGeom &g, const DevTables<R> &tb, const WinPlan &plan, int 
     }
     hipLaunchKernelGGL((hv_half_sweep<R, COLS>), dim3(gx), dim3(kBlock), sm, s, g, tb, W, H.d_grp,
                        reinterpret_cast<const Cx<R> *>(H.d_gco), H.d_msk, reinterpret_cast<const Cx<R> *>(H.d_mco),
-                       reinterpret_cast<const R *>(H.d_tdiag), plan.d_plist,
-                       reinterpret_cast<const Cx<R> *>(plan.d_pcoef), f, Pp);
+                       reinterpret_cast<const R *>(H.d_tdiag), H.d_plist,
+                       reinterpret_cast<const Cx<R> *>(H.d_pcoef), f, Pp);
     *last_gx = gx;
   }
   return FTLM_OK;
@@ -560,7 +560,13 @@ void plan_half(const std::vector<Cx<double>> &pcoef, WinPlan &plan) {
   H.gco.clear();
   H.msk.clear();
   H.mco.clear();
+  // (by j, then i, the tiles that an XCD works on share more partners: 2^22 rows, all pairs
+  // coupled, complex128 399 us against 539 by i, then j; the tile kernel of the other column
+  // counts keeps that order: 2^20 rows x 3 675 us, 853 by j, then i)
+  H.plist = plan.plist;
   for (WinPass &W : plan.passes) {
+    std::stable_sort(H.plist.begin() + W.p0 + W.np_ll + W.np_lh, H.plist.begin() + W.p0 + W.np,
+                     [](const int4 &a, const int4 &b) { return a.z != b.z ? a.z < b.z : a.y < b.y; });
     for (int L = 0; L < 4; L++) {
       W.hg[L] = (int)H.grp.size();
       const int lo = layout_base(L), nr = L == 3 ? 2 : 3;

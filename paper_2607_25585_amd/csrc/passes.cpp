@@ -390,8 +390,7 @@ int plan_l2_windows(const HostHam &hh, const std::vector<int> &pi, const std::ve
       std::stable_sort(prs.begin(), prs.end(), [&](int a, int b) {
         if (cls(a) != cls(b)) return cls(a) < cls(b);
         if (cls(a) == 1) return pj[a] < pj[b];
-        if (cls(a) == 2 && pj[a] != pj[b]) return pj[a] < pj[b];
-        return cls(a) == 2 && pi[a] < pi[b];
+        return false;
       });
       for (int p : prs) {
         plan.plist.push_back(make_int4(p, pi[p], pj[p], 0));
