@@ -2292,8 +2292,10 @@ static size_t hv_tile_win_smem(const HamGeom &g, const WinPass &W) {
 
 // Threads per tile-window block: 256 G (G groups of rows on one LDS tile).
 // want = 1, 2 or 4 (the tuned choice), else 2: the tile's LDS allows two blocks per
-// CU at complex128, so a second group doubles the resident waves.  At complex64
-// four 256-thread blocks fit and G = 1 is faster once there are four tiles per CU.
+// CU at complex128, so a second group doubles the resident waves (2^20 rows x 3, all pairs
+// coupled: 771, 677, 737 us with 1, 2, 4).  At complex64 four 256-thread blocks fit, and
+// G = 1 is as fast once there are four tiles per CU and column (2^16 rows x 3: 55 us with
+// 1, 43 with 2; 2^18 x 3 92 and 81; 2^20 x 3 337 and 340).
 static int tile_win_groups(int want, bool f32, uint32_t dim) {
   if (want == 1 || want == 2 || want == 4) return want;
   return f32 && dim >= (1u << 21) ? 1 : 2;
