@@ -203,6 +203,30 @@ static std::vector<Cx<R>> plist_coefs(const HostHam &hh, const std::vector<int> 
   return c;
 }
 
+// The half sweep's pair lists of a plan, laid out for the device in the plan's precision:
+// group heads, outer sites' masks, both lists' coefficients, the pair list and its coefficients.
+template <typename R>
+static void pack_half(const HostHam &hh, const std::vector<int> &perm, WinPlan &plan) {
+  HalfTables &H = plan.half;
+  H = HalfTables();
+  if (plan.passes.empty()) return;
+  const HalfLists P = plan_half(plist_coefs<double>(hh, perm, plan.plist), plan);
+  Blob b;
+  auto add_cx = [&](const std::vector<Cx<double>> &x) {
+    std::vector<Cx<R>> y;
+    for (const Cx<double> &c : x) y.push_back(Cx<R>{(R)c.re, (R)c.im});
+    return b.add(y.data(), y.size() * sizeof(Cx<R>));
+  };
+  H.at[0] = b.add(P.grp.data(), P.grp.size() * sizeof(uint32_t));
+  H.at[1] = b.add(P.msk.data(), P.msk.size() * sizeof(uint32_t));
+  H.at[2] = add_cx(P.gco);
+  H.at[3] = add_cx(P.mco);
+  H.at[4] = b.add(P.plist.data(), P.plist.size() * sizeof(int4));
+  const std::vector<Cx<R>> pc = plist_coefs<R>(hh, perm, P.plist);
+  H.at[5] = b.add(pc.data(), pc.size() * sizeof(Cx<R>));
+  H.packed = std::move(b.bytes);
+}
+
 template <typename R>
 static DevTables<R> resolve(const TableOffsets<R> &o, unsigned char *base) {
   DevTables<R> t;
@@ -386,11 +410,12 @@ int upload_tables(const HostHam &hh, DevHam &dh, std::string &err) {
       WinPlan &tw = dh.twc[0][f - 1];
       tw = WinPlan();
       if (hh.spin_half && n > kTileBits && (uint64_t)hh.dim << f >= kHalfColumnsRows) plan_columns(hh, spi, spj, f, tw);
-      if (!tw.passes.empty()) plan_half(plist_coefs<double>(hh, perm, tw.plist), tw);
       dh.twc[1][f - 1] = tw;
+      pack_half<double>(hh, perm, dh.twc[0][f - 1]);
+      pack_half<float>(hh, perm, dh.twc[1][f - 1]);
     }
-    for (WinPlan *tw : {&dh.tw64, &dh.tw32})
-      if (!tw->passes.empty()) plan_half(plist_coefs<double>(hh, perm, tw->plist), *tw);
+    pack_half<double>(hh, perm, dh.tw64);
+    pack_half<float>(hh, perm, dh.tw32);
     dh.plan_valid = true;
     dh.plan_smask = smask;
     dh.plan_wb = wb;
@@ -420,33 +445,19 @@ int upload_tables(const HostHam &hh, DevHam &dh, std::string &err) {
   const size_t off_c32 = b.add(tc32.data(), tc32.size() * sizeof(Cx<float>));
   // the half sweep's tables; the diagonal over a tile's sites is field dependent
   struct HalfOff {
-    WinPlan *pl;
-    bool f32;
-    size_t off[7];
+    HalfTables *tab;
+    size_t lists, diag;
   };
   std::vector<HalfOff> halves;
   for (int f = 0; f < 5; f++) {
-    const std::vector<double> td = (f ? dh.twc[0][f - 1] : dh.tw64).passes.empty() ? std::vector<double>() : half_tile_diagonal(hh, f);
-    if (td.empty()) continue;
+    if ((f ? dh.twc[0][f - 1] : dh.tw64).passes.empty()) continue;
+    const std::vector<double> td = half_tile_diagonal(hh, f);
     const std::vector<float> td32(td.begin(), td.end());
     for (int q = 0; q < 2; q++) {
-      WinPlan &tw = f ? dh.twc[q][f - 1] : q ? dh.tw32 : dh.tw64;
-      const HalfTables &H = tw.half;
-      HalfOff h{&tw, q != 0, {}};
-      auto add_cx = [&](const std::vector<Cx<double>> &x) {
-        if (!q) return b.add(x.data(), x.size() * sizeof(Cx<double>));
-        std::vector<Cx<float>> y;
-        for (const Cx<double> &c : x) y.push_back(Cx<float>{(float)c.re, (float)c.im});
-        return b.add(y.data(), y.size() * sizeof(Cx<float>));
-      };
-      h.off[0] = b.add(H.grp.data(), H.grp.size() * sizeof(uint32_t));
-      h.off[1] = b.add(H.msk.data(), H.msk.size() * sizeof(uint32_t));
-      h.off[2] = add_cx(H.gco);
-      h.off[3] = add_cx(H.mco);
-      h.off[4] = q ? b.add(td32.data(), td32.size() * sizeof(float)) : b.add(td.data(), td.size() * sizeof(double));
-      h.off[5] = b.add(H.plist.data(), H.plist.size() * sizeof(int4));
-      h.off[6] = add_cx(plist_coefs<double>(hh, perm, H.plist));
-      halves.push_back(h);
+      HalfTables &H = (f ? dh.twc[q][f - 1] : q ? dh.tw32 : dh.tw64).half;
+      const size_t lists = b.add(H.packed.data(), H.packed.size());
+      halves.push_back({&H, lists, q ? b.add(td32.data(), td32.size() * sizeof(float))
+                                     : b.add(td.data(), td.size() * sizeof(double))});
     }
   }
   // single-pass tile plans (64 KB tiles); field dependent (single flips,
@@ -529,14 +540,15 @@ int upload_tables(const HostHam &hh, DevHam &dh, std::string &err) {
   dh.tw32.d_plist = dh.tw32.plist.empty() ? nullptr : reinterpret_cast<const int4 *>(base + off_t32);
   dh.tw64.half.d_grp = dh.tw32.half.d_grp = nullptr;
   for (const HalfOff &h : halves) {
-    HalfTables &H = h.pl->half;
-    H.d_grp = reinterpret_cast<const uint32_t *>(base + h.off[0]);
-    H.d_msk = reinterpret_cast<const uint32_t *>(base + h.off[1]);
-    H.d_gco = base + h.off[2];
-    H.d_mco = base + h.off[3];
-    H.d_tdiag = base + h.off[4];
-    H.d_plist = reinterpret_cast<const int4 *>(base + h.off[5]);
-    H.d_pcoef = base + h.off[6];
+    HalfTables &H = *h.tab;
+    const unsigned char *at = base + h.lists;
+    H.d_grp = reinterpret_cast<const uint32_t *>(at + H.at[0]);
+    H.d_msk = reinterpret_cast<const uint32_t *>(at + H.at[1]);
+    H.d_gco = at + H.at[2];
+    H.d_mco = at + H.at[3];
+    H.d_plist = reinterpret_cast<const int4 *>(at + H.at[4]);
+    H.d_pcoef = at + H.at[5];
+    H.d_tdiag = base + h.diag;
   }
   dh.tw64.d_pcoef = dh.tw64.plist.empty() ? nullptr : base + off_c64;
   dh.tw32.d_pcoef = dh.tw32.plist.empty() ? nullptr : base + off_c32;

@@ -226,19 +226,25 @@ struct WinPass {
 // Rows times columns from which several columns take the half sweep by default.
 constexpr uint64_t kHalfColumnsRows = 1ull << 19;
 
-// Tables of the half sweep (half_sweep.hip) for a tile plan.
-struct HalfTables {
+// Pair lists of the half sweep (half_sweep.hip) for a tile plan.
+struct HalfLists {
   std::vector<uint32_t> grp;      // member mask | (lane site + 1, or 0) << 3; at most 19 per pass
   std::vector<Cx<double>> gco;    // [group][member][4]
   std::vector<uint32_t> msk;      // [outer site of a pass]: tile sites coupled to it
   std::vector<Cx<double>> mco;    // [outer site of a pass][its bit][tile site][the site's bit]
   std::vector<int4> plist;        // the plan's list, a pass's pairs of two outer sites by (j, i)
-  const uint32_t *d_grp = nullptr;  // device copies (inside the handle's table block)
+};
+
+// The same, laid out for the device, and its copy inside the handle's table block.
+struct HalfTables {
+  std::vector<unsigned char> packed;
+  size_t at[6] = {};              // of grp, msk, gco, mco, plist and the pairs' coefficients
+  const uint32_t *d_grp = nullptr;
   const uint32_t *d_msk = nullptr;
   const void *d_gco = nullptr, *d_mco = nullptr;  // in the plan's precision
-  const void *d_tdiag = nullptr;                  // [2048 / columns] diagonal over the tile's sites
   const int4 *d_plist = nullptr;
-  const void *d_pcoef = nullptr;  // the pairs' coefficients in the list's order
+  const void *d_pcoef = nullptr;
+  const void *d_tdiag = nullptr;                  // [2048 / columns] diagonal over the tile's sites
 };
 
 struct WinPlan {
@@ -254,8 +260,8 @@ struct WinPlan {
   const void *d_pcoef = nullptr;
   HalfTables half;  // tile plans
 };
-// Fills plan.half and the passes' records of it; pcoef: the coefficients in plist order.
-void plan_half(const std::vector<Cx<double>> &pcoef, WinPlan &plan);
+// The pair lists, and the passes' records of them; pcoef: the coefficients in plist order.
+HalfLists plan_half(const std::vector<Cx<double>> &pcoef, WinPlan &plan);
 // Diagonal over the sites of a tile of 2^f columns.
 std::vector<double> half_tile_diagonal(const HostHam &hh, int f);
 // The half sweep's plan for 2^f columns (f = 1 to 4).

@@ -554,12 +554,8 @@ int layout_base(int L) { return L == 0 ? 8 : L == 1 ? 5 : L == 2 ? 2 : 0; }
 // The in-tile pairs of every pass as groups (layout of the higher site j; the lower
 // site i when it is not a register bit of that layout), and the mixed pairs by outer
 // site; pcoef: four coefficients per list entry, by the row bits (i, j).
-void plan_half(const std::vector<Cx<double>> &pcoef, WinPlan &plan) {
-  HalfTables &H = plan.half;
-  H.grp.clear();
-  H.gco.clear();
-  H.msk.clear();
-  H.mco.clear();
+HalfLists plan_half(const std::vector<Cx<double>> &pcoef, WinPlan &plan) {
+  HalfLists H;
   // (by j, then i, the tiles that an XCD works on share more partners: 2^22 rows, all pairs
   // coupled, complex128 399 us against 539 by i, then j; the tile kernel of the other column
   // counts keeps that order: 2^20 rows x 3 675 us, 853 by j, then i)
@@ -610,6 +606,7 @@ void plan_half(const std::vector<Cx<double>> &pcoef, WinPlan &plan) {
       H.mco.insert(H.mco.end(), c, c + 4 * kTileBits);
     }
   }
+  return H;
 }
 
 // Doubled site by site: raising site k adds its own difference and the z-field g of the
