@@ -512,7 +512,7 @@ __global__ __launch_bounds__(kBlock, sizeof(R) == 8 ? 2 : 3) void hv_half_sweep(
 template <typename R, bool COLS>
 int launch_r(const HamGeom &g, const DevTables<R> &tb, const WinPlan &plan, int f, const HvParams &P, int cap,
              unsigned *last_gx, hipStream_t s) {
-  static std::atomic<size_t> granted{0};  // per instantiation: largest dynamic LDS size requested so far
+  static std::atomic<uint64_t> granted{0};
   const HalfTables &H = plan.half;
   if (!H.d_plist || !H.d_pcoef || !H.d_grp || plan.passes.empty()) return FTLM_EINVAL;
   // the blocks that are resident, but for a single pass of complex128 (2^22 rows: complex64
@@ -526,11 +526,8 @@ int launch_r(const HamGeom &g, const DevTables<R> &tb, const WinPlan &plan, int 
     HvParams Pp = P;
     if (!W.last) Pp.lanczos = 0;
     const size_t sm = HalfLds<R>(g.n + f, W.hg[4] - W.hg[0]).total;
-    if (sm > granted.load()) {
-      (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&hv_half_sweep<R, COLS>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
-      granted.store(sm);
-    }
+    const int rc = grant_lds(reinterpret_cast<const void *>(&hv_half_sweep<R, COLS>), 1024, sm, granted);  // (1 KB: the sums)
+    if (rc) return rc;
     hipLaunchKernelGGL((hv_half_sweep<R, COLS>), dim3(gx), dim3(kBlock), sm, s, g, tb, W, H.d_grp,
                        reinterpret_cast<const Cx<R> *>(H.d_gco), H.d_msk, reinterpret_cast<const Cx<R> *>(H.d_mco),
                        reinterpret_cast<const R *>(H.d_tdiag), H.d_plist,

@@ -5,6 +5,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
+
 #include "device_reduce.hpp"
 #include "ftlm_internal.hpp"
 
@@ -46,6 +48,24 @@ __device__ __forceinline__ void mac_real(Acc<R, KC> &a, R c, const Cx<R> *__rest
     a.re[q] = fma(c, xv.re, a.re[q]);
     a.im[q] = fma(c, xv.im, a.im[q]);
   }
+}
+
+// A launch with `dynamic` bytes of LDS beside a kernel's `fixed` ones: refused where a CU has
+// less, and granted where it is more than 64 KB.  The grant, per kernel and device (a bit of
+// `devices`), is all that the CU has, so that host threads whose systems need different
+// sizes do not take it from each other.
+inline int grant_lds(const void *kernel, size_t fixed, size_t dynamic, std::atomic<uint64_t> &devices) {
+  constexpr size_t kCu = 160 * 1024;
+  if (fixed + dynamic > kCu) return FTLM_EINVAL;
+  if (fixed + dynamic <= 64 * 1024) return FTLM_OK;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return FTLM_EHIP;
+  const uint64_t bit = 1ull << (dev & 63);
+  if (devices.load() & bit) return FTLM_OK;
+  if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kCu - fixed)) != hipSuccess)
+    return FTLM_EHIP;
+  devices.fetch_or(bit);
+  return FTLM_OK;
 }
 
 // ------------------------------------------------------------------ H*v

@@ -2197,42 +2197,41 @@ int hv_grid_blocks(const DevHam &dh, const HvLaunch &L, int *gx, int *gy, int *k
 }
 
 template <typename R, int KC, int LPR>
-static void launch_gen(const HamGeom &g, const DevTables<R> &tb, const HvParams &P, dim3 grid, hipStream_t s) {
-  const size_t sm = (size_t)GenBlob<R>(g.n, g.has_z, g.n_gpair).total;  // up to 137 KB: 31 sites, all pairs
-  static std::atomic<size_t> granted{64 * 1024};  // per instantiation: largest dynamic LDS size requested so far
-  if (sm > granted.load()) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&hv_gen<R, KC, LPR>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
-    granted.store(sm);
-  }
+static int launch_gen(const HamGeom &g, const DevTables<R> &tb, const HvParams &P, dim3 grid, hipStream_t s) {
+  // 31 sites, all pairs with s+- s^z pieces, complex128: 146,336 bytes beside the 16,384 of
+  // the sums of 8 columns per lane, of a CU's 163,840
+  const size_t sm = (size_t)GenBlob<R>(g.n, g.has_z, g.n_gpair).total;
+  static std::atomic<uint64_t> granted{0};
+  const int rc = grant_lds(reinterpret_cast<const void *>(&hv_gen<R, KC, LPR>), sizeof(double) * kBlock * KC, sm, granted);
+  if (rc) return rc;
   hipLaunchKernelGGL((hv_gen<R, KC, LPR>), grid, dim3(kBlock), sm, s, g, tb.gblob, P);
+  return FTLM_OK;
 }
 
 template <typename R, int KC>
-static void launch_hv_t(const DevHam &dh, const DevTables<R> &tb, const HvParams &P, dim3 grid, int lpr,
-                        hipStream_t s) {
+static int launch_hv_t(const DevHam &dh, const DevTables<R> &tb, const HvParams &P, dim3 grid, int lpr,
+                       hipStream_t s) {
   const HamGeom &g = dh.geom;
   if (g.spin_half && g.n >= kLowBits) {
     const UniformTabs<R> U = uniform_tabs(tb, false);
     hipLaunchKernelGGL((hv_half<R, KC>), grid, dim3(kBlock), hv_smem<R>(g), s, g, tb, U.pij, U.pzz, P);
-  } else if (lpr == 0) {
+    return FTLM_OK;
+  }
+  if (lpr == 0) {
     const UniformTabs<R> U = uniform_tabs(tb, false);
     const size_t sm = (sizeof(Cx<R>) + sizeof(R)) * 64 * (size_t)g.n;
     hipLaunchKernelGGL((hv_rows<R, KC>), grid, dim3(kBlock), sm, s, g, tb, U.pc, U.czp, U.czm, U.pij, U.pzz, P);
-  } else if (lpr == 8) {
-    launch_gen<R, KC, 8>(g, tb, P, grid, s);
-  } else if (lpr == 4) {
-    launch_gen<R, KC, 4>(g, tb, P, grid, s);
-  } else if (lpr == 2) {
-    launch_gen<R, KC, 2>(g, tb, P, grid, s);
-  } else {
-    launch_gen<R, KC, 1>(g, tb, P, grid, s);
+    return FTLM_OK;
   }
+  if (lpr == 8) return launch_gen<R, KC, 8>(g, tb, P, grid, s);
+  if (lpr == 4) return launch_gen<R, KC, 4>(g, tb, P, grid, s);
+  if (lpr == 2) return launch_gen<R, KC, 2>(g, tb, P, grid, s);
+  return launch_gen<R, KC, 1>(g, tb, P, grid, s);
 }
 
 template <typename R>
-static void launch_hv_r(const DevHam &dh, const DevTables<R> &tb, const HvParams &P, dim3 grid,
-                        int kc, int lpr, hipStream_t s) {
+static int launch_hv_r(const DevHam &dh, const DevTables<R> &tb, const HvParams &P, dim3 grid,
+                       int kc, int lpr, hipStream_t s) {
   if (use_tile(dh.geom, P.K)) {
     const size_t sm = hv_tile_smem<R>(dh.geom);
     static size_t granted = 0;  // per instantiation: largest dynamic LDS size requested so far
@@ -2242,13 +2241,13 @@ static void launch_hv_r(const DevHam &dh, const DevTables<R> &tb, const HvParams
       granted = sm;
     }
     hipLaunchKernelGGL((hv_tile<R>), grid, dim3(kBlock), sm, s, dh.geom, tb, tb.pij, tb.pc_half, tb.pzz, P);
-    return;
+    return FTLM_OK;
   }
   switch (kc) {
-    case 8: launch_hv_t<R, 8>(dh, tb, P, grid, lpr, s); break;
-    case 4: launch_hv_t<R, 4>(dh, tb, P, grid, lpr, s); break;
-    case 2: launch_hv_t<R, 2>(dh, tb, P, grid, lpr, s); break;
-    default: launch_hv_t<R, 1>(dh, tb, P, grid, lpr, s); break;
+    case 8: return launch_hv_t<R, 8>(dh, tb, P, grid, lpr, s);
+    case 4: return launch_hv_t<R, 4>(dh, tb, P, grid, lpr, s);
+    case 2: return launch_hv_t<R, 2>(dh, tb, P, grid, lpr, s);
+    default: return launch_hv_t<R, 1>(dh, tb, P, grid, lpr, s);
   }
 }
 
@@ -2488,8 +2487,8 @@ int launch_hv(const DevHam &dh, const HvLaunch &Lin, hipStream_t s) {
   } else {
     // (the blocks of hv_gen hold every column group)
     dim3 grid(gx, dh.geom.spin_half || lpr == 0 ? gy : 1);
-    if (L.precision == FTLM_C64) launch_hv_r<float>(dh, dh.t32, P, grid, kc, lpr, s);
-    else launch_hv_r<double>(dh, dh.t64, P, grid, kc, lpr, s);
+    rc = (L.precision == FTLM_C64) ? launch_hv_r<float>(dh, dh.t32, P, grid, kc, lpr, s)
+                                   : launch_hv_r<double>(dh, dh.t64, P, grid, kc, lpr, s);
     if (use_tile(dh.geom, L.K)) fin_kc = 1;
   }
   if (rc) return rc;

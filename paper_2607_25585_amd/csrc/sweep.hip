@@ -485,30 +485,27 @@ __global__ __launch_bounds__(sweep_threads(RPT), sweep_waves(sizeof(R), RPT)) vo
 }
 
 template <typename R, int RPT, bool CPLX>
-void launch_t(const SweepPass &G, const SweepTables &S, const DevTables<R> &tb, const HvParams &P, unsigned gx,
-              uint32_t chunk, hipStream_t s) {
-  static std::atomic<size_t> granted{64 * 1024};  // per instantiation: largest dynamic LDS size requested so far
+int launch_t(const SweepPass &G, const SweepTables &S, const DevTables<R> &tb, const HvParams &P, unsigned gx,
+             uint32_t chunk, hipStream_t s) {
+  static std::atomic<uint64_t> granted{0};
   const size_t sm = SweepLds<R>(G).total;
-  if (sm > granted.load()) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&hv_sweep<R, RPT, CPLX>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
-    granted.store(sm);
-  }
+  const int rc = grant_lds(reinterpret_cast<const void *>(&hv_sweep<R, RPT, CPLX>), 1024, sm, granted);  // (1 KB: the sums)
+  if (rc) return rc;
   hipLaunchKernelGGL((hv_sweep<R, RPT, CPLX>), dim3(gx), dim3(sweep_block(G)), sm, s, G, tb,
                      S.d_pij, reinterpret_cast<const Cx<R> *>(S.d_pc), reinterpret_cast<const R *>(S.d_tdiag), chunk, P);
+  return FTLM_OK;
 }
 
 template <typename R, bool CPLX>
 int launch_rpt(const SweepPass &G, const SweepTables &S, const DevTables<R> &tb, const HvParams &P, unsigned gx,
                uint32_t chunk, hipStream_t s) {
   switch (G.rtop) {
-    case 3: launch_t<R, 3, CPLX>(G, S, tb, P, gx, chunk, s); break;
-    case 4: launch_t<R, 4, CPLX>(G, S, tb, P, gx, chunk, s); break;
-    case 5: launch_t<R, 5, CPLX>(G, S, tb, P, gx, chunk, s); break;
-    case 6: launch_t<R, 6, CPLX>(G, S, tb, P, gx, chunk, s); break;
+    case 3: return launch_t<R, 3, CPLX>(G, S, tb, P, gx, chunk, s);
+    case 4: return launch_t<R, 4, CPLX>(G, S, tb, P, gx, chunk, s);
+    case 5: return launch_t<R, 5, CPLX>(G, S, tb, P, gx, chunk, s);
+    case 6: return launch_t<R, 6, CPLX>(G, S, tb, P, gx, chunk, s);
     default: return FTLM_EINVAL;
   }
-  return FTLM_OK;
 }
 
 template <typename R>

@@ -364,8 +364,9 @@ int launch_tridiag_full(int n_cols, int n_lanczos, const int *n_used, const doub
   constexpr size_t kLds = 160 * 1024 - 64;  // less the static words
   const int nbuf = full_smem(n_lanczos, 2) <= kLds ? 2 : 1;
   const size_t sm = full_smem(n_lanczos, nbuf);
+  // (the same value from every host thread, whatever its length)
   if (hipFuncSetAttribute(reinterpret_cast<const void *>(&tridiag_full_kernel),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm) != hipSuccess)
+                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds) != hipSuccess)
     return FTLM_EHIP;
   const int threads = kWave + std::min(192, (n_lanczos + kWave - 1) / kWave * kWave);
   hipLaunchKernelGGL(tridiag_full_kernel, dim3(n_cols), dim3(threads), sm, s, n_lanczos, nbuf, n_used, alpha, beta,
