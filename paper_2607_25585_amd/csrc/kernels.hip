@@ -993,7 +993,7 @@ __global__ __launch_bounds__(kBlock) void hv_gen(HamGeom g, const uint4 *__restr
 #pragma unroll
         for (int q = 0; q < KC; q++) x[u][q] = Cx<R>{0, 0};
         if (ok[u]) {
-          const Cx<R> *px = v + (size_t)(row + (uint32_t)off[u]) * P.K;
+          const Cx<R> *px = v + (size_t)(row + off[u]) * P.K;
 #pragma unroll
           for (int q = 0; q < KC; q++) x[u][q] = px[q];
         }
@@ -1012,7 +1012,8 @@ __global__ __launch_bounds__(kBlock) void hv_gen(HamGeom g, const uint4 *__restr
 #pragma unroll 1
     for (int k = s; k < n; k += LPR) {
       const int4 site = s_site[k];
-      const int dk = digit(k), rk = uni(site.y), st = uni(site.x), has = uni(site.z);
+      const int dk = digit(k), rk = uni(site.y), has = uni(site.z);
+      const uint32_t st = (uint32_t)uni(site.x);  // (twice a stride may pass 2^31)
       const Cx<R> *ho = s_hoff + k * 64 + dk;
       // the sites' z-components: the z-z coupling of k to the sites above it, and
       // the field of its s+- s^z pieces
@@ -1040,11 +1041,11 @@ __global__ __launch_bounds__(kBlock) void hv_gen(HamGeom g, const uint4 *__restr
       if (has & 2) {
         const Cx<R> c[4] = {ho[0], c1[0], c1[1], ho[48]};
         const bool ok[4] = {dk >= 2, dk >= 1, dk + 1 < rk, dk + 2 < rk};
-        const int off[4] = {-2 * st, -st, st, 2 * st};
+        const uint32_t off[4] = {0u - 2u * st, 0u - st, st, 2u * st};
         batch(c, ok, off);
       } else {
         const bool ok[2] = {dk >= 1, dk + 1 < rk};
-        const int off[2] = {-st, st};
+        const uint32_t off[2] = {0u - st, st};
         batch(c1, ok, off);
       }
     }
@@ -1053,7 +1054,7 @@ __global__ __launch_bounds__(kBlock) void hv_gen(HamGeom g, const uint4 *__restr
     for (int e = s; e < g.n_gpair; e += NB * LPR) {
       Cx<R> c[NB];
       bool ok[NB];
-      int off[NB];
+      uint32_t off[NB];
 #pragma unroll
       for (int u = 0; u < NB; u++) {
         const int eu = e + u * LPR;
@@ -1063,7 +1064,7 @@ __global__ __launch_bounds__(kBlock) void hv_gen(HamGeom g, const uint4 *__restr
         const R f = s_f[uni(G.fa) + digit(ab & 255)] * s_f[uni(G.fb) + digit(ab >> 8)];
         c[u] = Cx<R>{G.c.re * f, G.c.im * f};
         ok[u] = in && f != R(0);
-        off[u] = uni(G.off);
+        off[u] = (uint32_t)uni(G.off);
       }
       batch(c, ok, off);
     }
@@ -1196,7 +1197,7 @@ __global__ __launch_bounds__(kBlock) void hv_rows(HamGeom g, DevTables<R> tb, co
           c.re = fma(gg, fmr, c.re);
           c.im = fma(gg, fmi, c.im);
         }
-        const uint32_t partner = row + (uint32_t)(D * (int)st);
+        const uint32_t partner = row + (uint32_t)D * st;
         mac(acc, c, v + (size_t)partner * P.K);
       }
     }
@@ -1217,7 +1218,7 @@ __global__ __launch_bounds__(kBlock) void hv_rows(HamGeom g, DevTables<R> tb, co
         const bool vj = jm ? (dj <= rj - 2) : (dj >= 1);
         if (!(vi && vj)) continue;
         const R f = (im_ ? gmi : gpi) * (jm ? gmj : gpj);
-        const uint32_t partner = row + (im_ ? si : (uint32_t)(-(int)si)) + (jm ? sj : (uint32_t)(-(int)sj));
+        const uint32_t partner = row + (im_ ? si : 0u - si) + (jm ? sj : 0u - sj);
         mac(acc, Cx<R>{cq.re * f, cq.im * f}, v + (size_t)partner * P.K);
       }
     }
