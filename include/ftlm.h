@@ -220,7 +220,7 @@ int ftlm_run(const ftlm_hamiltonian *h, const ftlm_run_params *p, void *workspac
  * Each vector runs N_L Lanczos steps keeping all Krylov vectors; M is the ratio
  * sum_r <r|exp(-H/2T) O exp(-H/2T)|r> / sum_r <r|exp(-H/T)|r> with the double
  * sum of Eq. (E-2-H) over the Krylov eigenpairs, O = -sum_i g_i s_i.B_hat; ln Z,
- * E and C as ftlm_run.  Uses p->R, n_lanczos (<= 140), seed, instance, T, n_T,
+ * E and C as ftlm_run.  Uses p->R, n_lanczos (<= 141), seed, instance, T, n_T,
  * fields, n_fields, precision; columns is ignored and r_init must be NULL.
  * Workspace: (2 N_L + 1) vectors for each of the random vectors that iterate
  * together (one for dim >= 2^20 or where a second one's basis would pass 1 GiB,

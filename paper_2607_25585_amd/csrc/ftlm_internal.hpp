@@ -189,10 +189,10 @@ struct PassPlan {
 };
 
 struct HvTuning {
-  int variant = 0;   // 0 = heuristic, 1 = direct gather, 2 = windowed passes, 3 = LDS tile, 4 = L2 windows,
-                     // 5 = LDS tile over L2 windows, 6 = single-pass tiles (stream)
-  int grid_cap = 0;  // 0 = default
-  int kc = 0;        // columns per lane of the direct kernels (0 = widest dividing K)
+  int variant = 0;   // 0 = built-in choice, 1 = direct gather, 2 = windowed passes, 3 = LDS tile, 4 = L2 windows,
+                     // 5 = half sweep (or LDS tile) over L2 windows, 6 = single-pass tiles (sweep or stream)
+  int grid_cap = 0;  // 0 = the launch's own
+  int kc = 0;        // columns per lane of the direct kernels (0 = the launch's own), or the variant's bits
 };
 
 // One pass of the L2-window H*v.  The rows are walked window by window: a
@@ -316,7 +316,7 @@ struct SweepPass {
   int np, np_low, np_out;   // pairs: two lower | lower and top | mixed, by outer site | two outer
   uint32_t smask, smask2;   // sites with single flips; that move by 2
   int radix[kMaxSites];
-  uint32_t st[kMaxSites], wst[kMaxSites];  // strides in the basis / (tile sites) in the tile
+  uint32_t st[kMaxSites];   // strides in the basis (of the tile sites: in the tile as well)
   float s[kMaxSites];
   int ptop[kMaxSites];      // pair (lower site, top) or -1
   int mx[kMaxSites + 1];    // mixed pairs of outer site t + k: [mx[k], mx[k + 1])

@@ -338,7 +338,7 @@ int validate_sftlm(const ftlm_hamiltonian *h, const ftlm_run_params *p, std::str
   if (!p) { err = "params is NULL"; return FTLM_EINVAL; }
   if (p->R < 2 || (p->R & 1)) { err = "R must be even and >= 2 (time-reversed pairs)"; return FTLM_EINVAL; }
   if (p->n_lanczos < 1) { err = "n_lanczos must be >= 1"; return FTLM_ERANGE; }
-  if (tridiag_full_smem(p->n_lanczos) > 160 * 1024) { err = "n_lanczos too large for the sFTLM eigensolver (<= 140)"; return FTLM_ERANGE; }
+  if (tridiag_full_smem(p->n_lanczos) > 160 * 1024) { err = "n_lanczos too large for the sFTLM eigensolver (<= 141)"; return FTLM_ERANGE; }
   if (p->n_T < 1 || !p->T) { err = "a temperature grid is required"; return FTLM_EINVAL; }
   for (int i = 0; i < p->n_T; i++)
     if (!(p->T[i] > 0) || !std::isfinite(p->T[i])) { err = "temperatures must be positive"; return FTLM_EINVAL; }

@@ -159,7 +159,7 @@ __global__ __launch_bounds__(sweep_threads(RPT), sweep_waves(sizeof(R), RPT)) vo
   // offset of its rows within the basis; threads past Q repeat the last one's reads
   const bool act = (uint32_t)tid < Q;
   const uint32_t q = act ? (uint32_t)tid : Q - 1;
-  uint32_t dig = 0, goff = 0;  // (goff in bytes: below 4 GB, the plan checks)
+  uint32_t dig = 0, goff = 0;  // (goff in bytes, within the tile: its sites are the lowest digits)
   {
     uint32_t rem = q;
     for (int i = 0; i < top; i++) {
@@ -314,7 +314,7 @@ __global__ __launch_bounds__(sweep_threads(RPT), sweep_waves(sizeof(R), RPT)) vo
       const int pt = G.ptop[i];  // the pair (i, top), or -1
       const bool sg = (G.smask >> i) & 1u;
       if (!sg && pt < 0) continue;
-      const int di = digit(i), rd = G.radix[i], ws = (int)G.wst[i];
+      const int di = digit(i), rd = G.radix[i], ws = (int)G.st[i];
       const int nzt = pt < 0 ? 0 : uni(s_pij[pt].z);
 #pragma unroll
       for (int up = 0; up < 2; up++) {
@@ -353,7 +353,7 @@ __global__ __launch_bounds__(sweep_threads(RPT), sweep_waves(sizeof(R), RPT)) vo
     for (int p = 0; p < G.np_low; p++) {
       const int4 ab = s_pij[p];
       const int a = uni(ab.x), b = uni(ab.y), nz = uni(ab.z);
-      const int da = digit(a), db = digit(b), wa = (int)G.wst[a], wb = (int)G.wst[b];
+      const int da = digit(a), db = digit(b), wa = (int)G.st[a], wb = (int)G.st[b];
 #pragma unroll
       for (int qt = 0; qt < 4; qt++) {
         if (!((nz >> qt) & 1)) continue;
@@ -421,7 +421,7 @@ __global__ __launch_bounds__(sweep_threads(RPT), sweep_waves(sizeof(R), RPT)) vo
             const R fa = (au ? s_gm : s_gp)[a * 16 + da];
             const Cx<R> c = unic(s_pc[4 * p + 2 * au + up]);
             Cx<R> y[RPT];
-            const int ws = (int)G.wst[a];
+            const int ws = (int)G.st[a];
             lds_rows(y, fa != R(0) ? (int)q + (au ? ws : -ws) : (int)q);
             const R f = fa * fk;
             const Cx<R> cc{c.re * f, c.im * f};
@@ -555,7 +555,6 @@ void plan_sweep(const HostHam &hh, size_t es, uint32_t tile_rows, SweepPlan &pl)
   for (int k = 0; k < n; k++) {
     G.radix[k] = hh.radix[k];
     G.st[k] = hh.stride[k];
-    G.wst[k] = k == 0 ? 1u : G.wst[k - 1] * (uint32_t)G.radix[k - 1];
     G.s[k] = 0.5f * (float)hh.two_s[k];
     if (site_has_singles(hh, k)) G.smask |= 1u << k;
     for (int d = 0; d + 2 < hh.radix[k]; d++) {
@@ -610,7 +609,7 @@ void plan_sweep(const HostHam &hh, size_t es, uint32_t tile_rows, SweepPlan &pl)
   pl.cplx = cplx;
   // diagonal over the tile sites, per tile row, built site by site: a value d of site k adds
   // its own element and its moment times the z-field of the sites below (every row anew
-  // took 87 us of each field change of the centred cube, and this 5)
+  // took 87 us of each field change of the centred cube in either precision, and this 5)
   pl.tdiag.assign(T, 0.0);
   std::vector<double> zf(T);
   uint32_t below = 1;  // rows of the sites below k
@@ -629,7 +628,7 @@ void plan_sweep(const HostHam &hh, size_t es, uint32_t tile_rows, SweepPlan &pl)
     }
     below *= (uint32_t)G.radix[k];
   }
-  // a thread's byte offset in its tile has 32 bits; the block's tables and tile share the LDS
+  // the block's tables and tile share the LDS
   const size_t lds = es == 16 ? SweepLds<double>(G).total : SweepLds<float>(G).total;
   if (lds > 159 * 1024) return;  // 1 KB for static LDS
   pl.pass = G;
