@@ -1107,8 +1107,7 @@ __global__ __launch_bounds__(kBlock) void hv_gen(HamGeom g, const uint4 *__restr
 // list comes by scalar loads, so that a row pays for its valid moves alone; what bounds
 // it is one partner after the other, which the rows of a large vector hide.  hv_gen
 // works through every move of every lane: on sites of two values, of whose pair moves one
-// in four is valid, that costs more than it hides (17 sites, 1.97e5 rows, all pairs with
-// s+- s^z pieces, complex128: one column 168 us here, 234 there; 4 columns 247 and 509).
+// in four is valid, that costs more than it hides (the figures stand at rows_pay).
 template <typename R, int KC>
 __global__ __launch_bounds__(kBlock) void hv_rows(HamGeom g, DevTables<R> tb, const Cx<R> *__restrict__ pcg,
                                                  const Cx<R> *__restrict__ czp, const Cx<R> *__restrict__ czm,
@@ -2137,35 +2136,72 @@ struct Direct {
   int kc, lpr;
 };
 
-// General radices.  hv_gen takes 32 bytes of columns per lane (the coefficient work is
-// shared by the group, the loads stay contiguous; 10 s=1 sites, 20 columns, complex64:
-// 89, 48, 41 us at 1, 2, 4; complex128: 103, 67, 67) and shares a row's terms between
-// lanes where rows and groups leave the chip idle.  Measured (us, K columns in groups of kc):
+// General radices: is the lane-per-row kernel the faster one?  hv_gen works through every
+// move of every row, with the partners' loads in flight together; hv_rows takes one valid
+// move after the other.  Below some 10^5 rows hv_gen wins by far (59,049 rows of 10 s=1
+// sites, all pairs with s+- s^z pieces, complex128, one column: 31 us, hv_rows 59); above,
+// the rows hide hv_rows' latency, and what each does too much decides (us, hv_rows / hv_gen):
+// - mostly sites of two values, where one pair move in four is valid.  17 sites, 196,608
+//   rows, complex128, 1, 4, 8, 16 columns:
+//     chain                             25 / 36     42 / 67     130 / 121    203 / 236
+//     all pairs, no s+- s^z pieces      111 / 92    148 / 194   404 / 397    613 / 753
+//     all pairs with them               165 / 235   249 / 459   748 / 910    1129 / 1803
+//   complex64, 1, 4, 8, 20 columns:
+//     chain                             24 / 32     31 / 36     42 / 64      261 / 154
+//     all pairs with them               158 / 154   185 / 194   238 / 375    1673 / 997
+//   16 sites, 98,304 rows, complex64, one column: chain 21 / 18, all pairs 82 / 44
+// - other sites without single flips (which hv_rows works through all the same): hv_gen
+//   always (7 s=5/2 sites, nn + nnn, 2 columns, complex128: 37 / 30; 11 s=1, 8 columns: 184 / 79)
+// - other sites with them: hv_rows for one column (9 s=3/2 ring sites 20 / 23 to 29, 12 s=1
+//   sites 55 / 60; but 9 s=2 sites, 1.95e6 rows, 153 / 141), for two of few pairs (9 s=3/2
+//   ring sites, complex64, 19.3 / 21.7) and for 2 or 4 of large vectors with s+- s^z pieces
+//   (13 s=1 sites, 4 columns, complex128: 1623 / 1926; but 2 of complex64 768 / 662); hv_gen
+//   where its lanes' column groups read contiguously what hv_rows reads apart (11 s=1 sites,
+//   all pairs, complex128, 8 columns 482 / 272; 20 columns, with s+- s^z pieces, 1385 / 771)
+static bool rows_pay(const HamGeom &g, int K, int kc, bool f32, double values) {
+  const uint64_t rows = g.dim, items = rows * (uint64_t)(K / kc);
+  const bool few = g.npair < 3 * g.n, odd = kc == 1 && K > 1;
+  if (values < 2.6) {
+    if (odd) return items >= 98304 && (K == 3 ? few || (g.has_z && rows >= 98304) : f32 && few);
+    if (K <= 8) return rows >= 98304 && items >= 131072 && (few || g.has_z || K == (f32 ? 8 : 4));
+    return !f32 && rows >= (few || g.has_z ? 98304u : 131072u);
+  }
+  if (!g.single_mask) return false;
+  const bool mid = rows >= 131072 && rows < (1u << 19);
+  if (K == 1) return !g.has_z && rows >= 131072 && (mid || values < 3.5);
+  if (K == 2 && few && mid) return true;
+  if (K == 3) return few && values < 4.5 && rows >= 65536 && rows < 131072;
+  if (f32 || values >= 3.5) return false;
+  return (K == 4 && few && mid) || ((K == 2 || K == 4) && g.has_z && rows >= (1u << 20));
+}
+
+// hv_gen takes 32 bytes of columns per lane (the coefficient work is shared by the group,
+// the loads stay contiguous; 10 s=1 sites, 20 columns, complex64: 89, 48, 41 us at 1, 2, 4;
+// complex128: 103, 67, 67) and shares a row's terms between lanes where rows and groups
+// leave the chip idle.  Measured (us, K columns in groups of kc):
 //   rows x groups       1 lane   2      4      8
 //   729                 19.3     12.0   8.9    8.2   (6 s=1 sites, all pairs; K = 1)
 //   32,805              14.5     9.8    8.7    11.4  (8 s=1 sites, K = 20, complex64)
 //   65,610              15.1     12.6   16.0   17.3  (8 s=1 sites, K = 20, complex128)
+//   196,608             18.5     20.7   22.6   31.9  (8 s=3/2 ring sites, K = 3, by one, complex128)
+//   262,144             22.9     28.8   37.2   47.2  (9 s=3/2 ring sites, K = 1, complex128)
 //   295,245             41.4     38.5   52.7   65.3  (10 s=1 sites, K = 20, complex64)
+//   390,625             42.0     39.4                (8 s=2 ring sites, K = 4, complex64)
 //   655,360             60.6     64.2   89.6   120.8 (8 s=3/2 sites, K = 20, complex128)
-// (columns one by one, as 3 are, leave off sharing sooner: 65,536 rows x 3, complex128,
-// 8 s=3/2 ring sites: 18.4 us with 1 lane, 20.7 with 2.)
-// From 98,304 rows the lane-per-row kernel is at least as fast for the columns that one of
-// its lanes takes (1, 2, 4 or 8: a wave's loads are contiguous; 262,144 rows, 9 s=3/2 ring
-// sites, complex128: one column 20.6 us against 28.0), and from as many rows x groups
-// for any columns where the mean number of values per site is below 2.6, so that most pair
-// moves are not valid (98,304 rows, 16 sites, 20 columns, all pairs: 745 us against 1102).
-// Below, and for other columns, hv_gen is: 59,049 rows of 10 s=1 sites, all pairs, 59 us
-// against 31; 177,147 rows of 11, 20 columns, 1378 and 753.
+//   147,456             23.1     19.3                (13 sites, K = 3, by one, all pairs, complex64)
+// so that two lanes share a row up to 131,072, up to 163,840 complex64 columns one by one,
+// up to 196,608 with s+- s^z pieces, whose fields are work that lanes share, and up to
+// 393,216 where a row has few sites for its size or complex64 columns are many.
 static Direct direct_launch(const HamGeom &g, int K, int want, int precision) {
   if (g.spin_half) return Direct{pick_kc(K, want > 0 ? want : 8), 1};
-  constexpr uint64_t kRowsFrom = 98304;
-  const int kr = pick_kc(K, want > 0 ? want : 8);
-  const int kc = pick_kc(K, want > 0 ? want : precision == FTLM_C64 ? 4 : 2);
-  const int ncg = K / kc;
+  const bool f32 = precision == FTLM_C64;
+  const double values = std::exp2(std::log2((double)g.dim) / g.n);  // per site, geometric mean
+  const int kc = pick_kc(K, want > 0 ? want : f32 ? 4 : 2), ncg = K / kc;
+  if (rows_pay(g, K, kc, f32, values)) return Direct{pick_kc(K, want > 0 ? want : 8), 0};
   const uint64_t items = (uint64_t)g.dim * ncg;
-  if (kr == K && g.dim >= kRowsFrom) return Direct{kr, 0};
-  if (items >= kRowsFrom && std::log2((double)g.dim) < std::log2(2.6) * g.n) return Direct{kr, 0};
-  const uint64_t two = kc == 1 && K > 1 ? 98304 : 393216;
+  const bool odd = kc == 1 && K > 1;
+  const bool far = !odd && (values >= 5.5 || (f32 && (K > 8 || (K > 1 && values >= 4.9))));
+  const uint64_t two = far ? 393216 : g.has_z ? 196608 : odd && f32 ? 163840 : 131072;
   int lpr = items <= 16384 ? 8 : items <= 49152 ? 4 : items <= two ? 2 : 1;
   while (lpr * ncg > kBlock) lpr /= 2;
   return Direct{kc, lpr};
