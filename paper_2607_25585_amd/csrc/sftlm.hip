@@ -136,21 +136,37 @@ __global__ __launch_bounds__(256) void gram_kernel(const Cx<R> *__restrict__ X, 
       }
 }
 
-// Sums the partials over the splits in split order; the blocks below the diagonal
-// are mirrored.
-__global__ void gram_reduce_kernel(const double *__restrict__ part, int nsplit, int nl, int K,
-                                   double *__restrict__ ok) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x, c = blockIdx.y;
-  if (idx >= nl * nl) return;
-  int a = idx / nl, b = idx % nl;
-  if (a / kGB > b / kGB) {
-    const int t = a;
-    a = b;
-    b = t;
-  }
+// Sums the partials over the splits in a fixed order; the blocks below the diagonal are
+// mirrored.  PH threads share an element's splits (one after the other, each of its PHth
+// splits, then the threads in order): with few columns and steps there are thousands of
+// splits of few elements, and one thread's chain of loads took longer than the products
+// (2^20 rows, 30 steps, one column: 4096 splits of 900 elements).
+template <int PH>
+__global__ __launch_bounds__(256) void gram_reduce_kernel(const double *__restrict__ part, int nsplit, int nl, int K,
+                                                          double *__restrict__ ok) {
+  constexpr int NE = 256 / PH;  // elements per block
+  __shared__ double sh[PH][NE];
+  const int el = threadIdx.x % NE, ph = threadIdx.x / NE;
+  const int idx = blockIdx.x * NE + el, c = blockIdx.y;
   double r = 0;
-  for (int s = 0; s < nsplit; s++) r += part[((size_t)s * K + c) * nl * nl + (size_t)a * nl + b];
-  ok[(size_t)c * nl * nl + idx] = r;
+  if (idx < nl * nl) {
+    int a = idx / nl, b = idx % nl;
+    if (a / kGB > b / kGB) {
+      const int t = a;
+      a = b;
+      b = t;
+    }
+#pragma unroll 4
+    for (int s = ph; s < nsplit; s += PH) r += part[((size_t)s * K + c) * nl * nl + (size_t)a * nl + b];
+  }
+  if (PH > 1) {
+    sh[ph][el] = r;
+    __syncthreads();
+    if (ph > 0) return;
+    r = 0;
+    for (int p = 0; p < PH; p++) r += sh[p][el];
+  }
+  if (idx < nl * nl) ok[(size_t)c * nl * nl + idx] = r;
 }
 
 // Lowest Ritz value over a field's vectors (the QL output is unsorted).
@@ -508,8 +524,13 @@ int ftlm_run_sftlm(const ftlm_hamiltonian *hc, const ftlm_run_params *p, void *w
         hipLaunchKernelGGL(gram_kernel<double>, gg, dim3(256), 0, s, reinterpret_cast<const Cx<double> *>(V),
                            reinterpret_cast<const Cx<double> *>(Wb), K, NL, (uint32_t)pl.dim, chunk, pl.nsplit, sx, Kp,
                            gpart);
-      hipLaunchKernelGGL(gram_reduce_kernel, dim3((NL * NL + 255) / 256, K), dim3(256), 0, s, gpart, pl.nsplit, NL, K,
-                         at2<double>(ws, pl.OK) + (size_t)r0 * NL * NL);
+      double *okr = at2<double>(ws, pl.OK) + (size_t)r0 * NL * NL;
+      if (pl.nsplit >= 64)
+        hipLaunchKernelGGL(gram_reduce_kernel<16>, dim3((NL * NL + 15) / 16, K), dim3(256), 0, s, gpart, pl.nsplit, NL,
+                           K, okr);
+      else
+        hipLaunchKernelGGL(gram_reduce_kernel<1>, dim3((NL * NL + 255) / 256, K), dim3(256), 0, s, gpart, pl.nsplit, NL,
+                           K, okr);
       if (hipGetLastError() != hipSuccess) return fail(FTLM_EHIP, "sFTLM kernel launch failed");
       if (hipMemcpyAsync(nused_f + r0, at2<int>(ws, pl.nused), sizeof(int) * K, hipMemcpyDeviceToDevice, s) != hipSuccess)
         return fail(FTLM_EHIP, "copy of n_used failed");
