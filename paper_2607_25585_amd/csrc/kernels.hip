@@ -2138,41 +2138,69 @@ struct Direct {
 
 // General radices: is the lane-per-row kernel the faster one?  hv_gen works through every
 // move of every row, with the partners' loads in flight together; hv_rows takes one valid
-// move after the other.  Below some 10^5 rows hv_gen wins by far (59,049 rows of 10 s=1
-// sites, all pairs with s+- s^z pieces, complex128, one column: 31 us, hv_rows 59); above,
-// the rows hide hv_rows' latency, and what each does too much decides (us, hv_rows / hv_gen):
-// - mostly sites of two values, where one pair move in four is valid.  17 sites, 196,608
-//   rows, complex128, 1, 4, 8, 16 columns:
-//     chain                             25 / 36     42 / 67     130 / 121    203 / 236
-//     all pairs, no s+- s^z pieces      111 / 92    148 / 194   404 / 397    613 / 753
-//     all pairs with them               165 / 235   249 / 459   748 / 910    1129 / 1803
-//   complex64, 1, 4, 8, 20 columns:
-//     chain                             24 / 32     31 / 36     42 / 64      261 / 154
-//     all pairs with them               158 / 154   185 / 194   238 / 375    1673 / 997
-//   16 sites, 98,304 rows, complex64, one column: chain 21 / 18, all pairs 82 / 44
-// - other sites without single flips (which hv_rows works through all the same): hv_gen
-//   always (7 s=5/2 sites, nn + nnn, 2 columns, complex128: 37 / 30; 11 s=1, 8 columns: 184 / 79)
-// - other sites with them: hv_rows for one column (9 s=3/2 ring sites 20 / 23 to 29, 12 s=1
-//   sites 55 / 60; but 9 s=2 sites, 1.95e6 rows, 153 / 141), for two of few pairs (9 s=3/2
-//   ring sites, complex64, 19.3 / 21.7) and for 2 or 4 of large vectors with s+- s^z pieces
-//   (13 s=1 sites, 4 columns, complex128: 1623 / 1926; but 2 of complex64 768 / 662); hv_gen
-//   where its lanes' column groups read contiguously what hv_rows reads apart (11 s=1 sites,
-//   all pairs, complex128, 8 columns 482 / 272; 20 columns, with s+- s^z pieces, 1385 / 771)
-static bool rows_pay(const HamGeom &g, int K, int kc, bool f32, double values) {
-  const uint64_t rows = g.dim, items = rows * (uint64_t)(K / kc);
-  const bool few = g.npair < 3 * g.n, odd = kc == 1 && K > 1;
-  if (values < 2.6) {
-    if (odd) return items >= 98304 && (K == 3 ? few || (g.has_z && rows >= 98304) : f32 && few);
-    if (K <= 8) return rows >= 98304 && items >= 131072 && (few || g.has_z || K == (f32 ? 8 : 4));
-    return !f32 && rows >= (few || g.has_z ? 98304u : 131072u);
+// move after the other.  Below some 10^5 rows x columns hv_gen wins by far (59,049 rows of
+// 10 s=1 sites, all pairs with s+- s^z pieces, complex128, one column: 31 us, hv_rows 59);
+// above, the rows hide hv_rows' latency, and what each does too much decides.
+//
+// Mostly sites of two values: one pair move in four is valid.  Where hv_rows begins to
+// win, and ceases to where more and more columns are read apart, was measured over rows x
+// columns in units of 2^16, by columns; e.g. hv_rows / hv_gen (us) of 17 sites, 196,608 rows:
+//                                   1 column     4            8            16, 20
+//   complex128  chain               25 / 36      42 / 67      130 / 121    203 / 236
+//               all, s+- s^z pieces 165 / 235    249 / 459    748 / 910    1129 / 1803
+//               all, without them   111 / 92     148 / 194    404 / 397    613 / 753
+//   complex64   chain               24 / 32      31 / 36      42 / 64      261 / 154
+//               all, s+- s^z pieces 158 / 154    185 / 194    238 / 375    1673 / 997
+// and of 15 sites, 49,152 rows, complex128, chain: 1 column 18 / 14, 5 28 / 37, 12 39 / 55.
+struct Span {
+  uint16_t from, to;  // 0, 0: never
+};
+static bool rows_pay_narrow(const HamGeom &g, int K, bool f32, double values) {
+  constexpr uint16_t inf = 0xffff;
+  // columns: 1, 2, 3, 4, 6, 8, then other odd numbers, and other multiples of 2, 4 and 8
+  static constexpr Span few[2][10] = {
+      {{2, inf}, {4, inf}, {2, inf}, {4, inf}, {3, 12}, {0, 0}, {2, 6}, {2, 6}, {4, inf}, {32, inf}},
+      {{2, inf}, {4, inf}, {2, inf}, {8, inf}, {4, inf}, {8, inf}, {2, inf}, {4, 8}, {8, 16}, {0, 0}}};
+  static constexpr Span zed[2][10] = {
+      {{2, inf}, {4, inf}, {4, inf}, {4, inf}, {8, inf}, {8, inf}, {2, 6}, {4, 6}, {5, inf}, {16, inf}},
+      {{8, inf}, {16, inf}, {4, inf}, {8, inf}, {8, inf}, {16, inf}, {8, inf}, {0, 0}, {0, 0}, {0, 0}}};
+  static constexpr Span all[2][10] = {
+      {{0, 0}, {0, 0}, {0, 0}, {8, inf}, {0, 0}, {0, 0}, {0, 0}, {0, 0}, {8, inf}, {32, inf}},
+      {{0, 0}, {0, 0}, {0, 0}, {0, 0}, {0, 0}, {16, inf}, {0, 0}, {0, 0}, {0, 0}, {0, 0}}};
+  const int c = K <= 4 ? K - 1 : K == 6 ? 4 : K == 8 ? 5 : K & 1 ? 6 : K & 2 ? 7 : K & 4 ? 8 : 9;
+  const bool pairs = g.npair >= 3 * g.n;
+  Span sp = g.has_z ? zed[f32][c] : pairs ? all[f32][c] : few[f32][c];
+  if (values >= 2.2) {  // more of the moves are valid (12 sites of 2 and 3 values in turn)
+    if (!g.has_z && pairs) return false;
+    if (c < 2) sp.from *= 2;
+    else if (c == 3) sp.from = 16;
+    else if (c == 5) sp = g.has_z || f32 ? Span{32, inf} : Span{0, 0};
+    else if (c != 2 && !(f32 && !g.has_z && (c == 4 || c == 6))) return false;
   }
+  const uint64_t elems = (uint64_t)g.dim * K;
+  return sp.to && elems >= (uint64_t)sp.from << 16 && (sp.to == inf || elems < (uint64_t)sp.to << 16);
+}
+
+// Other sites.  Without single flips hv_gen always: hv_rows works through them all the same
+// (us, hv_rows / hv_gen: 7 s=5/2 sites, nn + nnn, 2 columns, complex128: 37 / 30; 11 s=1
+// sites, 8 columns: 184 / 79).  With them, hv_rows for one column (9 s=3/2 ring sites 20 /
+// 23 to 29, 12 s=1 sites 55 / 60; but 9 s=2 sites, 1.95e6 rows, 153 / 141), for two of few
+// pairs (9 s=3/2 ring sites, complex64, 19.3 / 21.7) and for 2 or 4 of large vectors with
+// s+- s^z pieces (13 s=1 sites, 4 columns, complex128: 1623 / 1926; but 2 of complex64 768 /
+// 662); hv_gen where its lanes' column groups read contiguously what hv_rows reads apart (11
+// s=1 sites, all pairs, complex128, 8 columns 482 / 272; 20 columns, with s+- s^z pieces,
+// 1385 / 771).
+static bool rows_pay(const HamGeom &g, int K, bool f32, double values) {
+  if (values < 2.6) return rows_pay_narrow(g, K, f32, values);
   if (!g.single_mask) return false;
-  const bool mid = rows >= 131072 && rows < (1u << 19);
+  const uint64_t rows = g.dim;
+  const bool few = g.npair < 3 * g.n, mid = rows >= 131072 && rows < (1u << 19);
   if (K == 1) return !g.has_z && rows >= 131072 && (mid || values < 3.5);
   if (K == 2 && few && mid) return true;
   if (K == 3) return few && values < 4.5 && rows >= 65536 && rows < 131072;
-  if (f32 || values >= 3.5) return false;
-  return (K == 4 && few && mid) || ((K == 2 || K == 4) && g.has_z && rows >= (1u << 20));
+  if (values >= 3.5) return false;
+  if (K == 4 && few && (f32 ? rows >= (1u << 19) : mid)) return true;
+  return !f32 && (K == 2 || K == 4) && g.has_z && rows >= (1u << 20);
 }
 
 // hv_gen takes 32 bytes of columns per lane (the coefficient work is shared by the group,
@@ -2197,7 +2225,7 @@ static Direct direct_launch(const HamGeom &g, int K, int want, int precision) {
   const bool f32 = precision == FTLM_C64;
   const double values = std::exp2(std::log2((double)g.dim) / g.n);  // per site, geometric mean
   const int kc = pick_kc(K, want > 0 ? want : f32 ? 4 : 2), ncg = K / kc;
-  if (rows_pay(g, K, kc, f32, values)) return Direct{pick_kc(K, want > 0 ? want : 8), 0};
+  if (rows_pay(g, K, f32, values)) return Direct{pick_kc(K, want > 0 ? want : 8), 0};
   const uint64_t items = (uint64_t)g.dim * ncg;
   const bool odd = kc == 1 && K > 1;
   const bool far = !odd && (values >= 5.5 || (f32 && (K > 8 || (K > 1 && values >= 4.9))));

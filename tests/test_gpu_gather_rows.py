@@ -38,7 +38,7 @@ def test_direct_gather_matches_oracle(name, couple):
     v = rng.standard_normal((ham.dim, 5)) + 1j * rng.standard_normal((ham.dim, 5))
     want = np.stack([ref.apply(v[:, c].copy()) for c in range(5)], axis=1)
     big = np.max(np.abs(want))
-    for K in (1, 2, 3, 4, 5, 8, 20):
+    for K in (1, 2, 3, 4, 5, 6, 8, 12, 20):
         cols = [c % 5 for c in range(K)]
         x = np.ascontiguousarray(v[:, cols]) if K > 1 else v[:, 0].copy()
         w = want[:, cols] if K > 1 else want[:, 0]
