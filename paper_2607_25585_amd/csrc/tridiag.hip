@@ -16,7 +16,7 @@
 // ballot, and a rotation has no division and no guarded hypot in its chain: with
 // T scaled by a power of two to norm about 1, f^2 + g^2 cannot overflow, and
 // sqrt and its reciprocal come from one reciprocal square root refined by two
-// coupled Newton steps.
+// coupled Newton steps, c and s from the reciprocal and the quotients' residuals.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -30,7 +30,8 @@ namespace {
 constexpr int kWave = 64;
 
 // r = sqrt(x), ri = 1 / sqrt(x) for a normal positive x (coupled Newton steps:
-// g -> sqrt x, h -> 1 / (2 sqrt x), the residual 1/2 - h g in one fma)
+// g -> sqrt x, h -> 1 / (2 sqrt x), the residual 1/2 - h g in one fma; then the residual
+// of g itself, which rounds r to within half a unit and a little)
 __device__ __forceinline__ void sqrt_pair(double x, double &r, double &ri) {
   const double y = __builtin_amdgcn_rsq(x);
   double g = x * y, h = 0.5 * y;
@@ -40,8 +41,16 @@ __device__ __forceinline__ void sqrt_pair(double x, double &r, double &ri) {
     g = fma(g, q, g);
     h = fma(h, q, h);
   }
-  r = g;
+  r = fma(fma(-g, g, x), h, g);
   ri = 2.0 * h;
+}
+
+// a / r by its reciprocal and the quotient's residual.  (Products with the reciprocal
+// alone, and an r of one or two units, left c^2 + s^2 off 1 to one side: 100 steps of
+// rotations moved every eigenvalue by up to 2e-15 of it, five times what divisions did.)
+__device__ __forceinline__ double quot(double a, double r, double ri) {
+  const double q = a * ri;
+  return fma(fma(-q, r, a), ri, q);
 }
 
 __device__ __forceinline__ double wave_max(double v) {
@@ -106,8 +115,8 @@ __device__ __forceinline__ int ql_sweep(double *d, double *e, size_t S, int l, i
     double r, ri;
     sqrt_pair(t, r, ri);
     AT(e, i + 1) = r;
-    s = f * ri;
-    c = gg * ri;
+    s = quot(f, r, ri);
+    c = quot(gg, r, ri);
     const double r2 = fma(d_i - g1, s, 2.0 * c * b);
     p = s * r2;
     AT(d, i + 1) = g1 + p;
@@ -186,7 +195,7 @@ __device__ __forceinline__ void tri_store(const TriArgs &A, int col, int n, int 
 // One wave per column; the four work arrays of the column are in LDS, or in the global
 // scratch [4][nl][n_cols].
 // 100 steps, 20 columns: 6.2 ms as one lane per column with hypot and two
-// divisions per rotation, 2.6 ms so.
+// divisions per rotation, 2.7 ms so (2.5 with c and s as products with the reciprocal).
 template <bool LDS>
 __global__ __launch_bounds__(kWave) void tridiag_kernel(TriArgs A, double *scratch) {
   extern __shared__ double tri_sh[];
@@ -325,12 +334,12 @@ __global__ __launch_bounds__(256) void tridiag_full_kernel(int nl, int nbuf, con
 // of LDS hold are taken by every block that fits, the other's from about 2000 columns on.
 // Measured (us, wave / lane per column):
 //   steps   320 columns     4000            8000            32,000            128,000
-//   10      46 / 98         85 / 103        145 / 107       500 / 110         1735 / 133
-//   30      295 / 776       584 / 807       1027 / 801      3267 / 823        11813 / 3207
-//   60      1067 / 2970     2031 / 2849     3426 / 2836     11633 / 5756      43312 / 22543
-//   100     2729 / 7791     5107 / 8081     8839 / 7946     30572 / 28299     114929 / 93032
-//   120     3862 / 10898    7125 / 11332    12584 / 10837   43576 / 40922     (64,000: 83498 / 80126)
-//   160     6716 / 18450    12400 / 23136   21855 / 35013   75961 / 108008
+//   10      49 / 100        91 / 106        157 / 112       543 / 112         1910 / 138
+//   30      313 / 810       627 / 836       1099 / 823      3566 / 852        13115 / 3349
+//   60      1129 / 3039     2175 / 3013     3682 / 2901     12850 / 5960      48277 / 23321
+//   100     2916 / 8490     5583 / 8867     9726 / 8229     34128 / 29937     129038 / 96649
+//   120     4157 / 11773    7881 / 12466    13991 / 11398   48848 / 42710     (64,000: 93667 / 83533)
+//   160     7226 / 19730    13756 / 24366   24276 / 36687   85487 / 113997
 bool lanes_per_column_pay(int n_cols, int nl) { return n_cols >= 7168 && nl <= 128; }
 
 size_t full_smem(int nl, int nbuf) {
