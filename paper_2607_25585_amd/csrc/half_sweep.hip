@@ -606,23 +606,26 @@ HalfLists plan_half(const std::vector<Cx<double>> &pcoef, WinPlan &plan) {
   return H;
 }
 
-// Doubled site by site: raising site k adds its own difference and the z-field g of the
-// others, g itself doubled over the sites below k.
+// Built site by site: a value of site k adds its own element and its moment times the
+// z-field of the sites below.  (From the row with every site down, each site adding what
+// raising it changes, the table carried roundings of that row's size: products of 18 spins
+// 1/2 with nn + nnn exchange were 1.3 times as far from 64 bits.)
 std::vector<double> half_tile_diagonal(const HostHam &hh, int f) {
   const int n = hh.n, nt = kTileBits - f;
-  std::vector<double> tdiag((size_t)1 << nt, 0.0), g((size_t)1 << nt);
-  for (int k = 0; k < nt; k++) {
-    tdiag[0] += hh.h[(size_t)k * 256].re;
-    for (int j = 0; j < k; j++) tdiag[0] += 0.25 * hh.zz[(size_t)k * n + j];
-  }
+  std::vector<double> tdiag((size_t)1 << nt, 0.0), zf((size_t)1 << nt);
   for (int k = 0; k < nt; k++) {
     const double *z = &hh.zz[(size_t)k * n];
-    g[0] = hh.h[(size_t)k * 256 + 17].re - hh.h[(size_t)k * 256].re;
-    for (int j = 0; j < nt; j++)
-      if (j != k) g[0] -= 0.5 * z[j];
+    const double dn = hh.h[(size_t)k * 256].re, up = hh.h[(size_t)k * 256 + 17].re;
+    zf[0] = 0.0;
     for (int j = 0; j < k; j++)
-      for (int r = 0; r < 1 << j; r++) g[r + (1 << j)] = g[r] + z[j];
-    for (int r = 0; r < 1 << k; r++) tdiag[r + (1 << k)] = tdiag[r] + g[r];
+      for (int r = 0; r < 1 << j; r++) {
+        zf[r + (1 << j)] = zf[r] + 0.5 * z[j];
+        zf[r] -= 0.5 * z[j];
+      }
+    for (int r = 0; r < 1 << k; r++) {
+      tdiag[r + (1 << k)] = tdiag[r] + (up + 0.5 * zf[r]);
+      tdiag[r] += dn - 0.5 * zf[r];
+    }
   }
   return tdiag;
 }
