@@ -22,13 +22,14 @@ def _system(two_s, couple):
                     B=np.array(FIELDS[1]), pos=pos, name=couple)
 
 
-@pytest.mark.parametrize("couple", ["dipolar", "exchange"])
-@pytest.mark.parametrize("two_s,K,variant", [([1] * 13, 1, 5), ([1] * 18, 2, 5), ([1] * 16, 8, 5), ([1] * 15, 16, 5),
-                                             ([5, 4, 4, 4, 4, 4, 3], 1, 6), ([2, 3, 1, 4, 2, 2, 3, 3, 2], 1, 6)])
+# (the tile sweep takes no s+- s^z pieces)
+@pytest.mark.parametrize("two_s,K,variant,couple", [
+    (s, K, 5, c) for s, K in (([1] * 13, 1), ([1] * 18, 2), ([1] * 16, 8), ([1] * 15, 16))
+    for c in ("dipolar", "exchange")] + [
+    ([5, 4, 4, 4, 4, 4, 3], 1, 6, "exchange"), ([2, 3, 1, 4, 2, 2, 3, 3, 2], 1, 6, "exchange"),
+    ([1, 2] * 6, 3, 1, "dipolar"), ([2] * 8, 4, 1, "dipolar"), ([2] * 11, 1, 1, "exchange")])
 def test_products_follow_the_field(two_s, K, variant, couple):
     import paper_2607_25585_amd as F
-    if variant == 6 and couple == "dipolar":
-        pytest.skip("the tile sweep takes no s+- s^z pieces")
     sysm = _system(two_s, couple)
     ham = F.Hamiltonian(sysm)
     rng = np.random.default_rng(1)
