@@ -37,7 +37,8 @@ def _kernel_sha():
     """Hash of the sources that define the H*v kernels (kernels, their shared
     device helpers and internal header)."""
     h = hashlib.sha256()
-    for name in ("kernels.hip", "stream.hip", "hv_common.hpp", "device_reduce.hpp", "ftlm_internal.hpp"):
+    for name in ("kernels.hip", "stream.hip", "sweep.hip", "half_sweep.hip", "half_win.hpp", "hv_common.hpp",
+                 "device_reduce.hpp", "ftlm_internal.hpp"):
         h.update(open(os.path.join(ROOT, "paper_2607_25585_amd", "csrc", name), "rb").read())
     return h.hexdigest()[:16]
 

@@ -30,11 +30,12 @@
 //   6 x 5^8 rows, 20 nonzeros per row    223 -> 121 / 138 -> 74 us
 //   5^12 rows, all pairs (204 per row)   71 -> 39.8 / 42.2 -> 21.6 ms
 //   5^12 rows, nn + nnn (32 per row)     13.8 -> 10.9 / 9.6 -> 5.8 ms
-// What bounds it now is the partner tiles that come from beyond L2 (all pairs, complex128:
-// 141 GB fetched of the 65 vector reads' 254 GB, 3.5 TB/s; nn + nnn 39 GB).  Passes over
-// subsets of the sites whose windows fit an XCD's L2 read a third of that, but took
-// longer (nn + nnn 12.1 -> 13.7 ms at complex128, all pairs 30 -> 35 at complex64):
-// every pass pays the own tile, the tables and a read-add of w.
+// What bounds it now is the partner tiles that come from beyond L2 (8 % of the requests hit
+// there): all pairs, complex128 / complex64, 282 / 144 GB at 7.1 / 6.7 TB/s, nn + nnn 79 GB
+// at 7.2 TB/s, where a copy that stays in the last-level cache moves 6.7 to 7.1; vector units
+// 28 / 51 % busy, LDS 20 / 29 %.  Passes over subsets of the sites whose windows fit an XCD's
+// L2 read a third of that, but took longer (nn + nnn 12.1 -> 13.7 ms at complex128, all pairs
+// 30 -> 35 at complex64): every pass pays the own tile, the tables and a read-add of w.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
