@@ -27,7 +27,7 @@
 //
 // Measured (one product, complex128 / complex64), against the earlier mapping of rows to
 // threads (row = thread + k * block: digits, validity and ladder factors per row):
-//   6 x 5^8 rows, 20 nonzeros per row    223 -> 121 / 138 -> 74 us
+//   6 x 5^8 rows, 20 pairs (51 per row)   223 -> 121 / 138 -> 74 us
 //   5^12 rows, all pairs (204 per row)   71 -> 39.8 / 42.2 -> 21.6 ms
 //   5^12 rows, nn + nnn (32 per row)     13.8 -> 10.9 / 9.6 -> 5.8 ms
 // What bounds it now is the partner tiles that come from beyond L2 (8 % of the requests hit
